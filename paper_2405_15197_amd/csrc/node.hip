@@ -51,12 +51,32 @@ using namespace geo;
 template <typename T>
 struct ArcL {
     T o[3], a[3], b[3];
-    T t1, t2;
+    T t1;
     T dt;            // t2 - t1, kept with its own relative precision
     uint32_t ns, ne; // vertex names at t1 / t2
     int vs, ve;      // local vertex indices
     int p, q, full;
     int nseg, mbase, contour, fbase;
+};
+
+// A kept piece in final form.
+template <typename T>
+struct PieceEnds {
+    T ss, sc, es, ec;  // directions (sin t, cos t) of the ends, unnormalised
+    uint32_t ns, ne;   // names of the ends
+    int p, q, rs, re;  // the conic, and the labels that bound the piece
+    int full;          // the whole conic (both ends its start, t = 0)
+};
+constexpr uint32_t kNoName = 0xffffffffu;
+
+// A lane holds the ends of its one arc; where a lane may have several (one
+// lane per node), they are kept with the node's other data.
+template <typename T, int N>
+struct ArcEnds {
+    PieceEnds<T> ends[N];
+};
+template <typename T>
+struct ArcEnds<T, 0> {
 };
 
 // Lanes per node and per-node capacities of one valence class: W lanes
@@ -76,7 +96,7 @@ using CfgBig = Cfg<kVmaxBig, kAcapBig, kVcapBig, 64 * kBigWaves>;
 using CfgMid = Cfg<kVmaxMid, kAcapMid, kVcapMid, 128>;
 
 template <typename T, typename C>
-struct Shared {
+struct Shared : ArcEnds<T, (C::AC > C::W ? C::AC : 0)> {
     SL<T> S[C::VM + 1];
     ArcL<T> A[C::AC];
     uint32_t vname[C::VC];
@@ -356,23 +376,6 @@ struct Pc {
     int rs, re;  // constraints whose lower / upper end bound the piece
 };
 
-// A kept piece in final form.
-template <typename T>
-struct Piece {
-    T ss, sc, es, ec;  // directions (sin t, cos t) of the ends, unnormalised
-    T len;
-    int rs, re;
-    int roots;  // bit 0: root of the start tie, bit 1: root of the end tie
-};
-
-template <typename T>
-struct TrimOut {
-    int n;        // arcs
-    int full;     // whole conic kept
-    int ovf;      // too many pieces
-    Piece<T> pc[NPieces<T>::n];
-};
-
 // Constraint r on conic (p, q): P_p - P_r = A sin t + B cos t + Cc.  Keeping
 // P_p >= P_r is R cos(t - psi) >= -Cc with psi = atan2(A, B) (Eqs. 8-9),
 // i.e. t - psi in [-beta, beta] with cos beta = -Cc / R.
@@ -517,62 +520,24 @@ __device__ inline void split_steps(TrimRun<float> &st, int kind, int r, float lo
      ...);
 }
 
-// final form: end directions and tie roots of every piece
-template <typename T>
-__device__ inline void trim_finish(const SL<T> *S, int p, int q, const Con<T> &C, V3<T> gp, T hp,
-                                   const TrimRun<T> &st, TrimOut<T> &TR)
-{
-    constexpr int NP = NPieces<T>::n;
-    TR.n = st.n;
-    TR.full = st.full;
-    TR.ovf = st.ovf ? 1 : 0;
-    if (st.full) return;
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        if (i < st.n) {
-            Piece<T> &o = TR.pc[i];
-            T a0, a1, a2, a3;
-            const Cons<T> ks = cons_of(S, gp, hp, st.pc[i].rs, C);
-            cons_ends(ks, o.ss, o.sc, a2, a3);
-            const int root_s = 1 - hi_root(S, p, q, st.pc[i].rs, C, ks);
-            const Cons<T> ke = cons_of(S, gp, hp, st.pc[i].re, C);
-            cons_ends(ke, a0, a1, o.es, o.ec);
-            const int root_e = hi_root(S, p, q, st.pc[i].re, C, ke);
-            o.len = st.pc[i].len;
-            o.rs = st.pc[i].rs;
-            o.re = st.pc[i].re;
-            o.roots = root_s | (root_e << 1);
-        }
-    }
-}
-
-template <typename T>
-__device__ void trim_conic(const SL<T> *S, int v, int p, int q, const Con<T> &C, TrimOut<T> &TR)
-{
-    const V3<T> gp = p ? gvec(S[p]) : zero3<T>();
-    const T hp = p ? S[p].h : (T)0;
-    TrimRun<T> st;
-    for (int r = 0; r <= v; ++r) {
-        if (r == p || r == q) continue;
-        T lo = (T)0, lc = (T)0;
-        const int kind = cons_interval(S, gp, hp, r, C, lo, lc);
-        trim_step(st, kind, lo, lc, r);
-        if (st.done) break;
-    }
-    trim_finish(S, p, q, C, gp, hp, st, TR);
-}
-
-// Conic point at the direction (sin t, cos t) ~ (s, c)
+// Conic point at the direction (sin t, cos t) ~ (s, c).  FP32: the products
+// are fused by hand, so that every schedule of the node pass rounds alike.
 template <typename T>
 __device__ inline V3<T> conic_dir(const Con<T> &C, T s, T c)
 {
-    const T inv = (T)1 / m_sqrt(s * s + c * c);
-    return C.o + C.a * (s * inv) + C.b * (c * inv);
+    if constexpr (sizeof(T) == 4) {
+        const T inv = __builtin_amdgcn_rsqf(fmaf(c, c, s * s)), u = s * inv, w = c * inv;
+        return v3(fmaf(C.b.x, w, fmaf(C.a.x, u, C.o.x)), fmaf(C.b.y, w, fmaf(C.a.y, u, C.o.y)),
+                  fmaf(C.b.z, w, fmaf(C.a.z, u, C.o.z)));
+    } else {
+        const T inv = (T)1 / m_sqrt(s * s + c * c);
+        return C.o + C.a * (s * inv) + C.b * (c * inv);
+    }
 }
 
-// Parameter range [t1, t2] (t1 in [0, 2 pi)) and span of a kept piece
+// Start t1 in [0, 2 pi) and span dt of a kept piece of pseudo length len
 template <typename T>
-__device__ inline void piece_range(const Piece<T> &pc, T &t1, T &t2, T &dt)
+__device__ inline void piece_range(const PieceEnds<T> &pc, T len, T &t1, T &dt)
 {
     const T tp = Cst<T>::two_pi;
     T ts = m_atan2(pc.ss, pc.sc), te = m_atan2(pc.es, pc.ec);
@@ -582,10 +547,9 @@ __device__ inline void piece_range(const Piece<T> &pc, T &t1, T &t2, T &dt)
     if (span < (T)0) span += tp;
     // agree with the pseudo length where rounding puts the ends of an
     // almost empty or almost full piece on the wrong side of each other
-    if (pc.len < (T)1 && span > (T)1.5 * Cst<T>::pi) span = (T)0;
-    if (pc.len > (T)3 && span < (T)0.5 * Cst<T>::pi) span = tp;
+    if (len < (T)1 && span > (T)1.5 * Cst<T>::pi) span = (T)0;
+    if (len > (T)3 && span < (T)0.5 * Cst<T>::pi) span = tp;
     t1 = ts;
-    t2 = ts + span;
     dt = span;
 }
 
@@ -1262,10 +1226,6 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                 q = p + 1 + rem;
             }
             Con<T> C;
-            TrimOut<T> TR;
-            TR.n = 0;
-            TR.full = 0;
-            TR.ovf = 0;
             const bool ell = grp && conic_of(sh.S, rho, p, q, C);
             if (act && !ell) atomicOr(&sh.status, NS_NON_ELLIPTIC);
             // a conic far larger than the node (kept or not): its points and
@@ -1276,144 +1236,203 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                 m_max(dot(C.o, C.o), dot(C.a, C.a)) > (T)(kConicMax * kConicMax) * rho * rho)
                 atomicOr(&sh.status, NS_PREC);
             if (F32 && group_status<WL>(sh)) break;
+            TrimRun<T> st;
             {
                 const V3<T> gp = p ? gvec(sh.S[p]) : zero3<T>();
                 const T hp = p ? sh.S[p].h : (T)0;
-                // split: this lane's constraint, the sub-th label of 0..v
-                // other than p and q (p < q)
-                int myr = sub, mykind = 0;
-                T mylo = (T)0, mylc = (T)0;
-                if (split) {
-                    if (myr >= p) ++myr;
-                    if (myr >= q) ++myr;
-                    if (ell && sub < v - 1) mykind = cons_interval(sh.S, gp, hp, myr, C, mylo, mylc);
-                }
-                const int nsteps = split ? 0 : (act && ell ? v + 1 : 0);
-                TrimRun<T> st;
+                // the j-th label of 0..v other than p and q (p < q)
+                auto other = [&](int j) {
+                    int r = j;
+                    if (r >= p) ++r;
+                    if (r >= q) ++r;
+                    return r;
+                };
                 if constexpr (F32) {
-                    if (split) split_steps(st, mykind, myr, mylo, mylc, std::make_integer_sequence<int, 7>{});
+                    if (split) {
+                        int kind = 0;
+                        T lo = (T)0, lc = (T)0;
+                        const int r = other(sub);
+                        if (ell && sub < v - 1) kind = cons_interval(sh.S, gp, hp, r, C, lo, lc);
+                        split_steps(st, kind, r, lo, lc, std::make_integer_sequence<int, 7>{});
+                    }
                 }
-                for (int s2 = 0; s2 < nsteps; ++s2) {
-                    int k2 = 0;
-                    T lo2 = (T)0, lc2 = (T)0;
-                    if (s2 != p && s2 != q) k2 = cons_interval(sh.S, gp, hp, s2, C, lo2, lc2);
-                    trim_step(st, k2, lo2, lc2, s2);
+                const int nsteps = split ? 0 : (act && ell ? v - 1 : 0);
+                for (int j = 0; j < nsteps; ++j) {
+                    const int r = other(j);
+                    T lo = (T)0, lc = (T)0;
+                    const int kind = cons_interval(sh.S, gp, hp, r, C, lo, lc);
+                    trim_step(st, kind, lo, lc, r);
                     if (st.done) break;
                 }
-                if (act && ell) {
-                    trim_finish(sh.S, p, q, C, gp, hp, st, TR);
-                    if (TR.ovf) atomicOr(&sh.status, F32 ? NS_PREC : NS_CAPACITY);
-                }
             }
-            // arcs of this conic, sorted by the smaller endpoint name
-            uint32_t ns_[NP], ne_[NP], key[NP];
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                if (TR.full) {
-                    ns_[i] = ne_[i] = vname3(p, q, 255, 0);
-                } else {
-                    ns_[i] = tie_name(p, q, TR.pc[i].rs, TR.pc[i].roots & 1);
-                    ne_[i] = tie_name(p, q, TR.pc[i].re, (TR.pc[i].roots >> 1) & 1);
-                }
-                key[i] = i < TR.n ? (ns_[i] < ne_[i] ? ns_[i] : ne_[i]) : 0xffffffffu;
+            int cnt = 0;
+            if (act && ell) {
+                cnt = st.n;
+                if (st.ovf) atomicOr(&sh.status, F32 ? NS_PREC : NS_CAPACITY);
             }
-            int ord[NP];
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                int rank = 0;
-#pragma unroll
-                for (int j = 0; j < NP; ++j) rank += (key[j] < key[i]) || (key[j] == key[i] && j < i);
-                ord[i] = rank;
-            }
-            int cnt = act ? TR.n : 0, tot;
-            int base = group_excl_scan<WL>(cnt, &tot) + sh.n_arc;
-            if (sh.n_arc + tot > CF::AC) {
+            int tot;
+            const int have = sh.n_arc;
+            const int base = group_excl_scan<WL>(cnt, &tot) + have;
+            const bool fits = have + tot <= CF::AC;
+            if (!fits) {
                 if (lane == 0) atomicOr(&sh.status, NS_CAPACITY);
             } else {
 #pragma unroll
                 for (int i = 0; i < NP; ++i) {
                     if (i < cnt) {
-                        ArcL<T> &A = sh.A[base + ord[i]];
+                        ArcL<T> &A = sh.A[base + i];
                         A.o[0] = C.o.x; A.o[1] = C.o.y; A.o[2] = C.o.z;
                         A.a[0] = C.a.x; A.a[1] = C.a.y; A.a[2] = C.a.z;
                         A.b[0] = C.b.x; A.b[1] = C.b.y; A.b[2] = C.b.z;
-                        A.p = p; A.q = q; A.full = TR.full;
-                        if (TR.full) {
-                            A.t1 = (T)0;
-                            A.t2 = tp;
-                            A.dt = tp;
-                        } else {
-                            piece_range(TR.pc[i], A.t1, A.t2, A.dt);
-                        }
-                        A.ns = ns_[i];
-                        A.ne = ne_[i];
+                        A.p = p; A.q = q; A.full = st.full;
+                        // for the next section: the labels that bound the
+                        // piece, its length, its place among its conic's
+                        A.vs = st.pc[i].rs;
+                        A.ve = st.pc[i].re;
+                        A.dt = st.pc[i].len;
+                        A.contour = i | (cnt << 8);
                     }
                 }
             }
-            // owned vertices: ties (p, q, r) with r > q, and whole-conic starts
-            uint32_t on[2 * NP];
-            T os_[2 * NP], oc_[2 * NP];
-            int orr[2 * NP];
-            int own = 0;
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-#pragma unroll
-                for (int end = 0; end < 2; ++end) {
-                    bool mine = false;
-                    uint32_t nm = 0;
-                    T ds = (T)0, dc = (T)1;  // direction of the point: t = 0 for a whole conic
-                    int r = -1;
-                    if (i < cnt) {
-                        if (TR.full) {
-                            mine = (end == 0 && i == 0);
-                            nm = ns_[i];
-                        } else {
-                            r = end ? TR.pc[i].re : TR.pc[i].rs;
-                            mine = r > q;
-                            nm = end ? ne_[i] : ns_[i];
-                            ds = end ? TR.pc[i].es : TR.pc[i].ss;
-                            dc = end ? TR.pc[i].ec : TR.pc[i].sc;
-                        }
-                    }
-                    // drop repeats within the conic (degenerate tangencies)
-#pragma unroll
-                    for (int j = 0; j < 2 * NP; ++j)
-                        if (j < own && on[j] == nm) mine = false;
-#pragma unroll
-                    for (int j = 0; j < 2 * NP; ++j)
-                        if (mine && j == own) { on[j] = nm; os_[j] = ds; oc_[j] = dc; orr[j] = r; }
-                    if (mine) ++own;
-                }
-            }
-            int ntot;
-            int vbase = group_excl_scan<WL>(own, &ntot) + sh.n_vert;
-            if (sh.n_vert + ntot > CF::VC) {
-                if (lane == 0) atomicOr(&sh.status, NS_CAPACITY);
+            __syncthreads();
+            if (lane == 0 && fits) sh.n_arc = have + tot;
+            __syncthreads();
+        }
+    }
+    if (group_status<WL>(sh) & (F32 ? ~0 : NS_CAPACITY)) goto tail;
+
+    // ---- arcs (names and parameters of their ends) and owned vertices -------
+    // Lanes over the kept pieces, which are about half as many as the conics
+    // (18 of 36 at a BCC node) and come from every round: one pass, one piece
+    // per lane, and no trimming state held across it.  Finishing each round's
+    // conics in place, with every lane ready for the most pieces, took 168
+    // VGPRs in FP32 and all 256 in FP64, with spills; now 139 and 186, no
+    // spills.  BCC 64^3, k = 16: step 4.21 -> 3.94 ms; sink BCC 128^3, k = 12:
+    // 29.0 -> 26.7 ms; 24 mixed parts, mostly FP64: 3.47 -> 3.18 ms.
+    {
+        constexpr bool ONE = CF::AC <= WL;  // a lane has at most one arc
+        const int E = sh.n_arc;
+        uint32_t *own_name = (uint32_t *)sh.entry_off;  // [2 E], free until the loops
+        auto ends_of = [&](int j) {
+            const ArcL<T> &A = sh.A[j];
+            PieceEnds<T> en;
+            en.p = A.p;
+            en.q = A.q;
+            en.rs = A.vs;
+            en.re = A.ve;
+            en.full = A.full;
+            if (en.full) {
+                en.ns = en.ne = vname3(en.p, en.q, 255, 0);
+                en.ss = en.es = (T)0;  // t = 0
+                en.sc = en.ec = (T)1;
             } else {
+                const Con<T> C = arc_con(A);
+                const V3<T> gp = en.p ? gvec(sh.S[en.p]) : zero3<T>();
+                const T hp = en.p ? sh.S[en.p].h : (T)0;
+                T u0, u1;
+                const Cons<T> ks = cons_of(sh.S, gp, hp, en.rs, C);
+                cons_ends(ks, en.ss, en.sc, u0, u1);
+                const Cons<T> ke = cons_of(sh.S, gp, hp, en.re, C);
+                cons_ends(ke, u0, u1, en.es, en.ec);
+                en.ns = tie_name(en.p, en.q, en.rs, 1 - hi_root(sh.S, en.p, en.q, en.rs, C, ks));
+                en.ne = tie_name(en.p, en.q, en.re, hi_root(sh.S, en.p, en.q, en.re, C, ke));
+            }
+            return en;
+        };
+        PieceEnds<T> en{};
+        for (int j = lane; j < E; j += WL) {
+            en = ends_of(j);
+            if constexpr (!ONE) sh.ends[j] = en;
+            ArcL<T> &A = sh.A[j];
+            if (en.full) {
+                A.t1 = (T)0;
+                A.dt = tp;
+            } else {
+                piece_range(en, A.dt, A.t1, A.dt);
+            }
+            A.ns = en.ns;
+            A.ne = en.ne;
+            // owned: ties (p, q, r) with r > q, and whole-conic starts
+            own_name[2 * j] = en.full || en.rs > en.q ? en.ns : kNoName;
+            own_name[2 * j + 1] = !en.full && en.re > en.q ? en.ne : kNoName;
+        }
+        __syncthreads();
+        int vt = 0;
+        for (int j0 = 0; j0 < E; j0 += WL) {
+            const int j = j0 + lane;
+            const bool act = j < E;
+            if constexpr (!ONE) en = sh.ends[j];
+            uint32_t nm[2] = {kNoName, kNoName};
+            int rank[2] = {0, 0}, before = 0;
+            if (act) {
+                const int place = sh.A[j].contour & 0xff, n = sh.A[j].contour >> 8;
+                nm[0] = own_name[2 * j];
+                nm[1] = own_name[2 * j + 1];
+                if (n == 1) {
+                    if (nm[1] == nm[0]) nm[1] = kNoName;  // a repeat (degenerate tangency)
+                    rank[0] = nm[1] < nm[0];
+                    rank[1] = nm[0] < nm[1];
+                } else {
+                    // several pieces of one conic: the owned names of all of
+                    // them in order, each once (where it comes first)
+                    const uint32_t *g = own_name + 2 * (j - place);
+                    for (int x = 0; x < 2 * n; ++x) {
+                        const uint32_t nx = g[x];
+                        bool first = nx != kNoName;
+                        for (int y = 0; y < x; ++y) first = first && g[y] != nx;
+                        if (!first) {
+                            if (x == 2 * place) nm[0] = kNoName;
+                            if (x == 2 * place + 1) nm[1] = kNoName;
+                            continue;
+                        }
+                        before += x < 2 * place;
+                        rank[0] += nx < g[2 * place];
+                        rank[1] += nx < g[2 * place + 1];
+                    }
+                }
+            }
+            const int own = (nm[0] != kNoName) + (nm[1] != kNoName);
+            int tot;
+            const int vbase = group_excl_scan<WL>(own, &tot) + vt - before;
+            vt += tot;
+            if (vt <= CF::VC) {
 #pragma unroll
-                for (int i = 0; i < 2 * NP; ++i) {
-                    if (i < own) {
-                        int rank = 0;
-#pragma unroll
-                        for (int j = 0; j < 2 * NP; ++j) rank += (j < own) && (on[j] < on[i]);
-                        V3<T> w = conic_dir(C, os_[i], oc_[i]);
-                        sh.vname[vbase + rank] = on[i];
-                        sh.vx[vbase + rank] = w.x;
-                        sh.vy[vbase + rank] = w.y;
-                        sh.vz[vbase + rank] = w.z;
-                        if (F32 && orr[i] >= 0 && !tie_trusted(sh.S, p, q, orr[i], w, rho, (T)P.kappa_max))
+                for (int e = 0; e < 2; ++e) {
+                    if (nm[e] != kNoName) {
+                        const V3<T> w = conic_dir(arc_con(sh.A[j]), e ? en.es : en.ss, e ? en.ec : en.sc);
+                        const int at = vbase + rank[e];
+                        sh.vname[at] = nm[e];
+                        sh.vx[at] = w.x;
+                        sh.vy[at] = w.y;
+                        sh.vz[at] = w.z;
+                        if (F32 && !en.full &&
+                            !tie_trusted(sh.S, en.p, en.q, e ? en.re : en.rs, w, rho, (T)P.kappa_max))
                             atomicOr(&sh.status, NS_PREC);
                     }
                 }
             }
-            __syncthreads();
-            // advance the running counts (tot / ntot are wave-uniform)
-            if (lane == 0) {
-                if (sh.n_arc + tot <= CF::AC) sh.n_arc += tot;
-                if (sh.n_vert + ntot <= CF::VC) sh.n_vert += ntot;
-            }
-            __syncthreads();
         }
+        __syncthreads();
+        if (lane == 0) {
+            sh.n_vert = vt;
+            if (vt > CF::VC) atomicOr(&sh.status, NS_CAPACITY);
+        }
+        // the arcs of a conic by their smaller end name
+        for (int j = lane; j < E; j += WL) {
+            if (sh.A[j].contour & 0xff) continue;
+            const int n = sh.A[j].contour >> 8;
+            for (int x = 1; x < n; ++x)
+                for (int y = j + x; y > j; --y) {
+                    ArcL<T> &a0 = sh.A[y - 1], &a1 = sh.A[y];
+                    const uint32_t k0 = a0.ns < a0.ne ? a0.ns : a0.ne, k1 = a1.ns < a1.ne ? a1.ns : a1.ne;
+                    if (k0 <= k1) break;
+                    const uint32_t ns = a0.ns, ne = a0.ne;
+                    const T t1 = a0.t1, dt = a0.dt;
+                    a0.ns = a1.ns; a0.ne = a1.ne; a0.t1 = a1.t1; a0.dt = a1.dt;
+                    a1.ns = ns; a1.ne = ne; a1.t1 = t1; a1.dt = dt;
+                }
+        }
+        __syncthreads();
     }
     if (group_status<WL>(sh)) goto tail;
 
@@ -1718,7 +1737,6 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
         }
         A.t1 = __uint_as_float(aw[9]);
         A.dt = __uint_as_float(aw[10]);
-        A.t2 = A.t1 + A.dt;
         const uint32_t u0 = aw[11], u1 = aw[12], u2 = aw[13];
         A.p = (int)(u0 & 0xffu);
         A.q = (int)((u0 >> 8) & 0xffu);
