@@ -230,11 +230,11 @@ __device__ inline int group_excl_scan(int x, int *total)
 // x of lane 8 g + S in the lane's group g of 8 lanes (row_newbcast:n sends
 // lane n of each row of 16 to the whole row)
 template <int S>
-__device__ inline int group8_lane(int x)
+__device__ inline float group8_lane(float x)
 {
-    const int a = __builtin_amdgcn_update_dpp(0, x, 0x150 + S, 0xf, 0xf, false);
-    const int b = __builtin_amdgcn_update_dpp(0, x, 0x158 + S, 0xf, 0xf, false);
-    return (threadIdx.x & 8) ? b : a;
+    const int a = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + S, 0xf, 0xf, true);
+    const int b = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x158 + S, 0xf, 0xf, true);
+    return __int_as_float((threadIdx.x & 8) ? b : a);
 }
 
 template <int W>
@@ -349,6 +349,15 @@ __device__ inline void over_lanes(int lane, int lo, int hi, F &&f)
     }
 }
 
+// Entry of label m in the node's strut table; entry 0 (the nodal sphere,
+// P_0 = 0) has g = 0 and h = 0.  Labels are small: the offset is a 24-bit
+// product, at full rate where a 32-bit one takes four issue slots.
+template <typename T>
+__device__ __forceinline__ const SL<T> &strut(const SL<T> *S, int m)
+{
+    return *(const SL<T> *)((const char *)S + __umul24((unsigned)m, (unsigned)sizeof(SL<T>)));
+}
+
 // ---------------------------------------------------------------------------
 // trimming of one conic: intersection of circular intervals
 
@@ -376,6 +385,19 @@ struct Pc {
     int rs, re;  // constraints whose lower / upper end bound the piece
 };
 
+// Labels p < q of the ci-th conic in lexicographic order of a node of v
+// struts: p v - p (p - 1) / 2 conics come before (p, p + 1).  The root is
+// within rounding of the row, one step either way makes it exact.
+__device__ __forceinline__ void conic_labels(int ci, int v, int &p, int &q)
+{
+    const float b = (float)(2 * v + 1);
+    auto before = [&](int i) { return __mul24(i, 2 * v + 1 - i) >> 1; };
+    p = (int)(0.5f * (b - __builtin_amdgcn_sqrtf(b * b - 8.f * (float)ci)));
+    if (before(p) > ci) --p;
+    if (before(p + 1) <= ci) ++p;
+    q = p + 1 + ci - before(p);
+}
+
 // Constraint r on conic (p, q): P_p - P_r = A sin t + B cos t + Cc.  Keeping
 // P_p >= P_r is R cos(t - psi) >= -Cc with psi = atan2(A, B) (Eqs. 8-9),
 // i.e. t - psi in [-beta, beta] with cos beta = -Cc / R.
@@ -387,13 +409,12 @@ struct Cons {
 template <typename T>
 __device__ inline Cons<T> cons_of(const SL<T> *S, V3<T> gp, T hp, int r, const Con<T> &C)
 {
-    V3<T> gr = r ? gvec(S[r]) : zero3<T>();
-    T hr = r ? S[r].h : (T)0;
-    V3<T> dg = gp - gr;
+    const SL<T> &Sr = strut(S, r);
+    V3<T> dg = gp - gvec(Sr);
     Cons<T> k;
     k.A = dot(dg, C.a);
     k.B = dot(dg, C.b);
-    k.Cc = dot(dg, C.o) - (hp - hr);
+    k.Cc = dot(dg, C.o) - (hp - Sr.h);
     k.R = m_sqrt(k.A * k.A + k.B * k.B);
     return k;
 }
@@ -418,8 +439,8 @@ template <typename T>
 __device__ inline int hi_root(const SL<T> *S, int p, int q, int r, const Con<T> &C, const Cons<T> &k)
 {
     const Tri3 xyz = sort3(p, q, r);
-    V3<T> gx = xyz.x ? gvec(S[xyz.x]) : zero3<T>();
-    V3<T> d = cross(gx - gvec(S[xyz.y]), gx - gvec(S[xyz.z]));
+    const V3<T> gx = gvec(strut(S, xyz.x));
+    V3<T> d = cross(gx - gvec(strut(S, xyz.y)), gx - gvec(strut(S, xyz.z)));
     return dot(C.a * k.B - C.b * k.A, d) > (T)0 ? 1 : 0;
 }
 
@@ -453,8 +474,8 @@ __device__ inline int cons_interval(const SL<T> *S, V3<T> gp, T hp, int r, const
 template <typename T>
 struct TrimRun {
     Pc<T> pc[NPieces<T>::n];
-    int n = 1, full = 1;
-    bool ovf = false, done = false;
+    int n = 1, full = 1;  // n == 0: nothing is kept
+    bool ovf = false;
 };
 
 template <typename T>
@@ -462,11 +483,10 @@ __device__ inline void trim_step(TrimRun<T> &st, int kind, T lo, T lc, int r)
 {
     constexpr int NP = NPieces<T>::n;
     const T tp = (T)4;
-    if (st.done || kind == 0) return;
+    if (st.n == 0 || kind == 0) return;
     if (kind == 1) {
         st.n = 0;
         st.full = 0;
-        st.done = true;
         return;
     }
     if (st.full) {
@@ -506,19 +526,77 @@ __device__ inline void trim_step(TrimRun<T> &st, int kind, T lo, T lc, int r)
     st.n = no;
 #pragma unroll
     for (int j = 0; j < NP; ++j) st.pc[j] = out[j];
-    if (no == 0) st.done = true;
 }
 
-// Split trimming round: the constraint of lane S of the group (kind, label,
-// interval) intersected in constraint order, S = 0 .. 6
-template <int... S>
-__device__ inline void split_steps(TrimRun<float> &st, int kind, int r, float lo, float lc,
+// Piece P cut to [lo, lo + lc]: A, from lo on (or P's own start), when a; then
+// B, from P's start to the interval's end, when b (the interval wraps around
+// to it).
+__device__ __forceinline__ void cut_piece(const Pc<float> &P, float lo, float lc, int r, Pc<float> &A, bool &a,
+                                          Pc<float> &B, bool &b)
+{
+    float c0 = lo - P.s;
+    c0 = c0 < 0.f ? c0 + 4.f : c0;
+    const float c1 = c0 + lc, w1 = c1 - 4.f;
+    const bool ns = c0 > 0.f, ne = c1 < P.len, nw = w1 < P.len;
+    a = c0 < P.len;
+    b = c1 > 4.f;
+    A = Pc<float>{ns ? lo : P.s, (ne ? c1 : P.len) - c0, ns ? r : P.rs, ne ? r : P.re};
+    B = Pc<float>{P.s, nw ? w1 : P.len, P.rs, nw ? r : P.re};
+}
+
+// FP32, at most two pieces: the same step without a branch for a conic that
+// holds one (selects where the loop over pieces and outputs above branches
+// on each: the trimming loop is bound by instruction issue).  A second piece
+// is cut in a branch of its own.  With label 0 in the strut table and 24-bit
+// offsets, the conics of a BCC node pair take 14.9 k cycles instead of 19.5 k,
+// those of an octet node 26.7 k instead of 34.5 k (k = 16; BCC 64^3 step 3.94
+// -> 3.81 ms, sink BCC 128^3 26.7 -> 25.5 ms).
+__device__ __forceinline__ void trim_step(TrimRun<float> &st, int kind, float lo, float lc, int r)
+{
+    Pc<float> A, B;
+    bool a, b;
+    cut_piece(st.pc[0], lo, lc, r, A, a, B, b);
+    const bool whole = st.full != 0;
+    a = whole || a;
+    b = !whole && b;
+    A.s = whole ? lo : A.s;
+    A.len = whole ? lc : A.len;
+    A.rs = whole ? r : A.rs;
+    A.re = whole ? r : A.re;
+    Pc<float> q0{a ? A.s : B.s, a ? A.len : B.len, a ? A.rs : B.rs, a ? A.re : B.re}, q1 = B;
+    int n = (a ? 1 : 0) + (b ? 1 : 0);
+    if (st.n == 2 && kind == 2) {
+        cut_piece(st.pc[1], lo, lc, r, A, a, B, b);
+        const Pc<float> f{a ? A.s : B.s, a ? A.len : B.len, a ? A.rs : B.rs, a ? A.re : B.re};
+        const int m = (a ? 1 : 0) + (b ? 1 : 0);
+        if (n < 2) q1 = n == 0 ? B : f;
+        if (n == 0) q0 = f;
+        n += m;
+        if (n > 2) {
+            n = 2;
+            st.ovf = true;
+        }
+    }
+    if (kind != 0 && st.n != 0) {
+        st.pc[0] = q0;
+        st.pc[1] = q1;
+        st.n = kind == 1 ? 0 : n;
+        st.full = 0;
+    }
+}
+
+// Split trimming round: the kept sets of the lanes of the group (start and
+// length, see kept_code) intersected in constraint order, S = 0 .. 6
+template <typename R, int... S>
+__device__ inline void split_steps(TrimRun<float> &st, float lo, float code, R &&label,
                                    std::integer_sequence<int, S...>)
 {
-    (trim_step(st, group8_lane<S>(kind), __int_as_float(group8_lane<S>(__float_as_int(lo))),
-               __int_as_float(group8_lane<S>(__float_as_int(lc))), group8_lane<S>(r)),
-     ...);
+    auto step = [&](float l, float c, int r) { trim_step(st, c < 0.f ? 1 : (c > 4.f ? 0 : 2), l, c, r); };
+    (step(group8_lane<S>(lo), group8_lane<S>(code), label(S)), ...);
 }
+// a kept set's length, beyond a turn for a constraint that is never active,
+// negative where nothing is kept
+__device__ inline float kept_code(int kind, float lc) { return kind == 2 ? lc : (kind ? -1.f : 8.f); }
 
 // Conic point at the direction (sin t, cos t) ~ (s, c).  FP32: the products
 // are fused by hand, so that every schedule of the node pass rounds alike.
@@ -1170,6 +1248,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         sh.fsum = 0;
         sh.ncirc = 0;
         sh.rec = -1;
+        sh.S[0].gx = sh.S[0].gy = sh.S[0].gz = sh.S[0].h = (T)0;
     }
     __syncthreads();
     if (v == 0 || v > CF::VM) {
@@ -1207,24 +1286,23 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
 
     // ---- conics, trimming, arcs and owned vertices ------------------------
     {
+        // two nodes per wave: 36 conics at v = 8 for 32 lanes.  (Four per wave
+        // have at most 10 for 16 lanes, one per wave 36 for 64.)
+        constexpr bool SPLIT = F32 && WL == 32;
         const int nconic = v * (v + 1) / 2;
         for (int c0 = 0; c0 < nconic;) {
             // A last round of at most WL / 8 conics (v <= 8: at most 7
             // constraints each) runs on 8 lanes per conic, one constraint per
-            // lane; the conic's first lane intersects the kept sets in
+            // lane; the conic's first lane then intersects the kept sets in
             // constraint order.  Otherwise one lane per conic.
-            const bool split = F32 && WL >= 16 && v <= 8 && (nconic - c0) * 8 <= WL;
+            const bool split = SPLIT && v <= 8 && (nconic - c0) * 8 <= WL;
             const int ci = split ? c0 + (lane >> 3) : c0 + lane;
             const int sub = split ? (lane & 7) : 0;
             const bool grp = ci < nconic;
             const bool act = grp && sub == 0;
             c0 += split ? WL / 8 : WL;
             int p = 0, q = 0;
-            if (grp) {
-                int rem = ci;
-                while (rem >= v - p) { rem -= v - p; ++p; }
-                q = p + 1 + rem;
-            }
+            if (grp) conic_labels(ci, v, p, q);
             Con<T> C;
             const bool ell = grp && conic_of(sh.S, rho, p, q, C);
             if (act && !ell) atomicOr(&sh.status, NS_NON_ELLIPTIC);
@@ -1238,8 +1316,8 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             if (F32 && group_status<WL>(sh)) break;
             TrimRun<T> st;
             {
-                const V3<T> gp = p ? gvec(sh.S[p]) : zero3<T>();
-                const T hp = p ? sh.S[p].h : (T)0;
+                const V3<T> gp = gvec(strut(sh.S, p));
+                const T hp = strut(sh.S, p).h;
                 // the j-th label of 0..v other than p and q (p < q)
                 auto other = [&](int j) {
                     int r = j;
@@ -1247,22 +1325,21 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                     if (r >= q) ++r;
                     return r;
                 };
-                if constexpr (F32) {
+                if constexpr (SPLIT) {
                     if (split) {
                         int kind = 0;
                         T lo = (T)0, lc = (T)0;
-                        const int r = other(sub);
-                        if (ell && sub < v - 1) kind = cons_interval(sh.S, gp, hp, r, C, lo, lc);
-                        split_steps(st, kind, r, lo, lc, std::make_integer_sequence<int, 7>{});
+                        if (ell && sub < v - 1) kind = cons_interval(sh.S, gp, hp, other(sub), C, lo, lc);
+                        split_steps(st, lo, kept_code(kind, lc), other, std::make_integer_sequence<int, 7>{});
                     }
                 }
-                const int nsteps = split ? 0 : (act && ell ? v - 1 : 0);
+                const int nsteps = !split && act && ell ? v - 1 : 0;
                 for (int j = 0; j < nsteps; ++j) {
                     const int r = other(j);
                     T lo = (T)0, lc = (T)0;
                     const int kind = cons_interval(sh.S, gp, hp, r, C, lo, lc);
                     trim_step(st, kind, lo, lc, r);
-                    if (st.done) break;
+                    if (st.n == 0) break;
                 }
             }
             int cnt = 0;
@@ -1327,8 +1404,8 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                 en.sc = en.ec = (T)1;
             } else {
                 const Con<T> C = arc_con(A);
-                const V3<T> gp = en.p ? gvec(sh.S[en.p]) : zero3<T>();
-                const T hp = en.p ? sh.S[en.p].h : (T)0;
+                const V3<T> gp = gvec(strut(sh.S, en.p));
+                const T hp = strut(sh.S, en.p).h;
                 T u0, u1;
                 const Cons<T> ks = cons_of(sh.S, gp, hp, en.rs, C);
                 cons_ends(ks, en.ss, en.sc, u0, u1);
