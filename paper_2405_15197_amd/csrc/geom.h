@@ -62,9 +62,9 @@ struct SL {
     T gx, gy, gz, h;   // P_m(w) = g . w - h
     T ex, ey, ez, sig; // unit direction node -> far node, sigma
     T rx, ry, rz, kap; // strut frame r, kappa
-    T qx, qy, qz, len; // strut frame q, length
+    T qx, qy, qz;      // strut frame q
     T sx, sy, sz;      // canonical strut direction (lower -> higher node id)
-    int lower, sid, far;
+    int lower, far;
 };
 
 template <typename T>
@@ -89,7 +89,7 @@ __device__ inline SL<T> strut_entry(V3<T> cen, T rho, V3<T> cf, T rf, int lower,
     }
     T kap = m_sqrt(((T)1 - sig) * ((T)1 + sig));
     V3<T> e = d * ((T)1 / L);
-    s.ex = e.x; s.ey = e.y; s.ez = e.z; s.sig = sig; s.kap = kap; s.len = L;
+    s.ex = e.x; s.ey = e.y; s.ez = e.z; s.sig = sig; s.kap = kap;
     s.gx = e.x / kap; s.gy = e.y / kap; s.gz = e.z / kap;
     s.h = rho * sig / kap;
     s.lower = lower;

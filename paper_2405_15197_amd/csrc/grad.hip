@@ -369,7 +369,6 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         const float4 f4 = W.node4[he.x];
         bool bad;
         SL<float> s = strut_entry(cen, rho, v3(f4.x, f4.y, f4.z), f4.w, (int)((int64_t)he.x > n), bad);
-        s.sid = he.y;
         s.far = he.x;
         S[lane + 1] = s;
     }

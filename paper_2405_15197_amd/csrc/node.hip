@@ -54,10 +54,13 @@ struct ArcL {
     T t1;
     T dt;            // t2 - t1, kept with its own relative precision
     uint32_t ns, ne; // vertex names at t1 / t2
-    int vs, ve;      // local vertex indices
-    int p, q, full;
-    int nseg, mbase, contour, fbase;
+    int mbase, fbase;
+    uint16_t nseg;       // at most k <= 4096
+    uint8_t vs, ve;      // local vertex indices
+    uint8_t p, q, full;
+    uint8_t contour;     // kNone: not on a hole
 };
+constexpr int kNone = 255;  // above every vertex and contour index
 
 // A kept piece in final form.
 template <typename T>
@@ -85,7 +88,9 @@ template <int VM_, int AC_, int VC_, int W_>
 struct Cfg {
     static constexpr int VM = VM_, AC = AC_, VC = VC_, W = W_;
 };
-using CfgV4 = Cfg<4, 16, 16, 16>;   // v <= 4: four nodes per wave
+// v <= 4: four nodes per wave (16 arcs have at most 12 vertices: three arcs
+// meet at one, and at most four are whole conics with one of their own)
+using CfgV4 = Cfg<4, 16, 12, 16>;
 using CfgV8 = Cfg<8, 32, 24, 32>;   // v <= 8: two nodes per wave
 using CfgV16 = Cfg<kVmax, kAcap, kVcap, 64>;
 // v = kVmax + 1 .. kVmaxBig: one node per block of kBigWaves waves, lanes of
@@ -101,26 +106,42 @@ struct Shared : ArcEnds<T, (C::AC > C::W ? C::AC : 0)> {
     ArcL<T> A[C::AC];
     uint32_t vname[C::VC];
     T vx[C::VC], vy[C::VC], vz[C::VC];
-    uint8_t loop_arc[2 * C::AC];
-    int8_t loop_dir[2 * C::AC];
-    uint8_t loop_ord[2 * C::AC];
+    // Parts of the pass that follow one another share their space: with it a
+    // block stays below the 10 KB at which sixteen of them fit a compute unit.
+    union {
+        struct {  // until the loop samples are laid out
+            uint8_t loop_arc[2 * C::AC];
+            int8_t loop_dir[2 * C::AC];
+            uint8_t loop_ord[2 * C::AC];
+        };
+        T ph_last[2 * C::AC];  // phi key of the last sample of the entry of each arc and side
+    };
+    T ph_first[2 * C::AC];    // ... and of its first sample
     int loop_base[C::VM + 2];
     int loop_len[C::VM + 1];  // samples |L_m|
-    int loop_cnt[C::VM + 1];  // arcs per loop, then fill cursor
-    int loop_first[C::VM + 1];
-    int loop_full[C::VM + 1];
-    uint16_t loop_next[2 * C::AC];
-    int vdeg[C::VC];
-    uint32_t clabel[C::AC];
-    T hc[C::AC][3];           // hole centre (local) per contour
-    int entry_off[2 * C::AC + 1];   // first loop sample of each loop entry
-    uint8_t entry_m[2 * C::AC];     // strut label of each loop entry
+    union {
+        int loop_cnt[C::VM + 1];   // arcs per loop, then fill cursor
+        int loop_desc[C::VM + 1];  // descents of phi along each loop
+    };
+    union {
+        int loop_first[C::VM + 1];
+        int loop_rot[C::VM + 1];  // loop position of the smallest phi
+    };
+    union {
+        int loop_full[C::VM + 1];
+        int lbase[C::VM + 1];  // loop samples before each strut's loop
+    };
+    union {
+        struct {  // until the hole contours are known
+            uint16_t loop_next[2 * C::AC];
+            int vdeg[C::VC];
+            uint32_t clabel[C::AC];
+        };
+        T hc[C::AC][3];  // hole centre (local) per contour
+    };
+    int entry_off[2 * C::AC];       // first loop sample of the entry of each arc and side
+    uint8_t entry_m[2 * C::AC];     // strut label of each loop entry, in loop order
     uint16_t entry_arc[2 * C::AC];  // arc of each loop entry | 0x8000 when run forward
-    int loop_desc[C::VM + 1];       // descents of phi along each loop
-    int loop_rot[C::VM + 1];        // loop position of the smallest phi
-    T ph_first[C::VM + 1], ph_last[C::VM + 1];  // phi keys of each loop's ends
-    int lbase[C::VM + 2];           // loop samples before each strut's loop
-    uint8_t wmark[C::W <= 64 ? C::W : 1];  // loop entries starting in a window of samples
     int status, n_arc, n_vert, n_contour;
     int wsum, fsum, ncirc;
     int64_t rec;                    // first word of the node record, -1: none
@@ -194,6 +215,20 @@ __device__ inline int group_last_lane(int x)
     }
 }
 
+// OR over the group's W = 16, 32 or 64 lanes, for every lane
+template <int W>
+__device__ inline uint32_t group_or(uint32_t m)
+{
+    int x = (int)m;
+    x |= dpp_move<kDppRowShr + 1>(x);
+    x |= dpp_move<kDppRowShr + 2>(x);
+    x |= dpp_move<kDppRowShr + 4>(x);
+    x |= dpp_move<kDppRowShr + 8>(x);
+    if constexpr (W >= 32) x |= dpp_move<kDppBcast15, 0xa>(x);
+    if constexpr (W >= 64) x |= dpp_move<kDppBcast31, 0xc>(x);
+    return (uint32_t)group_last_lane<W>(x);
+}
+
 // exclusive scan over the W lanes of a node; every lane of the group must
 // call it.  A group wider than a wave (the whole block) combines the waves'
 // totals through LDS.
@@ -227,14 +262,26 @@ __device__ inline int group_excl_scan(int x, int *total)
     }
 }
 
-// x of lane 8 g + S in the lane's group g of 8 lanes (row_newbcast:n sends
-// lane n of each row of 16 to the whole row)
-template <int S>
-__device__ inline float group8_lane(float x)
+// x of lane L g + S in the lane's group g of L lanes: quad_perm within four,
+// row_newbcast:n (lane n of each row of 16 to the whole row) for eight
+template <int L, int S>
+__device__ inline int sub_lane(int x)
 {
-    const int a = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + S, 0xf, 0xf, true);
-    const int b = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x158 + S, 0xf, 0xf, true);
-    return __int_as_float((threadIdx.x & 8) ? b : a);
+    static_assert(L == 4 || L == 8, "groups of 4 or 8 lanes");
+    if constexpr (L == 4) {
+        return __builtin_amdgcn_mov_dpp(x, S * 0x55, 0xf, 0xf, true);
+    } else {
+        const int a = __builtin_amdgcn_mov_dpp(x, 0x150 + S, 0xf, 0xf, true);
+        const int b = __builtin_amdgcn_mov_dpp(x, 0x158 + S, 0xf, 0xf, true);
+        return (threadIdx.x & 8) ? b : a;
+    }
+}
+template <int L, int S>
+__device__ inline float sub_lane(float x) { return __int_as_float(sub_lane<L, S>(__float_as_int(x))); }
+template <int L, int S>
+__device__ inline double sub_lane(double x)
+{
+    return __hiloint2double(sub_lane<L, S>(__double2hiint(x)), sub_lane<L, S>(__double2loint(x)));
 }
 
 template <int W>
@@ -585,18 +632,19 @@ __device__ __forceinline__ void trim_step(TrimRun<float> &st, int kind, float lo
     }
 }
 
-// Split trimming round: the kept sets of the lanes of the group (start and
-// length, see kept_code) intersected in constraint order, S = 0 .. 6
-template <typename R, int... S>
-__device__ inline void split_steps(TrimRun<float> &st, float lo, float code, R &&label,
-                                   std::integer_sequence<int, S...>)
+// Split trimming round: the kept sets of the group's L lanes (start and
+// length, see kept_code) intersected in constraint order; label(S) is the
+// constraint of lane S.
+template <int L, typename T, typename R, int... S>
+__device__ inline void split_steps(TrimRun<T> &st, T lo, T code, R &&label, std::integer_sequence<int, S...>)
 {
-    auto step = [&](float l, float c, int r) { trim_step(st, c < 0.f ? 1 : (c > 4.f ? 0 : 2), l, c, r); };
-    (step(group8_lane<S>(lo), group8_lane<S>(code), label(S)), ...);
+    auto step = [&](T l, T c, int r) { trim_step(st, c < (T)0 ? 1 : (c > (T)4 ? 0 : 2), l, c, r); };
+    (step(sub_lane<L, S>(lo), sub_lane<L, S>(code), label(S)), ...);
 }
 // a kept set's length, beyond a turn for a constraint that is never active,
 // negative where nothing is kept
-__device__ inline float kept_code(int kind, float lc) { return kind == 2 ? lc : (kind ? -1.f : 8.f); }
+template <typename T>
+__device__ inline T kept_code(int kind, T lc) { return kind == 2 ? lc : (kind ? (T)-1 : (T)8); }
 
 // Conic point at the direction (sin t, cos t) ~ (s, c).  FP32: the products
 // are fused by hand, so that every schedule of the node pass rounds alike.
@@ -695,7 +743,7 @@ __device__ inline int find_vert(const SH &sh, uint32_t name)
         if (m < name) lo = mid + 1;
         else hi = mid - 1;
     }
-    return -1;
+    return kNone;
 }
 
 // Eq. 12 index ii (1..nseg-1) of an interior point -> node-local mesh index
@@ -936,181 +984,201 @@ __device__ __forceinline__ void node_tail(const Params &P, Shared<T, CF> &sh, co
         }
         __syncthreads();
         if (group_status<WL>(sh)) goto finish;
+        // record space: bump allocation in the node's region, asked for here
+        // and needed after the loops are laid out (the atomic's way to memory
+        // and back is hidden by them).  Every arc is on the loops of both of
+        // its labels but the nodal sphere's.
+        const int nent = 2 * E - sh.ncirc;                               // loop entries: (arc, side)
+        const int ns_tot = 2 * (sh.wsum - V + E) - sh.fsum;              // loop samples
+        const int64_t lw = SINK ? 0 : rec_loop_word(V, E, NC + sh.wsum - V, rec_table_bytes(v, nent, WIDE));
+        const int64_t words = lw + (((int64_t)2 * ns_tot + 3) & ~(int64_t)3);
+        unsigned long long old = 0;
+        if (lane == 0) old = atomicAdd(&W.rec_top[n & (kRecRegions - 1)], (unsigned long long)words);
         // strut end loops must be graphs over phi: every step (mod 2 pi)
-        // positive and exactly one descent, i.e. one turn.  Lanes run over
-        // all loop samples of the node and store them in the node record.
-        // loop entries (arcs of every loop, loops in label order): first
-        // sample of each entry by a carried prefix sum over the lanes
+        // positive and exactly one descent, i.e. one turn.
+        // Loop entries (arcs of every loop, loops in label order): the first
+        // sample of each by a carried prefix sum over the lanes, kept per arc
+        // and side (0: its label p, 1: q; complemented when the loop runs
+        // against the arc).
         {
-            const int nent = sh.loop_base[v + 1];
             int off = 0;
             for (int e0 = 0; e0 < nent; e0 += WL) {
                 const int e = e0 + lane;
-                int ns = 0, m = 1;
+                int ns = 0, m = 0, aj = 0, pp = 0;
                 if (e < nent) {
-                    while (sh.loop_base[m + 1] <= e) ++m;
-                    const int pp = sh.loop_base[m] + sh.loop_ord[e];
-                    const int aj = sh.loop_arc[pp];
+                    m = sh.entry_m[e];
+                    pp = sh.loop_base[m] + sh.loop_ord[e];
+                    aj = sh.loop_arc[pp];
                     ns = sh.A[aj].nseg;
-                    sh.entry_arc[e] = (uint16_t)(aj | (sh.loop_dir[pp] > 0 ? 0x8000 : 0));
                 }
                 int tot;
-                const int ex = group_excl_scan<WL>(ns, &tot);
+                const int s0 = off + group_excl_scan<WL>(ns, &tot);
                 if (e < nent) {
-                    sh.entry_off[e] = off + ex;
-                    sh.entry_m[e] = (uint8_t)m;
+                    const bool fw = sh.loop_dir[pp] > 0;
+                    sh.entry_arc[e] = (uint16_t)(aj | (fw ? 0x8000 : 0));
+                    sh.entry_off[2 * aj + (sh.A[aj].q == m ? 1 : 0)] = fw ? s0 : ~s0;
+                    if (e == sh.loop_base[m]) sh.lbase[m] = s0;
                 }
                 off += tot;
-            }
-            if (lane == 0) sh.entry_off[nent] = off;
-        }
-        __syncthreads();
-        // index v: the total
-        over_lanes<WL, CF::VM>(lane, 0, v, [&](int l) { sh.lbase[l + 1] = sh.entry_off[sh.loop_base[l + 1]]; });
-        if (lane == 0) {
-            const int off = sh.entry_off[sh.loop_base[v + 1]];
-            // record space: bump allocation in the node's region
-            // the node's interior points follow its hole centres
-            const int HX = NC + sh.wsum - V;
-            const int64_t words =
-                (SINK ? 0 : rec_loop_word(V, E, HX, rec_table_bytes(v, sh.loop_base[v + 1], WIDE))) +
-                (((int64_t)2 * off + 3) & ~(int64_t)3);
-            const int g = (int)(n & (kRecRegions - 1));
-            const int64_t region = W.rec_words / kRecRegions;
-            const unsigned long long old = atomicAdd(&W.rec_top[g], (unsigned long long)words);
-            if ((int64_t)old + words <= region) {
-                sh.rec = (int64_t)g * region + (int64_t)old;
-            } else {
-                sh.rec = -1;
-                atomicOr(&W.flags[0], DF_RECCAP);
             }
         }
         over_lanes<WL, CF::VM>(lane, 0, v - 1, [&](int l) {
             sh.loop_desc[l + 1] = 0;
             sh.loop_rot[l + 1] = 0;
         });
-        __syncthreads();
-        {
-            const int nent = sh.loop_base[v + 1];
-            const int ns_tot = sh.entry_off[nent];
-            const int HX = NC + sh.wsum - V;
-            int2 *rl = sh.rec >= 0
-                           ? (int2 *)(W.rec + sh.rec + (SINK ? 0 : rec_loop_word(V, E, HX, rec_table_bytes(v, nent, WIDE))))
-                           : nullptr;
-            // the node's Eq. 12 points in the record (stored mode), indexed
-            // by node-local mesh index: the expansion copies them
-            uint32_t *RI = (!SINK && sh.rec >= 0) ? W.rec + sh.rec + rec_table_word(V, E, NC) - 3 * V : nullptr;
-            // phi key and local mesh index of sample j of loop entry e (on
-            // the loop of strut m); an interior point is stored by the loop
-            // of its arc's label q (every arc is on that loop)
-            auto sample = [&](int e, int m, int j, int &li) -> T {
-                const uint32_t ea = sh.entry_arc[e];
-                const ArcL<T> &A = sh.A[ea & 0x7fffu];
-                const bool fw = (ea & 0x8000u) != 0;
-                const int ii = fw ? j : A.nseg - j;
-                li = j == 0 ? (fw ? A.vs : A.ve) : interior_idx(A, ii);
-                const V3<T> w = j == 0 ? vert_pos(sh, li) : interior_pt(sh, A, ii);
-                if (j != 0 && m == A.q) {
-                    if (RI) {
-                        RI[3 * li] = __float_as_uint((float)w.x);
-                        RI[3 * li + 1] = __float_as_uint((float)w.y);
-                        RI[3 * li + 2] = __float_as_uint((float)w.z);
-                    }
-                    if (hash_pts) {
-                        // as stored: the point rounded once, plus the centre
-                        const float x = (float)cen.x + (float)w.x, y = (float)cen.y + (float)w.y,
-                                    z = (float)cen.z + (float)w.z;
-                        pt_v += vert_key(vid_of(ln_sink, li), x, y, z);
-                        pt_x += (uint64_t)llrint((double)x * 1048576.0);
-                        pt_y += (uint64_t)llrint((double)y * 1048576.0);
-                        pt_z += (uint64_t)llrint((double)z * 1048576.0);
-                    }
-                }
-                // tangency circles are parametrised in the strut frame: phi
-                // is the parameter itself
-                if (A.p == 0) {
-                    T st, ct;
-                    m_sincos(sub_param(A, ii), &st, &ct);
-                    return phi_key(st, ct);
-                }
-                const SL<T> &sm = sh.S[m];
-                return phi_key(dot(w, v3(sm.qx, sm.qy, sm.qz)), dot(w, v3(sm.rx, sm.ry, sm.rz)));
-            };
-            // each lane checks the step from the previous sample of its loop
-            // (the previous lane's, or the last of the previous chunk); the
-            // step that closes a loop is checked afterwards.  A valid loop
-            // has exactly one descent, just before its smallest phi.
-            T carry = (T)0;
-            int e_carry = -1;  // loop entry of the sample before the window
-            for (int base = 0; base < ns_tot; base += WL) {
-                const int sidx = base + lane;
-                const bool act = sidx < ns_tot;
-                int m = 1, idx = 0, nloop = 1, li = 0;
-                T ph = (T)0;
-                int e = 0;  // loop entry of sample sidx
-                if constexpr (WL >= 16 && WL <= 64) {
-                    // the entries that start in the window [base, base + WL)
-                    // are e_carry + 1, e_carry + 2, ... (every entry has a
-                    // sample): each marks its first sample, and a scan of the
-                    // marks over the lanes gives every sample its entry
-                    sh.wmark[lane] = 0;
-                    const int ec = e_carry + 1 + lane;
-                    if (ec < nent) {
-                        const int o = sh.entry_off[ec] - base;
-                        if (o < WL) sh.wmark[o] = 1;
-                    }
-                    __syncthreads();
-                    e = e_carry + wave_incl_scan<WL>((int)sh.wmark[lane]);
-                    e_carry = group_last_lane<WL>(e);
-                } else if (act) {
-                    int lo = 0, hi = nent - 1;  // last entry with entry_off <= sidx
-                    while (lo < hi) {
-                        int mid = (lo + hi + 1) >> 1;
-                        if (sh.entry_off[mid] <= sidx) lo = mid;
-                        else hi = mid - 1;
-                    }
-                    e = lo;
-                }
-                if (act) {
-                    m = sh.entry_m[e];
-                    idx = sidx - sh.lbase[m];
-                    nloop = sh.loop_len[m];
-                    ph = sample(e, m, sidx - sh.entry_off[e], li);
-                }
-                T prev, last;
-                group_prev_last<WL>(ph, carry, prev, last);
-                carry = last;
-                if (act) {
-                    if (idx == 0) {
-                        sh.ph_first[m] = ph;
-                    } else {
-                        T dp = ph - prev;  // in key units: a full turn is 4
-                        if (dp <= (T)-2) dp += (T)4;
-                        if (dp > (T)2) dp -= (T)4;
-                        if (!(dp > (T)0)) atomicOr(&sh.status, NS_LOOP);
-                        if (ph < prev) {
-                            atomicAdd(&sh.loop_desc[m], 1);
-                            sh.loop_rot[m] = idx;
-                        }
-                    }
-                    if (idx == nloop - 1) sh.ph_last[m] = ph;
-                    if (rl) rl[sidx] = make_int2(li, __float_as_int((float)ph));
-                }
+        if (lane == 0) {
+            const int64_t region = W.rec_words / kRecRegions;
+            if ((int64_t)old + words <= region) {
+                sh.rec = (n & (kRecRegions - 1)) * region + (int64_t)old;
+            } else {
+                sh.rec = -1;
+                atomicOr(&W.flags[0], DF_RECCAP);
             }
         }
         __syncthreads();
-        over_lanes<WL, CF::VM>(lane, 0, v - 1, [&](int l) {
-            const int m = l + 1;
-            const T a = sh.ph_last[m], b = sh.ph_first[m];
-            T dp = b - a;
-            if (dp <= (T)-2) dp += (T)4;
-            if (dp > (T)2) dp -= (T)4;
-            if (!(dp > (T)0)) atomicOr(&sh.status, NS_LOOP);
-            if (b < a) {
-                atomicAdd(&sh.loop_desc[m], 1);
-                sh.loop_rot[m] = 0;
+        // Lanes over the points of all arcs: a point is evaluated once for the
+        // two loops that its arc is on (94 points for the 152 loop samples of
+        // a BCC node at k = 16; with the record asked for before the loops
+        // are laid out, 21.1 -> 16.9 k cycles per node pair, and FP64 nodes
+        // half the sines: 24 mixed parts 3.08 -> 2.98 ms).  An arc of two loops, which run along
+        // it in either direction, has the points 0 .. nseg for tasks, a
+        // circular arc the nseg that are samples of its one loop.  Each lane
+        // stores its sample of either loop and checks the step to it from the
+        // lane before; the steps between arcs are checked afterwards.
+        {
+            const int ncirc = sh.ncirc, tasks = sh.wsum - V + nent;
+            int2 *rl = sh.rec >= 0 ? (int2 *)(W.rec + sh.rec + lw) : nullptr;
+            // the node's Eq. 12 points in the record (stored mode), indexed
+            // by node-local mesh index: the expansion copies them
+            uint32_t *RI = (!SINK && sh.rec >= 0) ? W.rec + sh.rec + rec_table_word(V, E, NC) - 3 * V : nullptr;
+            auto first_task = [&](int j) { return sh.A[j].mbase - V + 2 * j - (j < ncirc ? j : ncirc); };
+            // a step of a loop (in key units a full turn is 4) must be
+            // positive; a valid loop has exactly one descent, just before
+            // its smallest phi
+            auto step = [&](T from, T to, int m, int rot) {
+                T dp = to - from;
+                if (dp <= (T)-2) dp += (T)4;
+                if (dp > (T)2) dp -= (T)4;
+                if (!(dp > (T)0)) atomicOr(&sh.status, NS_LOOP);
+                if (to < from) {
+                    atomicAdd(&sh.loop_desc[m], 1);
+                    sh.loop_rot[m] = rot;
+                }
+            };
+            T carry[2] = {(T)0, (T)0};
+            int a_carry = -1;  // arc of the task before the window
+            for (int base = 0; base < tasks; base += WL) {
+                const int t = base + lane;
+                const bool act = t < tasks;
+                int a = 0;
+                if constexpr (WL >= 16 && WL <= 64) {
+                    // the arcs that start in the window [base, base + WL) are
+                    // a_carry + 1, a_carry + 2, ...: the lanes at which they
+                    // do, as a mask, give every task its arc
+                    const int ac = a_carry + 1 + lane;
+                    const int o = ac < E ? first_task(ac) - base : WL;
+                    const uint32_t upto = 0xffffffffu >> (31 - (lane & 31));
+                    const uint32_t m0 = group_or<WL>(o < 32 && o < WL ? 1u << o : 0u);
+                    a = a_carry + __popc(WL > 32 && lane > 31 ? m0 : m0 & upto);
+                    a_carry += __popc(m0);
+                    if constexpr (WL > 32) {
+                        const uint32_t m1 = group_or<WL>(o >= 32 && o < WL ? 1u << (o - 32) : 0u);
+                        if (lane > 31) a += __popc(m1 & upto);
+                        a_carry += __popc(m1);
+                    }
+                } else if (act) {
+                    int lo = 0, hi = E - 1;  // last arc with first_task <= t
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (first_task(mid) <= t) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    a = lo;
+                }
+                const ArcL<T> &A = sh.A[a];
+                int ii = 0, nseg = 1, li = 0;
+                T ph[2] = {(T)0, (T)0};
+                if (act) {
+                    ii = t - first_task(a);
+                    if (a < ncirc && sh.entry_off[2 * a + 1] < 0) ++ii;  // against the arc: 1 .. nseg
+                    nseg = A.nseg;
+                    li = ii ? A.ve : A.vs;
+                    V3<T> w;
+                    if (ii > 0 && ii < nseg) {
+                        li = interior_idx(A, ii);
+                        w = interior_pt(sh, A, ii);
+                        if (RI) {
+                            RI[3 * li] = __float_as_uint((float)w.x);
+                            RI[3 * li + 1] = __float_as_uint((float)w.y);
+                            RI[3 * li + 2] = __float_as_uint((float)w.z);
+                        }
+                        if (hash_pts) {
+                            // as stored: the point rounded once, plus the centre
+                            const float x = (float)cen.x + (float)w.x, y = (float)cen.y + (float)w.y,
+                                        z = (float)cen.z + (float)w.z;
+                            pt_v += vert_key(vid_of(ln_sink, li), x, y, z);
+                            pt_x += (uint64_t)llrint((double)x * 1048576.0);
+                            pt_y += (uint64_t)llrint((double)y * 1048576.0);
+                            pt_z += (uint64_t)llrint((double)z * 1048576.0);
+                        }
+                    } else {
+                        w = vert_pos(sh, li);
+                    }
+                    if (A.p == 0) {
+                        // tangency circles are parametrised in the strut
+                        // frame: phi is the parameter itself
+                        T st, ct;
+                        m_sincos(sub_param(A, ii), &st, &ct);
+                        ph[1] = phi_key(st, ct);
+                    } else {
+                        const SL<T> &sp = strut(sh.S, A.p), &sq = strut(sh.S, A.q);
+                        ph[0] = phi_key(dot(w, v3(sp.qx, sp.qy, sp.qz)), dot(w, v3(sp.rx, sp.ry, sp.rz)));
+                        ph[1] = phi_key(dot(w, v3(sq.qx, sq.qy, sq.qz)), dot(w, v3(sq.rx, sq.ry, sq.rz)));
+                    }
+                }
+                T prev[2];
+#pragma unroll
+                for (int side = 0; side < 2; ++side) {
+                    T last;
+                    group_prev_last<WL>(ph[side], carry[side], prev[side], last);
+                    carry[side] = last;
+                }
+                if (act) {
+#pragma unroll
+                    for (int side = 0; side < 2; ++side) {
+                        const int m = side ? A.q : A.p;
+                        if (m == 0) continue;
+                        const int so = sh.entry_off[2 * a + side];
+                        const bool fw = so >= 0;
+                        const int s0 = fw ? so : ~so, j = fw ? ii : nseg - ii;  // j-th sample of the entry
+                        const T x = ph[side];
+                        if (j < nseg) {
+                            if (rl) rl[s0 + j] = make_int2(li, __float_as_int((float)x));
+                            if (j == 0) sh.ph_first[2 * a + side] = x;
+                            if (j == nseg - 1) sh.ph_last[2 * a + side] = x;
+                        }
+                        // points ii - 1 and ii, both samples of the entry
+                        if (ii > (fw ? 0 : 1) && ii < (fw ? nseg : nseg + 1)) {
+                            if (fw) step(prev[side], x, m, s0 + j - sh.lbase[m]);
+                            else step(x, prev[side], m, s0 + j + 1 - sh.lbase[m]);
+                        }
+                    }
+                }
             }
-        });
+            __syncthreads();
+            // from each entry's last sample to the next one's first, the last
+            // of a loop to its first
+            for (int e = lane; e < nent; e += WL) {
+                const int m = sh.entry_m[e], b0 = sh.loop_base[m];
+                const int before = e == b0 ? sh.loop_base[m + 1] - 1 : e - 1;
+                auto at = [&](int i) {
+                    const int j = sh.entry_arc[i] & 0x7fff;
+                    return 2 * j + (sh.A[j].q == m ? 1 : 0);
+                };
+                const int x = at(e), so = sh.entry_off[x];
+                step(sh.ph_last[at(before)], sh.ph_first[x], m, e == b0 ? 0 : (so >= 0 ? so : ~so) - sh.lbase[m]);
+            }
+        }
         __syncthreads();
         over_lanes<WL, CF::VM>(lane, 0, v - 1, [&](int l) {
             if (sh.loop_desc[l + 1] != 1) atomicOr(&sh.status, NS_LOOP);
@@ -1202,7 +1270,7 @@ finish:
                                 (uint32_t)A.p | ((uint32_t)A.q << 8) | ((uint32_t)A.full << 16) | (fwd << 17) |
                                     (lower << 18));
             dst[3] = make_uint4((uint32_t)A.vs | ((uint32_t)A.ve << 16),
-                                (uint32_t)A.nseg | (((uint32_t)A.contour & 0xffffu) << 16), (uint32_t)A.mbase,
+                                (uint32_t)A.nseg | ((A.contour == kNone ? 0xffffu : (uint32_t)A.contour) << 16), (uint32_t)A.mbase,
                                 (uint32_t)A.fbase);
         }
         uint32_t *RH = RA + kRecArcFields * E;
@@ -1270,7 +1338,6 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         float4 f4 = W.node4[far];
         bool bad;
         SL<T> s = strut_entry(cen, rho, v3((T)f4.x, (T)f4.y, (T)f4.z), (T)f4.w, (int)((int64_t)far > n), bad);
-        s.sid = he.y;
         s.far = far;
         if (bad || far == n) atomicOr(&sh.status, NS_INVALID_STRUT);
         sh.S[l + 1] = s;
@@ -1286,21 +1353,22 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
 
     // ---- conics, trimming, arcs and owned vertices ------------------------
     {
-        // two nodes per wave: 36 conics at v = 8 for 32 lanes.  (Four per wave
-        // have at most 10 for 16 lanes, one per wave 36 for 64.)
-        constexpr bool SPLIT = F32 && WL == 32;
+        // A last round of few conics is split: L lanes per conic test as many
+        // constraints at once, and the conic's first lane intersects the kept
+        // sets in constraint order.  Two nodes per wave: 36 conics at v = 8
+        // for 32 lanes, the last four on 8 lanes each.  One node per wave: 78
+        // at v = 12 for 64 lanes, the last fourteen on 4 lanes each (30.0 ->
+        // 26.1 k cycles at an octet node).  (Four nodes per wave have at most
+        // 10 for 16 lanes.)
+        constexpr int L = WL == 32 ? 8 : (WL >= 64 ? 4 : 1);
         const int nconic = v * (v + 1) / 2;
         for (int c0 = 0; c0 < nconic;) {
-            // A last round of at most WL / 8 conics (v <= 8: at most 7
-            // constraints each) runs on 8 lanes per conic, one constraint per
-            // lane; the conic's first lane then intersects the kept sets in
-            // constraint order.  Otherwise one lane per conic.
-            const bool split = SPLIT && v <= 8 && (nconic - c0) * 8 <= WL;
-            const int ci = split ? c0 + (lane >> 3) : c0 + lane;
-            const int sub = split ? (lane & 7) : 0;
+            const bool split = L > 1 && (nconic - c0) * L <= WL;
+            const int ci = split ? c0 + lane / L : c0 + lane;
+            const int sub = split ? lane & (L - 1) : 0;
             const bool grp = ci < nconic;
             const bool act = grp && sub == 0;
-            c0 += split ? WL / 8 : WL;
+            c0 += split ? WL / L : WL;
             int p = 0, q = 0;
             if (grp) conic_labels(ci, v, p, q);
             Con<T> C;
@@ -1325,12 +1393,13 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                     if (r >= q) ++r;
                     return r;
                 };
-                if constexpr (SPLIT) {
-                    if (split) {
+                if constexpr (L > 1) {
+                    for (int j0 = 0; split && j0 < v - 1; j0 += L) {
                         int kind = 0;
                         T lo = (T)0, lc = (T)0;
-                        if (ell && sub < v - 1) kind = cons_interval(sh.S, gp, hp, other(sub), C, lo, lc);
-                        split_steps(st, lo, kept_code(kind, lc), other, std::make_integer_sequence<int, 7>{});
+                        if (ell && j0 + sub < v - 1) kind = cons_interval(sh.S, gp, hp, other(j0 + sub), C, lo, lc);
+                        split_steps<L>(st, lo, kept_code(kind, lc), [&](int j) { return other(j0 + j); },
+                                       std::make_integer_sequence<int, (CF::VM - 1 < L ? CF::VM - 1 : L)>{});
                     }
                 }
                 const int nsteps = !split && act && ell ? v - 1 : 0;
@@ -1367,7 +1436,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                         A.vs = st.pc[i].rs;
                         A.ve = st.pc[i].re;
                         A.dt = st.pc[i].len;
-                        A.contour = i | (cnt << 8);
+                        A.contour = i | (cnt << 4);
                     }
                 }
             }
@@ -1442,7 +1511,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             uint32_t nm[2] = {kNoName, kNoName};
             int rank[2] = {0, 0}, before = 0;
             if (act) {
-                const int place = sh.A[j].contour & 0xff, n = sh.A[j].contour >> 8;
+                const int place = sh.A[j].contour & 0xf, n = sh.A[j].contour >> 4;
                 nm[0] = own_name[2 * j];
                 nm[1] = own_name[2 * j + 1];
                 if (n == 1) {
@@ -1496,8 +1565,8 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         }
         // the arcs of a conic by their smaller end name
         for (int j = lane; j < E; j += WL) {
-            if (sh.A[j].contour & 0xff) continue;
-            const int n = sh.A[j].contour >> 8;
+            if (sh.A[j].contour & 0xf) continue;
+            const int n = sh.A[j].contour >> 4;
             for (int x = 1; x < n; ++x)
                 for (int y = j + x; y > j; --y) {
                     ArcL<T> &a0 = sh.A[y - 1], &a1 = sh.A[y];
@@ -1518,10 +1587,11 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         const int E = sh.n_arc, V = sh.n_vert;
         for (int j = lane; j < E; j += WL) {
             ArcL<T> &A = sh.A[j];
-            A.vs = find_vert(sh, A.ns);
-            A.ve = find_vert(sh, A.ne);
-            if (A.vs < 0 || A.ve < 0) atomicOr(&sh.status, NS_TOPOLOGY);
-            A.contour = -1;
+            const int vs = find_vert(sh, A.ns), ve = find_vert(sh, A.ne);
+            if (vs == kNone || ve == kNone) atomicOr(&sh.status, NS_TOPOLOGY);
+            A.vs = vs;
+            A.ve = ve;
+            A.contour = kNone;
         }
         // segment counts (Eq. 11)
         for (int i = lane; i < V; i += WL) sh.vdeg[i] = 0;
@@ -1538,7 +1608,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         }
         for (int j = lane; j < E; j += WL) {
             const ArcL<T> &A = sh.A[j];
-            if (A.full || A.vs < 0 || A.ve < 0) continue;
+            if (A.full || A.vs == kNone || A.ve == kNone) continue;
             atomicAdd(&sh.vdeg[A.vs], 1);
             atomicAdd(&sh.vdeg[A.ve], 1);
         }
@@ -1734,7 +1804,7 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
 {
     using T = float;
     constexpr int WL = CF::W;
-    static_assert(CF::AC == WL && CF::VC <= WL && (1 + CF::VM + 2 * CF::AC + 3) / 4 <= 2 * CF::AC + 1,
+    static_assert(CF::AC == WL && CF::VC <= WL && (1 + CF::VM + 2 * CF::AC + 3) / 4 <= 2 * CF::AC,
                   "one arc, vertex and table word per lane; the table is staged in entry_off");
     const int lane = threadIdx.x & (WL - 1);
     const Work &W = P.w;
@@ -1782,7 +1852,6 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
     if (lane < v) {
         bool bad;
         SL<T> st = strut_entry(cen, rho, v3((T)f4.x, (T)f4.y, (T)f4.z), (T)f4.w, (int)((int64_t)he.x > n), bad);
-        st.sid = he.y;
         st.far = he.x;
         sh.S[lane + 1] = st;
     }
@@ -1822,7 +1891,7 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
         A.ve = (int)(u1 >> 16);
         A.ns = sh.vname[A.vs];
         A.ne = sh.vname[A.ve];
-        A.contour = (u2 >> 16) == 0xffffu ? -1 : (int)(u2 >> 16);
+        A.contour = (u2 >> 16) == 0xffffu ? kNone : (int)(u2 >> 16);
         // Eq. 11 at the new resolution
         if (A.full) {
             A.nseg = k;
@@ -1843,6 +1912,7 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
         sh.loop_arc[e] = (uint8_t)(b & 0x7f);
         sh.loop_dir[e] = (b & 0x80) ? 1 : -1;
         sh.loop_ord[e] = (uint8_t)(e - tbyte(m - 1));  // loop_base[m] = tbyte(m - 1)
+        sh.entry_m[e] = (uint8_t)m;
     }
     __syncthreads();
     if (lane >= 1 && lane <= v) {
@@ -1916,10 +1986,14 @@ __device__ inline void drain_class(const Params &P, int cls, Shared<float, C> *s
     }
 }
 
-// At most 168 VGPRs: three waves per SIMD (LDS allows as many), where one
-// register more would leave two.
+// At most 128 VGPRs and 10,240 bytes of LDS per block: four waves per SIMD.
+// The pass is bound by vector issue, at three waves 77 % of the peak with LDS
+// and scalar chains to wait for.  Three waves (12.5 KB; LDS is given out in
+// 1,280-byte pieces) against four, six registers spilled: BCC 64^3, k = 16,
+// step 3.84 -> 3.37 ms; sink BCC 128^3, k = 12, 26.4 -> 22.3 ms; octet 32^3
+// forward + adjoint 4.20 -> 4.04 ms.
 template <typename C, int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) k_node32(Params P, int cls)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_node32(Params P, int cls)
 {
     __shared__ Shared<float, C> sh[64 / C::W];
     __shared__ int s_grab[2];
@@ -1935,7 +2009,7 @@ union SharedV4V8 {
     Shared<float, CfgV4> a[4];
 };
 template <int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) k_node32_v8v4(Params P)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_node32_v8v4(Params P)
 {
     __shared__ SharedV4V8 sh;
     __shared__ int s_grab[2];
@@ -2028,8 +2102,8 @@ constexpr unsigned kFp64MidGrid = 1024;
 constexpr unsigned kFp64BigGrid = 512;
 constexpr int64_t kBigGrid = 2048;  // blocks of a multi-wave class launch
 // waves of a one-wave-class launch: as many as the chip holds at once (256
-// compute units, 12 blocks of 64 threads each by LDS)
-constexpr int64_t kNodeGrid = 256 * 12;
+// compute units, 16 blocks of 64 threads each by registers and LDS)
+constexpr int64_t kNodeGrid = 256 * 16;
 constexpr int64_t kRedoGrid = 512;       // waves of that launch over a redo list
 constexpr int64_t kMinGrid = 32;         // blocks of a class launch sized by an estimate
 
