@@ -160,10 +160,12 @@ void carve_fixed(lm_plan *P, Carver &c, int64_t N, int64_t S)
     w.rec_top = c.take<unsigned long long>(lm::kRecRegions);
     w.queue = c.take<int32_t>(N + 1);
     w.cls_info = c.take<int64_t>(8);
-    w.work_ctr = c.take<int32_t>(8);
     P->codec_ctr = c.take<unsigned long long>(1);
     w.node_k = nullptr;
 }
+
+// The work counters (lm_forward_sink_static has its own beside its array).
+void carve_sched(lm_plan *P, Carver &c) { P->w.sched = c.take<int32_t>(lm::kSchedWords); }
 
 void carve_grad(lm_plan *P, Carver &c, int64_t N, int64_t S)
 {
@@ -254,12 +256,10 @@ int run_count(lm_plan *P, int k, const lm::FillOut *out, const lm::Work &w, cons
               const int64_t *src_node_rec = nullptr, int32_t *redo = nullptr, int32_t *redo_cnt = nullptr)
 {
     const int64_t N = P->in.n_nodes, S = P->in.n_struts;
-    // flags[0] (count / fill) and flags[2] (FP64 hand-over count)
-    HIPCHK(hipMemsetAsync(w.flags, 0, sizeof(int32_t), P->st));
-    HIPCHK(hipMemsetAsync(w.flags + 2, 0, sizeof(int32_t), P->st));
+    HIPCHK(hipMemsetAsync(w.flags, 0, sizeof(int32_t), P->st));  // count / fill
     HIPCHK(hipMemsetAsync(w.totals, 0, sizeof(int64_t) * 16, P->st));
     HIPCHK(hipMemsetAsync(w.rec_top, 0, sizeof(unsigned long long) * lm::kRecRegions, P->st));
-    HIPCHK(hipMemsetAsync(w.work_ctr, 0, sizeof(int32_t) * 8, P->st));
+    HIPCHK(hipMemsetAsync(w.sched, 0, sizeof(int32_t) * lm::kSchedWords, P->st));
     {
         PhaseTimer t(P, PH_NODE32);
         if (redo_cnt) HIPCHK(hipMemsetAsync(redo_cnt, 0, sizeof(int32_t) * 8, P->st));
@@ -407,10 +407,11 @@ int first_prepare(lm_plan *P)
 }
 
 // Carves (or, with base null, sizes) every part of a caller-owned workspace.
-size_t ws_layout(lm_plan *P, void *base, int64_t N, int64_t S, const lm_options &o)
+size_t ws_layout(lm_plan *P, void *base, int64_t N, int64_t S, const lm_options &o, bool sched = true)
 {
     Carver c(base);
     carve_fixed(P, c, N, S);
+    if (sched) carve_sched(P, c);
     if (o.flags & LM_WS_GRADIENT) carve_grad(P, c, N, S);
     if (o.flags & LM_WS_SINK) {
         carve_sink(P, c, N, S);
@@ -426,6 +427,13 @@ size_t ws_layout(lm_plan *P, void *base, int64_t N, int64_t S, const lm_options 
     P->w.rec = c.take<uint32_t>(rw);
     P->w.rec_words = rw;
     return c.off;
+}
+
+int check_sizes(int64_t n_nodes, int64_t n_struts)
+{
+    if (n_nodes < 0 || n_struts < 0) return LM_ERR_INVALID_ARG;
+    if (n_nodes >= ((int64_t)1 << 31) || n_struts >= ((int64_t)1 << 31)) return LM_ERR_UNSUPPORTED;
+    return LM_OK;
 }
 
 int check_options(const lm_options *opt, lm_options *o)
@@ -448,10 +456,10 @@ extern "C" {
 
 int lm_workspace_size(int64_t n_nodes, int64_t n_struts, const lm_options *opt, size_t *bytes)
 {
-    if (!bytes || n_nodes < 0 || n_struts < 0) return LM_ERR_INVALID_ARG;
-    if (n_nodes >= ((int64_t)1 << 31) || n_struts >= ((int64_t)1 << 31)) return LM_ERR_UNSUPPORTED;
+    int rc = bytes ? check_sizes(n_nodes, n_struts) : LM_ERR_INVALID_ARG;
+    if (rc) return rc;
     lm_options o;
-    int rc = check_options(opt, &o);
+    rc = check_options(opt, &o);
     if (rc) return rc;
     lm_plan tmp;
     *bytes = ws_layout(&tmp, nullptr, n_nodes, n_struts, o);
@@ -503,12 +511,14 @@ int lm_plan_create(lm_plan **plan, const lm_lattice *lat, void *stream)
     if (!P) return LM_ERR_INTERNAL;
     Carver c0(nullptr);
     carve_fixed(P, c0, lat->n_nodes, lat->n_struts);
+    carve_sched(P, c0);
     if (hipMalloc(&P->ws, c0.off) != hipSuccess) {
         delete P;
         return LM_ERR_HIP;
     }
     Carver c(P->ws);
     carve_fixed(P, c, lat->n_nodes, lat->n_struts);
+    carve_sched(P, c);
     if ((rc = first_prepare(P))) {
         (void)hipFree(P->ws);
         delete P;
@@ -735,7 +745,7 @@ int sink_range(lm_plan *P, int k, int64_t r, int64_t n0, int64_t n1, int t16, in
     wc.queue = P->sk_lists;
     wc.cls_info = P->sk_info;
     HIPCHK(hipMemsetAsync(w.rec_top, 0, sizeof(unsigned long long) * lm::kRecRegions, P->st));
-    HIPCHK(hipMemsetAsync(w.work_ctr, 0, sizeof(int32_t) * 8, P->st));
+    HIPCHK(hipMemsetAsync(w.sched, 0, sizeof(int32_t) * lm::kSchedWords, P->st));
     so.n0 = n0;
     so.n1 = n1;
     {
@@ -1115,6 +1125,7 @@ const char *lm_status_string(int code)
 // process ends.  In host code `scratch` only stands for the symbol: its device
 // address comes from hipGetSymbolAddress, once per device.
 static __device__ __align__(256) unsigned char scratch[LM_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) int32_t scratch_sched[lm::kSchedWords];  // the plan's work counters
 
 __global__ void lm_k_fill_u32(uint32_t *p, uint32_t v, int64_t n)
 {
@@ -1126,22 +1137,27 @@ namespace {
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
-void *g_scratch_ptr[kMaxDevices] = {};
+struct StaticMem {
+    void *base;
+    int32_t *sched;
+};
+StaticMem g_scratch[kMaxDevices] = {};
 
-// Device address of `scratch` on the current device (looked up at the first
-// call on that device).
-int static_scratch(void **out)
+// Device addresses of `scratch` and its counters on the current device (looked
+// up at the first call on that device).
+int static_scratch(StaticMem *out)
 {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return LM_ERR_HIP;
     if (dev < 0 || dev >= kMaxDevices) return LM_ERR_UNSUPPORTED;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
+    if (!g_scratch[dev].base) {
+        void *p = nullptr, *q = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return LM_ERR_HIP;
-        g_scratch_ptr[dev] = p;
+        if (hipGetSymbolAddress(&q, HIP_SYMBOL(scratch_sched)) != hipSuccess || !q) return LM_ERR_HIP;
+        g_scratch[dev] = StaticMem{p, (int32_t *)q};
     }
-    *out = g_scratch_ptr[dev];
+    *out = g_scratch[dev];
     return LM_OK;
 }
 
@@ -1165,7 +1181,11 @@ int lm_static_scratch_size(int64_t n_nodes, int64_t n_struts, int k, size_t *byt
     o.k_max = k;
     o.record_bytes = 0;
     o.max_parts = 0;
-    return lm_workspace_size(n_nodes, n_struts, &o, bytes);
+    int rc = check_sizes(n_nodes, n_struts);
+    if (rc) return rc;
+    lm_plan tmp;
+    *bytes = ws_layout(&tmp, nullptr, n_nodes, n_struts, o, false);
+    return LM_OK;
 }
 
 int lm_forward_sink_static(const lm_lattice *lat, int k, uint64_t *d_words, void *stream)
@@ -1182,8 +1202,8 @@ int lm_forward_sink_static(const lm_lattice *lat, int k, uint64_t *d_words, void
         if ((rc = fill_u32(d_words, 2 * LM_SINK_WORDS, st))) return rc;
         return hipStreamSynchronize(st) == hipSuccess ? LM_OK : LM_ERR_HIP;
     }
-    void *base = nullptr;
-    if ((rc = static_scratch(&base))) return rc;
+    StaticMem mem;
+    if ((rc = static_scratch(&mem))) return rc;
     // a plan on the stack, every device buffer carved from the array
     lm_plan P{};  // value-initialised: every device pointer starts null
     init_plan(&P, lat, stream);
@@ -1194,7 +1214,8 @@ int lm_forward_sink_static(const lm_lattice *lat, int k, uint64_t *d_words, void
     o.k_max = k;
     o.record_bytes = 0;
     o.max_parts = 0;
-    ws_layout(&P, base, lat->n_nodes, lat->n_struts, o);
+    ws_layout(&P, mem.base, lat->n_nodes, lat->n_struts, o, false);
+    P.w.sched = mem.sched;
     // the array keeps the previous call's contents: clear what the sink
     // range expects at zero (node marks, slots, the range's failure flag)
     if ((rc = fill_u32(P.sk_mark, N + 1, st)) ||

@@ -59,8 +59,7 @@ enum NodeCol : int {
 constexpr int kNodeScanCols = 5;  // columns 0..4 are prefix-summed
 
 // Device-side flag words: flags[0] DevFlag bits of the last count / fill,
-// flags[1] DevFlag bits of the lattice preparation, flags[2] number of nodes
-// handed to the FP64 pass.
+// flags[1] DevFlag bits of the lattice preparation.
 enum DevFlag : int {
     DF_CAPACITY = 1,   // an output was too small, writes skipped
     DF_BADLAT = 4,     // a strut endpoint is out of range
@@ -143,10 +142,10 @@ struct Work {
     int64_t scan_tmp_len;
     int32_t *flags;         // [4] see DevFlag
     int64_t *totals;        // [16] device copy of totals
-    int32_t *fb_list;       // [N] nodes for the FP64 pass
+    int32_t *fb_list;       // [N] nodes for the FP64 pass, in kSub sub-lists (see hand_base)
     int32_t *queue;         // [N] node ids grouped by valence class
     int64_t *cls_info;      // [8] nodes per class (0..3), queue start per class (4..7)
-    int32_t *work_ctr;      // [8] work counters: FP32 classes 0..3, FP64 passes 4 (one wave), 5 (four waves) and 6 (two waves)
+    int32_t *sched;         // [kSchedWords] work and hand-over counters (see sched_ctr)
     const int16_t *node_k;  // [N] per-node resolution (batched parts) or null
     // adjoint scratch (set before lm_loss / lm_backward run)
     double *loss_node;      // [N][3] loss terms per node
@@ -173,6 +172,33 @@ __host__ __device__ inline int valence_class(int64_t v, int t16 = 4, int t32 = 8
     return v <= t16 ? 0 : (v <= t32 ? 1 : (v <= kVmax ? 2 : 3));
 }
 constexpr int kClasses = 4;
+
+// Work counters.  An atomic on a counter takes 11.6 ns of the counter's cache
+// line, whichever of the line's words it is, and lines do not wait for each
+// other (16,384 adds: 190 us on one line, 18 us on sixteen); so a list's work
+// is dealt out through kSub counters, each in a line of its own.
+constexpr int kSub = 16;
+constexpr int kSchedLine = 32;  // words from one counter to the next (128 bytes)
+enum SchedList : int {
+    SCHED_CLASS = 0,   // FP32, valence classes 0..3
+    SCHED_FP64 = 4,    // FP64: one wave, two waves, four waves per node
+    SCHED_REDO = 7,    // full solves after a re-subdivision, classes 0..3
+    SCHED_HAND = 11,   // nodes handed to FP64: at most kVmax struts, more
+    kSchedLists = 13,
+};
+constexpr int kSchedWords = kSchedLists * kSub * kSchedLine;
+__host__ __device__ inline int32_t *sched_ctr(int32_t *sched, int list, int sub)
+{
+    return sched + (list * kSub + sub) * kSchedLine;
+}
+// Nodes handed to the FP64 pass: node n goes to sub-list n mod kSub of
+// fb_list, whose space starts here (as many entries as there are such nodes);
+// nodes of at most kVmax struts from its start, larger ones from its end.
+__host__ __device__ inline int64_t hand_base(int64_t n_nodes, int sub)
+{
+    const int64_t r = n_nodes % kSub;
+    return n_nodes / kSub * sub + (sub < r ? sub : r);
+}
 
 // sin and cos of x in FP32 for every FP32 pass (one definition, so the node
 // pass, the expansion, sink-mode hashing and the adjoint evaluate the same

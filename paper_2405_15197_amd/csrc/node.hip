@@ -794,10 +794,9 @@ struct Params {
     const uint32_t *src_rec;
     const int64_t *src_node_rec;
     // nodes to solve in full after a re-subdivision pass: per class a list
-    // at the class's queue offset, its length and a work counter
+    // at the class's queue offset, and its length
     int32_t *redo;
     int32_t *redo_cnt;  // [4]
-    int32_t *redo_ctr;  // [4]
     // sink mode: where the counts and hashes of vertices and fans go
     SinkOut sink;
 };
@@ -1199,7 +1198,11 @@ finish:
                 W.node_rec[n] = -1;
                 // hand the node to the FP64 pass when precision may be at fault
                 const bool retry = F32 && (status & kRetry);
-                if (retry) W.fb_list[atomicAdd(&W.flags[2], 1)] = (int32_t)n;
+                if (retry) {
+                    const int sub = (int)(n % kSub), large = v > kVmax ? 1 : 0;
+                    const int i = atomicAdd(sched_ctr(W.sched, SCHED_HAND + large, sub), 1);
+                    W.fb_list[large ? hand_base(N, sub + 1) - 1 - i : hand_base(N, sub) + i] = (int32_t)n;
+                }
                 // FP64, two-wave class: a node beyond its capacities goes on
                 // to the four-wave kernel (the caller marks its list entry)
                 constexpr bool kHandOn = !F32 && CF::VM > kVmax && CF::VM < kVmaxBig;
@@ -1932,58 +1935,164 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
 // sink mode (end loops kept, vertices and fans hashed).
 enum { kModeMesh = 0, kModeRetri = 1, kModeRedo = 2, kModeSink = 3 };
 
-// Guided self-scheduling on a work counter shared by the grid: a block takes
-// a share of the items left (half of them over the grid, from what its last
-// grab saw), at least one and at most kGrabMax, as the range [first, end).  The counter is one address for the whole chip and its
-// atomics are serialised there: one per item throttled the node pass (a
-// pass without the trimming, the re-subdivision, took as long as a full
-// one); a few per block do not, and the last grabs are still single items.
-// Block-uniform; every thread of the block calls it.  Blocks at or beyond
-// the item count take nothing (a short list leaves most of the grid idle
-// without an atomic each).
+// Work distribution: a list in kSub sub-lists, each with its counter.  Block b
+// belongs to sub-list b mod kSub.  Its first range is given (no counter: a
+// list no longer than the grid takes no atomic at all), then it takes ranges
+// by guided self-scheduling, half of what its last grab saw left over its
+// sub-list's blocks, at least one and at most kGrabMax.  When its own is used
+// up it helps with the others, which it finds by reading all counters at once.
+// With one counter for the list, every block's first grab, every further one
+// and a last, futile one stood in line for it: a pass over some 10^4 nodes was
+// bound by that: the launch for the 7.8 k nodes of 12 struts of octet 13^3
+// 163 -> 105 us, k-NN 19^3 (6.9 k nodes, most of them handed to FP64 through
+// one more counter) 677 -> 448 us per step, 24 mixed parts 2.78 -> 2.26 ms.
+// Every block reaches the end: a grab that fails has found its counter past
+// its sub-list's end, and counters only grow.
+// Block-uniform; every thread of the block calls it.
 constexpr int kGrabMax = 16;
-__device__ inline bool grab_items(int32_t *ctr, int64_t items, int64_t &seen, int *s_grab, int64_t &first,
-                                  int64_t &end)
+__device__ inline int lane_value(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
+
+// A list: `items` dealt to the sub-lists in tiles of 1 << t (adjacent nodes to
+// one block where there are many), or, with hand set, sub-lists whose lengths
+// are those counters.
+struct List {
+    int32_t *ctr;         // the list's first work counter
+    int32_t *hand;
+    int items, t;
+};
+__device__ inline List dealt_list(int32_t *sched, int list, int64_t items)
 {
-    if ((int64_t)blockIdx.x >= items) return false;
-    if (threadIdx.x == 0) {
-        int64_t g = (items - seen) / (2 * (int64_t)gridDim.x);
-        g = g < 1 ? 1 : (g > kGrabMax ? kGrabMax : g);
-        s_grab[0] = atomicAdd(ctr, (int)g);
-        s_grab[1] = (int)g;
-    }
-    __syncthreads();
-    first = s_grab[0];
-    const int g = s_grab[1];
-    __syncthreads();
-    seen = first + g;
-    end = seen < items ? seen : items;
-    return first < items;
+    return List{sched_ctr(sched, list, 0), nullptr, (int)items, items >= 32 * (int64_t)gridDim.x ? 4 : 0};
+}
+// length of sub-list l (0 from kSub on)
+__device__ inline int sub_len(const List &q, int l)
+{
+    if (l >= kSub) return 0;
+    if (q.hand) return q.hand[l * kSchedLine];
+    const int64_t items = q.items, tiles = (items + (1 << q.t) - 1) >> q.t, mine = (tiles - l + kSub - 1) / kSub;
+    const bool last = (tiles - 1) % kSub == l;  // holds the last, maybe short, tile
+    return items > 0 && mine > 0 ? (int)((mine << q.t) - (last ? (tiles << q.t) - items : 0)) : 0;
+}
+// the item that is the i-th of sub-list c of a dealt list
+__device__ inline int64_t dealt_item(int t, int c, int i)
+{
+    return ((((int64_t)(i >> t) * kSub) + c) << t) + (i & ((1 << t) - 1));
 }
 
-template <typename C, int MODE>
-__device__ inline void drain_class(const Params &P, int cls, Shared<float, C> *sh, int *s_grab)
+// items of a first range, and of those of all blocks l, l + kSub, ... of the
+// grid, which start on sub-list l of n items
+__device__ inline int first_range(int n)
 {
-    constexpr int NPW = 64 / C::W;
-    const int slot = threadIdx.x / C::W;
+    const int g = n / (2 * (((int)gridDim.x + kSub - 1) / kSub));
+    return g < 1 ? 1 : (g > kGrabMax ? kGrabMax : g);
+}
+__device__ inline int first_ranges(int n, int l)
+{
+    return l < kSub ? first_range(n) * (((int)gridDim.x - l + kSub - 1) / kSub) : 0;
+}
+
+struct Grab {
+    int c, seen;     // the sub-list worked on (-1: the list is used up), and what of it the last grab saw taken
+    int first, end;  // the range
+};
+
+// the block's first range; b: its rank in the grid
+__device__ inline Grab grab_first(const List &q, unsigned b)
+{
+    const int c = (int)(b % kSub), n = lane_value(sub_len(q, threadIdx.x & 63), c), g = first_range(n);
+    const int first = (int)(b / kSub) * g;
+    return Grab{c, first_ranges(n, c), first, first + g < n ? first + g : n};
+}
+
+// The next range, by one wave.  A function of its own: few calls per block,
+// and inlined its bookkeeping took 25 registers through the node's whole
+// computation.
+__device__ __attribute__((noinline)) Grab grab_more(List q, int c, int seen)
+{
+    const int lane = threadIdx.x & 63, blocks = ((int)gridDim.x + kSub - 1) / kSub;
+    const int mine = sub_len(q, lane), pre = first_ranges(mine, lane);
+    for (;;) {
+        const int n = lane_value(mine, c);
+        if (seen < n) {
+            int g = (n - seen) / (2 * blocks), v = 0;
+            g = g < 1 ? 1 : (g > kGrabMax ? kGrabMax : g);
+            if (lane == 0) v = atomicAdd(q.ctr + c * kSchedLine, g);
+            const int first = lane_value(pre, c) + __builtin_amdgcn_readfirstlane(v);
+            seen = first + g;
+            if (first < n) return Grab{c, seen, first, seen < n ? seen : n};
+        }
+        // what is left of every sub-list: none, where first ranges were all
+        int left = mine - pre;
+        if (left > 0)
+            left -= __hip_atomic_load(q.ctr + lane * kSchedLine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long m = __ballot(left > 0);
+        if (m == 0) return Grab{-1, 0, 0, 0};
+        const unsigned long long after = m & ~((2ull << c) - 1);
+        c = __builtin_ctzll(after ? after : m);
+        seen = lane_value(mine, c) - lane_value(left, c);
+    }
+}
+
+// f(sub-list, place in it) for the items of the list that fall to this block,
+// whose every thread calls it; b: its rank in the grid
+template <typename F>
+__device__ __forceinline__ void drain(const List &q, unsigned b, int *s_grab, F &&f)
+{
+    Grab G = grab_first(q, b);
+    for (;;) {
+        for (int i = G.first; i < G.end; ++i) {
+            f(G.c, i);
+            __syncthreads();
+        }
+        if (blockDim.x == 64) {
+            G = grab_more(q, __builtin_amdgcn_readfirstlane(G.c), __builtin_amdgcn_readfirstlane(G.seen));
+        } else {
+            if (threadIdx.x < 64) {
+                G = grab_more(q, __builtin_amdgcn_readfirstlane(G.c), __builtin_amdgcn_readfirstlane(G.seen));
+                if (threadIdx.x == 0) {
+                    s_grab[0] = G.c;
+                    s_grab[1] = G.seen;
+                    s_grab[2] = G.first;
+                    s_grab[3] = G.end;
+                }
+            }
+            __syncthreads();
+            G = Grab{s_grab[0], s_grab[1], s_grab[2], s_grab[3]};
+            __syncthreads();
+        }
+        G.c = __builtin_amdgcn_readfirstlane(G.c);
+        G.seen = __builtin_amdgcn_readfirstlane(G.seen);
+        G.first = __builtin_amdgcn_readfirstlane(G.first);
+        G.end = __builtin_amdgcn_readfirstlane(G.end);
+        if (G.c < 0) return;
+    }
+}
+
+// b: the block's rank; returns the number of blocks with a first range, so
+// that a list drained after this one can start with the others
+template <typename C, int MODE>
+__device__ inline int drain_class(const Params &P, int cls, Shared<float, C> *sh, int *s_grab, unsigned b)
+{
+    constexpr int NPW = C::W <= 64 ? 64 / C::W : 1;
+    const int slot = C::W <= 64 ? threadIdx.x / C::W : 0;
     const int64_t cnt = MODE == kModeRedo ? (int64_t)P.redo_cnt[cls] : P.w.cls_info[cls];
     const int64_t base = P.w.cls_info[4 + cls];
     const int32_t *list = MODE == kModeRedo ? P.redo : P.w.queue;
-    int32_t *ctr = MODE == kModeRedo ? P.redo_ctr : P.w.work_ctr;
     const int64_t items = (cnt + NPW - 1) / NPW;
-    int64_t seen = 0, first, end;
-    while (grab_items(&ctr[cls], items, seen, s_grab, first, end)) {
-        for (int64_t item = first; item < end; ++item) {
-            const int64_t qi = item * NPW + slot;
-            if (qi < cnt) {
-                const int64_t node = list[base + qi];
-                if (MODE == kModeRetri) node_retri<C>(P, sh[slot], node, cls);
-                else if (MODE == kModeSink) node_body<float, C, true>(P, sh[slot], node);
-                else node_body<float, C>(P, sh[slot], node);
-            }
-            __syncthreads();
+    const List q = dealt_list(P.w.sched, (MODE == kModeRedo ? SCHED_REDO : SCHED_CLASS) + cls, items);
+    drain(q, b, s_grab, [&](int c, int i) {
+        const int64_t qi = dealt_item(q.t, c, i) * NPW + slot;
+        if (qi >= cnt) return;
+        const int64_t node = list[base + qi];
+        if constexpr (MODE == kModeRetri) {
+            if constexpr (C::W <= 64) node_retri<C>(P, sh[slot], node, cls);
+            // a multi-wave node's record is not read: solved in full
+            else if (threadIdx.x == 0) P.redo[base + atomicAdd(&P.redo_cnt[cls], 1)] = (int32_t)node;
+        } else {
+            node_body<float, C, MODE == kModeSink>(P, sh[slot], node);
         }
-    }
+    });
+    return (int)(items < (int64_t)gridDim.x ? items : 0);
 }
 
 // At most 128 VGPRs and 10,240 bytes of LDS per block: four waves per SIMD.
@@ -1996,8 +2105,7 @@ template <typename C, int MODE>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_node32(Params P, int cls)
 {
     __shared__ Shared<float, C> sh[64 / C::W];
-    __shared__ int s_grab[2];
-    drain_class<C, MODE>(P, cls, sh, s_grab);
+    drain_class<C, MODE>(P, cls, sh, nullptr, blockIdx.x);
 }
 
 // The classes v <= 4 (four nodes per wave) and 5..8 (two) in one persistent
@@ -2012,38 +2120,19 @@ template <int MODE>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_node32_v8v4(Params P)
 {
     __shared__ SharedV4V8 sh;
-    __shared__ int s_grab[2];
-    drain_class<CfgV8, MODE>(P, 1, sh.b, s_grab);
-    drain_class<CfgV4, MODE>(P, 0, sh.a, s_grab);
+    const unsigned used = (unsigned)drain_class<CfgV8, MODE>(P, 1, sh.b, nullptr, blockIdx.x);
+    drain_class<CfgV4, MODE>(P, 0, sh.a, nullptr, (blockIdx.x + gridDim.x - used) % gridDim.x);
 }
 
 // The multi-wave class: one node per block of kBigWaves waves, items from the
 // class's work counter as above.  Re-subdivision does not read these nodes'
 // records: they are queued for a full solve (MODE 1), which MODE 2 runs.
 template <int MODE>
-__global__ void __launch_bounds__(64 * kBigWaves) k_node32_big(Params P)
+__global__ void __launch_bounds__(64 * kBigWaves) __attribute__((amdgpu_waves_per_eu(4))) k_node32_big(Params P)
 {
-    constexpr int cls = 3;
     __shared__ Shared<float, CfgBig> sh;
-    __shared__ int s_grab[2];
-    const int64_t cnt = MODE == kModeRedo ? (int64_t)P.redo_cnt[cls] : P.w.cls_info[cls];
-    const int64_t base = P.w.cls_info[4 + cls];
-    const int32_t *list = MODE == kModeRedo ? P.redo : P.w.queue;
-    int32_t *ctr = MODE == kModeRedo ? P.redo_ctr : P.w.work_ctr;
-    int64_t seen = 0, first, end;
-    while (grab_items(&ctr[cls], cnt, seen, s_grab, first, end)) {
-        for (int64_t item = first; item < end; ++item) {
-            const int64_t node = list[base + item];
-            if (MODE == kModeRetri) {
-                if (threadIdx.x == 0) P.redo[base + atomicAdd(&P.redo_cnt[cls], 1)] = (int32_t)node;
-            } else if (MODE == kModeSink) {
-                node_body<float, CfgBig, true>(P, sh, node);
-            } else {
-                node_body<float, CfgBig>(P, sh, node);
-            }
-            __syncthreads();
-        }
-    }
+    __shared__ int s_grab[4];
+    drain_class<CfgBig, MODE>(P, 3, &sh, s_grab, blockIdx.x);
 }
 
 // Thread-centric ablation: every lane meshes a node of its own (64 nodes per
@@ -2069,32 +2158,28 @@ template <typename C, bool SINK>
 __global__ void __launch_bounds__(C::W) __attribute__((amdgpu_waves_per_eu(2))) k_node64(Params P)
 {
     __shared__ Shared<double, C> sh;
-    __shared__ int s_grab[2];
+    __shared__ int s_grab[4];
     // the kernel's class: 0 one wave (v <= kVmax), 1 two waves (v <= kVmaxMid),
     // 2 four waves; the launches run in that order
     constexpr int cls = C::VM <= kVmax ? 0 : (C::VM <= kVmaxMid ? 1 : 2);
-    constexpr int ctr = cls == 0 ? 4 : (cls == 1 ? 6 : 5);
-    const int64_t cnt = P.w.flags[2];
-    // guided grabs over the hand-over list (its nodes differ in cost)
-    int64_t seen = 0, first, end;
-    while (grab_items(&P.w.work_ctr[ctr], cnt, seen, s_grab, first, end)) {
-        for (int64_t i = first; i < end; ++i) {
-            // an entry the two-wave kernel could not hold is stored negated
-            // (~node): the four-wave kernel takes it whatever its valence
-            const int32_t e = P.w.fb_list[i];
-            const int64_t node = e < 0 ? ~e : e;
+    const int64_t N = P.in.n_nodes;
+    const List q{sched_ctr(P.w.sched, SCHED_FP64 + cls, 0), sched_ctr(P.w.sched, SCHED_HAND + (cls ? 1 : 0), 0), 0, 0};
+    drain(q, blockIdx.x, s_grab, [&](int c, int i) {
+        const int64_t at = cls ? hand_base(N, c + 1) - 1 - i : hand_base(N, c) + i;
+        // an entry the two-wave kernel could not hold is stored negated
+        // (~node): the four-wave kernel takes it whatever its valence
+        const int32_t e = P.w.fb_list[at];
+        const int64_t node = e < 0 ? ~e : e;
+        if constexpr (cls != 0) {
             const int64_t v = P.w.row[node + 1] - P.w.row[node];
-            const int ncls = e < 0 ? 2 : (v <= kVmax ? 0 : (v <= kVmaxMid ? 1 : 2));
-            if (ncls == cls) {
-                node_body<double, C, SINK>(P, sh, node);
-                if constexpr (cls == 1) {
-                    __syncthreads();
-                    if (threadIdx.x == 0 && (sh.status & NS_CAPACITY)) P.w.fb_list[i] = ~(int32_t)node;
-                }
-            }
-            __syncthreads();
+            if ((e < 0 || v > kVmaxMid) != (cls == 2)) return;
         }
-    }
+        node_body<double, C, SINK>(P, sh, node);
+        if constexpr (cls == 1) {
+            __syncthreads();
+            if (threadIdx.x == 0 && (sh.status & NS_CAPACITY)) P.w.fb_list[at] = ~(int32_t)node;
+        }
+    });
 }
 
 constexpr unsigned kFp64Grid = 2048;
@@ -2126,7 +2211,6 @@ hipError_t launch_node_thread(const Inputs &in, const Work &w, int k, float kapp
     P.src_node_rec = nullptr;
     P.redo = nullptr;
     P.redo_cnt = nullptr;
-    P.redo_ctr = nullptr;
     P.sink = SinkOut{};
     const int64_t blocks = (in.n_nodes + 63) / 64;
     k_node32_thread<<<(unsigned)(blocks < kThreadGrid ? blocks : kThreadGrid), 64, 0, st>>>(
@@ -2149,7 +2233,6 @@ hipError_t launch_node(const Inputs &in, const Work &w, int k, float kappa_max, 
     P.src_node_rec = src_node_rec;
     P.redo = redo;
     P.redo_cnt = redo_cnt;
-    P.redo_ctr = redo_cnt ? redo_cnt + 4 : nullptr;
     if (fp64) {
         if (sink) {
             k_node64<CfgV16, true><<<kFp64Grid, 64, 0, st>>>(P);

@@ -317,7 +317,6 @@ __global__ void k_range_done(int32_t *flags, int32_t *fail, int64_t r)
     if (threadIdx.x != 0) return;
     fail[r] = flags[0] & DF_RECCAP;
     flags[0] = 0;
-    flags[2] = 0;
 }
 
 // zero the per-part slots of parts [p0, p1)

@@ -204,7 +204,8 @@ __global__ void __launch_bounds__(64) k_zip(int64_t S, const int64_t *band_off, 
 
 // Totals (device) and capacity checks for the fill pass.
 __global__ void k_totals(int64_t N, int64_t S, const int64_t *node_off, const unsigned long long *rec_top,
-                         const int64_t *band_off, FillOut o, int check, int64_t *totals, int32_t *flags)
+                         int32_t *sched, const int64_t *band_off, FillOut o, int check, int64_t *totals,
+                         int32_t *flags)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const int64_t Np1 = N + 1;
@@ -222,7 +223,9 @@ __global__ void k_totals(int64_t N, int64_t S, const int64_t *node_off, const un
     totals[5] = nb;
     totals[6] = nf;
     totals[7] = nl;
-    totals[10] = flags[2];
+    int64_t handed = 0;
+    for (int c = 0; c < 2 * kSub; ++c) handed += *sched_ctr(sched, SCHED_HAND + c / kSub, c % kSub);
+    totals[10] = handed;
     if (nm > 0x7fffffffLL) atomicOr(flags, DF_RECCAP);
     if (check) {
         bool bad = nm > o.cap_mesh || nb + nf > o.cap_tri;
@@ -270,7 +273,7 @@ hipError_t launch_zip(const Inputs &in, const Work &w, const FillOut &o, int k, 
 hipError_t launch_totals(const Inputs &in, const Work &w, const FillOut *o, hipStream_t st)
 {
     FillOut oo = o ? *o : FillOut{};
-    k_totals<<<1, 64, 0, st>>>(in.n_nodes, in.n_struts, w.node_off, w.rec_top, w.band_off, oo, o ? 1 : 0,
+    k_totals<<<1, 64, 0, st>>>(in.n_nodes, in.n_struts, w.node_off, w.rec_top, w.sched, w.band_off, oo, o ? 1 : 0,
                                w.totals, w.flags);
     return hipGetLastError();
 }
