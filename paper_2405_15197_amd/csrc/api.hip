@@ -24,7 +24,7 @@ struct lm_plan {
     void *sink_mem = nullptr;
     int32_t *sk_mark = nullptr;     // [N] epoch of the last range listing the node
     int32_t *sk_lists = nullptr;    // [kClasses][N + 1] range node lists
-    int32_t *sk_cnt = nullptr;      // [8] list sizes, then the strut count
+    int32_t *sk_cnt = nullptr;      // [8] the range's strut count
     int64_t *sk_info = nullptr;     // [8] class sizes / starts for the node kernel
     int32_t *sk_struts = nullptr;   // [S + 1] struts owned by the range
     int32_t *sk_fail = nullptr;     // [N + 1] per range: records overflowed
@@ -65,12 +65,6 @@ struct lm_plan {
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> ev;
     std::vector<hipEvent_t> pool;
 };
-
-__global__ void lm_k_status_u8(const int32_t *s, uint8_t *d, int64_t n)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) d[i] = (uint8_t)s[i];
-}
 
 namespace {
 
@@ -131,8 +125,9 @@ struct Carver {
     }
 };
 
-// The fixed workspace: adjacency, counts, offsets, queues, flags.
-void carve_fixed(lm_plan *P, Carver &c, int64_t N, int64_t S)
+// The fixed workspace: adjacency, counts, offsets, queues, flags.  Without
+// `sizes`, for sink mode only.
+void carve_fixed(lm_plan *P, Carver &c, int64_t N, int64_t S, bool sizes = true)
 {
     lm::Work &w = P->w;
     const int64_t H = 2 * S;
@@ -148,9 +143,7 @@ void carve_fixed(lm_plan *P, Carver &c, int64_t N, int64_t S)
     w.he_rot = c.take<int32_t>(H + 1);
     w.band_cnt = c.take<int32_t>(S + 1);
     w.band_off = c.take<int64_t>(S + 1);
-    int64_t tl = lm::scan_tmp_needed(N, lm::kNodeScanCols);
-    const int64_t t2 = lm::scan_tmp_needed(S, 1);
-    if (t2 > tl) tl = t2;
+    const int64_t tl = lm::scan_tmp_needed(N, S, sizes);
     w.scan_tmp = c.take<int64_t>(tl);
     w.scan_tmp_len = tl;
     w.flags = c.take<int32_t>(4);
@@ -249,20 +242,40 @@ lm::FillOut to_fill(const lm_outputs *o)
     return f;
 }
 
+lm::OffsetsOut to_offsets(const lm_outputs *o)
+{
+    return lm::OffsetsOut{o->d_node_off, o->d_strut_off, o->d_node_status};
+}
+
+// what every node pass starts from at zero: flags[0], the records' bump
+// counters, the work counters
+lm::ClearRuns begin_pass(const lm::Work &w)
+{
+    lm::ClearRuns c;
+    c.p[0] = (uint32_t *)w.flags;
+    c.n[0] = 1;
+    c.p[1] = (uint32_t *)w.rec_top;
+    c.n[1] = 2 * lm::kRecRegions;
+    c.p[2] = (uint32_t *)w.sched;
+    c.n[2] = lm::kSchedWords;
+    return c;
+}
+
 // Node pass (meta-meshing at k, or with src_rec set the re-subdivision of
 // the meta-mesh in those records) into the records of w, then band counts,
 // prefix sums and device totals (and capacity flags when out != nullptr).
-int run_count(lm_plan *P, int k, const lm::FillOut *out, const lm::Work &w, const uint32_t *src_rec = nullptr,
-              const int64_t *src_node_rec = nullptr, int32_t *redo = nullptr, int32_t *redo_cnt = nullptr)
+int run_count(lm_plan *P, int k, const lm::FillOut *out, const lm::OffsetsOut &off, const lm::Work &w,
+              const uint32_t *src_rec = nullptr, const int64_t *src_node_rec = nullptr, int32_t *redo = nullptr,
+              int32_t *redo_cnt = nullptr)
 {
-    const int64_t N = P->in.n_nodes, S = P->in.n_struts;
-    HIPCHK(hipMemsetAsync(w.flags, 0, sizeof(int32_t), P->st));  // count / fill
-    HIPCHK(hipMemsetAsync(w.totals, 0, sizeof(int64_t) * 16, P->st));
-    HIPCHK(hipMemsetAsync(w.rec_top, 0, sizeof(unsigned long long) * lm::kRecRegions, P->st));
-    HIPCHK(hipMemsetAsync(w.sched, 0, sizeof(int32_t) * lm::kSchedWords, P->st));
+    lm::ClearRuns c = begin_pass(w);
+    c.p[3] = (uint32_t *)w.totals;
+    c.n[3] = 2 * 16;
+    c.p[4] = (uint32_t *)redo_cnt;
+    c.n[4] = redo_cnt ? 8 : 0;
+    HIPCHK(lm::launch_clear(c, P->st));
     {
         PhaseTimer t(P, PH_NODE32);
-        if (redo_cnt) HIPCHK(hipMemsetAsync(redo_cnt, 0, sizeof(int32_t) * 8, P->st));
         if (P->schedule == LM_SCHEDULE_THREAD && !src_rec) {
             if (!P->thread_scratch) HIPCHK(hipMalloc(&P->thread_scratch, lm::node_thread_scratch_bytes()));
             HIPCHK(lm::launch_node_thread(P->in, w, k, P->kappa_max, P->thread_scratch, P->st));
@@ -276,11 +289,7 @@ int run_count(lm_plan *P, int k, const lm::FillOut *out, const lm::Work &w, cons
         HIPCHK(lm::launch_node(P->in, w, k, P->kappa_max, 1, P->st, src_rec, src_node_rec));
     }
     PhaseTimer t(P, PH_SIZES);
-    HIPCHK(lm::launch_band_count(P->in, w, P->st));
-    HIPCHK(lm::launch_scan(w.node_cnt, w.node_off, N, lm::kNodeScanCols, N, N + 1, w.scan_tmp, w.scan_tmp_len,
-                           P->st));
-    HIPCHK(lm::launch_scan(w.band_cnt, w.band_off, S, 1, 0, 0, w.scan_tmp, w.scan_tmp_len, P->st));
-    HIPCHK(lm::launch_totals(P->in, w, out, P->st));
+    HIPCHK(lm::launch_sizes(P->in, w, out, off, P->st));
     return LM_OK;
 }
 
@@ -324,29 +333,14 @@ int ensure_rec(lm_plan *P, int64_t words)
     return LM_OK;
 }
 
-int fill_common(lm_plan *P, int k, const lm::FillOut &f, const lm_outputs *out, const lm::Work &w)
+int fill_common(lm_plan *P, int k, const lm::FillOut &f, const lm::Work &w)
 {
-    const int64_t N = P->in.n_nodes;
     {
         PhaseTimer t(P, PH_EXPAND);
         HIPCHK(lm::launch_expand(P->in, w, f, P->st));
     }
-    {
-        PhaseTimer t(P, PH_ZIP);
-        HIPCHK(lm::launch_zip(P->in, w, f, k, P->st));
-    }
-    if (out->d_node_off)
-        HIPCHK(hipMemcpyAsync(out->d_node_off, w.node_off, sizeof(int64_t) * lm::kNodeScanCols * (N + 1),
-                              hipMemcpyDeviceToDevice, P->st));
-    if (out->d_strut_off)
-        HIPCHK(hipMemcpyAsync(out->d_strut_off, w.band_off, sizeof(int64_t) * (P->in.n_struts + 1),
-                              hipMemcpyDeviceToDevice, P->st));
-    if (out->d_node_status && N > 0) {
-        // int32 status column -> uint8 (values fit in 8 bits)
-        lm_k_status_u8<<<(unsigned)((N + 255) / 256), 256, 0, P->st>>>(
-            w.node_cnt + (int64_t)lm::NC_STATUS * N, out->d_node_status, N);
-        HIPCHK(hipGetLastError());
-    }
+    PhaseTimer t(P, PH_ZIP);
+    HIPCHK(lm::launch_zip(P->in, w, f, k, P->st));
     return LM_OK;
 }
 
@@ -390,12 +384,26 @@ lm_plan *new_plan(const lm_lattice *lat, void *stream)
     return P;
 }
 
-// Validation and adjacency of a new plan (synchronises).
-int first_prepare(lm_plan *P)
+// Validation and adjacency of a new plan (synchronises).  With sink, what sink
+// mode expects at zero is cleared as well (node marks, slots, and the failure
+// flag of range 0).
+int first_prepare(lm_plan *P, bool sink = false)
 {
     int32_t fl = 0;
-    if (hipMemsetAsync(P->w.flags, 0, sizeof(int32_t) * 4, P->st) != hipSuccess ||
-        hipMemsetAsync(P->w.totals, 0, sizeof(int64_t) * 16, P->st) != hipSuccess ||
+    lm::ClearRuns c;
+    c.p[0] = (uint32_t *)P->w.flags;
+    c.n[0] = 4;
+    c.p[1] = (uint32_t *)P->w.totals;
+    c.n[1] = 2 * 16;
+    if (sink) {
+        c.p[2] = (uint32_t *)P->sk_mark;
+        c.n[2] = P->in.n_nodes + 1;
+        c.p[3] = (uint32_t *)P->sk_slots;
+        c.n[3] = 2 * lm::sink_slots_words();
+        c.p[4] = (uint32_t *)P->sk_fail;
+        c.n[4] = 1;
+    }
+    if (lm::launch_clear(c, P->st) != hipSuccess ||
         lm::launch_prepare(P->in, P->w, P->st) != hipSuccess ||
         hipMemcpyAsync(&fl, P->w.flags + 1, sizeof(int32_t), hipMemcpyDeviceToHost, P->st) != hipSuccess ||
         hipMemcpyAsync(P->cls_est, P->w.cls_info, sizeof(P->cls_est), hipMemcpyDeviceToHost, P->st) != hipSuccess ||
@@ -406,12 +414,14 @@ int first_prepare(lm_plan *P)
     return LM_OK;
 }
 
-// Carves (or, with base null, sizes) every part of a caller-owned workspace.
-size_t ws_layout(lm_plan *P, void *base, int64_t N, int64_t S, const lm_options &o, bool sched = true)
+// Carves (or, with base null, sizes) every part of a caller-owned workspace,
+// or of lm_forward_sink_static's array.
+size_t ws_layout(lm_plan *P, void *base, int64_t N, int64_t S, const lm_options &o, bool fixed_array = false)
 {
     Carver c(base);
-    carve_fixed(P, c, N, S);
-    if (sched) carve_sched(P, c);
+    carve_fixed(P, c, N, S, !fixed_array);
+    if (fixed_array) (void)c.take<int32_t>(8);  // the array's published sizes: its counters are beside it
+    else carve_sched(P, c);
     if (o.flags & LM_WS_GRADIENT) carve_grad(P, c, N, S);
     if (o.flags & LM_WS_SINK) {
         carve_sink(P, c, N, S);
@@ -485,15 +495,7 @@ int lm_plan_create_in(lm_plan **plan, const lm_lattice *lat, const lm_options *o
         return LM_ERR_CAPACITY;
     }
     ws_layout(P, d_workspace, lat->n_nodes, lat->n_struts, o);
-    if (o.flags & LM_WS_SINK) {
-        if (hipMemsetAsync(P->sk_mark, 0, sizeof(int32_t) * (lat->n_nodes + 1), P->st) != hipSuccess ||
-            hipMemsetAsync(P->sk_slots, 0, sizeof(unsigned long long) * lm::sink_slots_words(), P->st) !=
-                hipSuccess) {
-            delete P;
-            return LM_ERR_HIP;
-        }
-    }
-    if ((rc = first_prepare(P))) {
+    if ((rc = first_prepare(P, o.flags & LM_WS_SINK))) {
         delete P;
         return rc;
     }
@@ -581,7 +583,7 @@ int lm_count(lm_plan *P, int k, lm_totals *totals)
     P->k = 0;
     P->last_on_host = false;
     for (int attempt = 0; attempt < 2; ++attempt) {
-        if ((rc = run_count(P, k, nullptr, P->w))) return rc;
+        if ((rc = run_count(P, k, nullptr, lm::OffsetsOut{}, P->w))) return rc;
         if ((rc = read_totals(P, totals, &fl))) return rc;
         if (totals->n_mesh_vertices > 0x7fffffffLL) return LM_ERR_UNSUPPORTED;
         if (!(fl & lm::DF_RECCAP)) break;
@@ -606,7 +608,8 @@ int lm_fill(lm_plan *P, const lm_outputs *out)
     if (f.vert_name && out->cap_vertices < t.n_vertices) return LM_ERR_CAPACITY;
     if (f.arc_f32 && out->cap_arcs < t.n_arcs) return LM_ERR_CAPACITY;
     if (P->base_slot != 0) return LM_ERR_STATE;  // re-subdivided since lm_count
-    return fill_common(P, P->k, f, out, P->w);
+    HIPCHK(lm::launch_copy_offsets(P->in, P->w, to_offsets(out), P->st));
+    return fill_common(P, P->k, f, P->w);
 }
 
 int lm_forward(lm_plan *P, int k, const lm_outputs *out)
@@ -615,12 +618,12 @@ int lm_forward(lm_plan *P, int k, const lm_outputs *out)
     lm::FillOut f = to_fill(out);
     int rc = LM_OK;
     if (P->w.rec_words == 0 && (rc = ensure_rec(P, rec_estimate(P, k)))) return rc;
-    rc = run_count(P, k, &f, P->w);
+    rc = run_count(P, k, &f, to_offsets(out), P->w);
     if (rc) return rc;
     P->k = k;
     P->base_slot = 0;
     P->last_on_host = false;
-    return fill_common(P, k, f, out, P->w);
+    return fill_common(P, k, f, P->w);
 }
 
 }  // extern "C"
@@ -731,21 +734,25 @@ int sink_range(lm_plan *P, int k, int64_t r, int64_t n0, int64_t n1, int t16, in
 {
     const int64_t N = P->in.n_nodes;
     lm::Work &w = P->w;
-    HIPCHK(hipMemsetAsync(P->sk_cnt, 0, sizeof(int32_t) * 8, P->st));
+    lm::ClearRuns c = begin_pass(w);
+    c.n[0] = 0;  // flags[0] was read and cleared after the range before
+    c.p[3] = (uint32_t *)P->sk_cnt;
+    c.n[3] = 1;
+    c.p[4] = (uint32_t *)P->sk_info;
+    c.n[4] = 2 * 8;
+    HIPCHK(lm::launch_clear(c, P->st));
     if (++P->sk_epoch <= 0) {  // epochs wrapped: clear the marks
         HIPCHK(hipMemsetAsync(P->sk_mark, 0, sizeof(int32_t) * (N + 1), P->st));
         P->sk_epoch = 1;
     }
     {
         PhaseTimer t(P, PH_SIZES);
-        HIPCHK(lm::launch_chunk_list(w, n0, n1, P->sk_mark, P->sk_epoch, P->sk_lists, N + 1, P->sk_cnt, P->sk_info,
-                                     t16, t32, P->st));
+        HIPCHK(lm::launch_chunk_list(w, n0, n1, P->sk_mark, P->sk_epoch, P->sk_lists, N + 1, P->sk_info, t16, t32,
+                                     P->st));
     }
     lm::Work wc = w;
     wc.queue = P->sk_lists;
     wc.cls_info = P->sk_info;
-    HIPCHK(hipMemsetAsync(w.rec_top, 0, sizeof(unsigned long long) * lm::kRecRegions, P->st));
-    HIPCHK(hipMemsetAsync(w.sched, 0, sizeof(int32_t) * lm::kSchedWords, P->st));
     so.n0 = n0;
     so.n1 = n1;
     {
@@ -756,11 +763,9 @@ int sink_range(lm_plan *P, int k, int64_t r, int64_t n0, int64_t n1, int t16, in
         PhaseTimer t(P, PH_NODE64);
         HIPCHK(lm::launch_node(P->in, wc, k, P->kappa_max, 1, P->st, nullptr, nullptr, nullptr, nullptr, &so));
     }
-    HIPCHK(lm::launch_range_done(w.flags, P->sk_fail, r, P->st));
-    HIPCHK(hipMemsetAsync(P->sk_cnt + 4, 0, sizeof(int32_t), P->st));
     {
         PhaseTimer t(P, PH_ZIP);
-        HIPCHK(lm::launch_sink_bands(P->in, w, n0, n1, k, P->sk_struts, P->sk_cnt + 4, so, P->st));
+        HIPCHK(lm::launch_sink_bands(P->in, w, n0, n1, k, P->sk_struts, P->sk_cnt, P->sk_fail + r, so, P->st));
     }
     if (out_chunk) HIPCHK(lm::launch_sink_reduce(P->sk_slots, out_chunk, P->st));
     return LM_OK;
@@ -777,8 +782,12 @@ int sink_ranges(lm_plan *P, const std::vector<int64_t> &bound, const std::vector
     const int64_t R = (int64_t)bound.size() - 1;
     int rc = ensure_rec(P, rec_words);
     if (rc && rc != LM_ERR_CAPACITY) return rc;  // caller-owned space: try with what there is
-    HIPCHK(hipMemsetAsync(P->w.flags, 0, sizeof(int32_t) * 3, P->st));
-    HIPCHK(hipMemsetAsync(P->sk_fail, 0, sizeof(int32_t) * (R + 1), P->st));
+    lm::ClearRuns c;
+    c.p[0] = (uint32_t *)P->w.flags;
+    c.n[0] = 3;
+    c.p[1] = (uint32_t *)P->sk_fail;
+    c.n[1] = R + 1;
+    HIPCHK(lm::launch_clear(c, P->st));
     for (int64_t r = 0; r < R; ++r)
         if ((rc = sink_range(P, kmax[r], r, bound[r], bound[r + 1], t16, t32, so,
                              d_out_chunks ? d_out_chunks + r * LM_SINK_WORDS : nullptr)))
@@ -966,9 +975,9 @@ int lm_retriangulate(lm_plan *P, int k, const lm_outputs *out)
         wd = P->w;
     }
     lm::FillOut f = to_fill(out);
-    int rc = run_count(P, k, &f, wd, src_rec, src_node_rec, P->redo, P->redo_cnt);
+    int rc = run_count(P, k, &f, to_offsets(out), wd, src_rec, src_node_rec, P->redo, P->redo_cnt);
     if (rc) return rc;
-    rc = fill_common(P, k, f, out, wd);
+    rc = fill_common(P, k, f, wd);
     if (rc) return rc;
     if (base_in_w) {  // the new records become current; the meta-mesh moves to the other slot
         std::swap(P->w.rec, P->alt_rec);
@@ -991,8 +1000,12 @@ int lm_arc_encode(lm_plan *P, const float *d_arc_f32, const uint32_t *d_arc_u32,
         return LM_ERR_CAPACITY;
     *n_fallback = 0;
     if (n_arcs == 0) return LM_OK;
-    HIPCHK(hipMemsetAsync(P->codec_ctr, 0, sizeof(unsigned long long), P->st));
-    HIPCHK(hipMemsetAsync(c->d_fallback_mask, 0, sizeof(uint32_t) * ((n_arcs + 31) / 32), P->st));
+    lm::ClearRuns cl;
+    cl.p[0] = (uint32_t *)P->codec_ctr;
+    cl.n[0] = 2;
+    cl.p[1] = c->d_fallback_mask;
+    cl.n[1] = (n_arcs + 31) / 32;
+    HIPCHK(lm::launch_clear(cl, P->st));
     HIPCHK(lm::launch_arc_codec(P->in, P->w, true, d_arc_f32, d_arc_u32, n_arcs, ld, (double)r_min, (double)r_max,
                                 c->d_codes, c->d_fallback_mask, c->d_fallback, c->cap_fallback, P->codec_ctr,
                                 nullptr, 0, P->st));
@@ -1031,7 +1044,6 @@ int lm_prepare(lm_plan *P)
 {
     if (!P) return LM_ERR_INVALID_ARG;
     PhaseTimer t(P, PH_PREPARE);
-    HIPCHK(hipMemsetAsync(P->w.flags + 1, 0, sizeof(int32_t), P->st));
     HIPCHK(lm::launch_prepare(P->in, P->w, P->st));
     return LM_OK;
 }
@@ -1127,12 +1139,6 @@ const char *lm_status_string(int code)
 static __device__ __align__(256) unsigned char scratch[LM_STATIC_SCRATCH_BYTES];
 static __device__ __align__(256) int32_t scratch_sched[lm::kSchedWords];  // the plan's work counters
 
-__global__ void lm_k_fill_u32(uint32_t *p, uint32_t v, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 namespace {
 
 constexpr int kMaxDevices = 64;
@@ -1161,14 +1167,6 @@ int static_scratch(StaticMem *out)
     return LM_OK;
 }
 
-// Clears n 32-bit words with a kernel (no memset node).
-int fill_u32(void *p, int64_t n, hipStream_t st)
-{
-    if (n <= 0) return LM_OK;
-    lm_k_fill_u32<<<(unsigned)((n + 255) / 256), 256, 0, st>>>((uint32_t *)p, 0u, n);
-    return hipGetLastError() == hipSuccess ? LM_OK : LM_ERR_HIP;
-}
-
 }  // namespace
 
 extern "C" {
@@ -1184,7 +1182,7 @@ int lm_static_scratch_size(int64_t n_nodes, int64_t n_struts, int k, size_t *byt
     int rc = check_sizes(n_nodes, n_struts);
     if (rc) return rc;
     lm_plan tmp;
-    *bytes = ws_layout(&tmp, nullptr, n_nodes, n_struts, o, false);
+    *bytes = ws_layout(&tmp, nullptr, n_nodes, n_struts, o, true);
     return LM_OK;
 }
 
@@ -1199,7 +1197,10 @@ int lm_forward_sink_static(const lm_lattice *lat, int k, uint64_t *d_words, void
     hipStream_t st = (hipStream_t)stream;
     const int64_t N = lat->n_nodes;
     if (N == 0) {
-        if ((rc = fill_u32(d_words, 2 * LM_SINK_WORDS, st))) return rc;
+        lm::ClearRuns c;
+        c.p[0] = (uint32_t *)d_words;
+        c.n[0] = 2 * LM_SINK_WORDS;
+        HIPCHK(lm::launch_clear(c, st));
         return hipStreamSynchronize(st) == hipSuccess ? LM_OK : LM_ERR_HIP;
     }
     StaticMem mem;
@@ -1214,15 +1215,11 @@ int lm_forward_sink_static(const lm_lattice *lat, int k, uint64_t *d_words, void
     o.k_max = k;
     o.record_bytes = 0;
     o.max_parts = 0;
-    ws_layout(&P, mem.base, lat->n_nodes, lat->n_struts, o, false);
+    ws_layout(&P, mem.base, lat->n_nodes, lat->n_struts, o, true);
     P.w.sched = mem.sched;
-    // the array keeps the previous call's contents: clear what the sink
-    // range expects at zero (node marks, slots, the range's failure flag)
-    if ((rc = fill_u32(P.sk_mark, N + 1, st)) ||
-        (rc = fill_u32(P.sk_slots, 2 * lm::sink_slots_words(), st)) || (rc = fill_u32(P.sk_fail, 1, st)))
-        return rc;
-    if ((rc = first_prepare(&P))) return rc;  // synchronises; LM_ERR_BAD_LATTICE
-    if ((rc = fill_u32(P.w.flags, 3, st))) return rc;
+    // the array keeps the previous call's contents: what the sink range
+    // expects at zero is cleared with the preparation
+    if ((rc = first_prepare(&P, true))) return rc;  // synchronises; LM_ERR_BAD_LATTICE
     lm::SinkOut so{0, 0, P.sk_slots, nullptr, nullptr, nullptr};
     if ((rc = sink_range(&P, k, 0, 0, N, 4, 8, so, d_words))) return rc;
     int32_t fail = 0;

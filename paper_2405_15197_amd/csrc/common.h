@@ -345,8 +345,13 @@ hipError_t launch_prepare(const Inputs &in, const Work &w, hipStream_t st);
 hipError_t launch_end_radii(const Inputs &in, const Work &w, const float *end_r, float rel_tol, float *radius,
                             int32_t *mismatch, hipStream_t st);
 hipError_t launch_end_grad(const Inputs &in, const Work &w, const float *grad_r, float *grad_end, hipStream_t st);
-hipError_t launch_scan(const int32_t *src, int64_t *dst, int64_t n, int ncols, int64_t src_stride,
-                       int64_t dst_stride, int64_t *tmp, int64_t tmp_len, hipStream_t st);
+// runs of 32-bit words to clear (a kernel: no memset node when captured)
+struct ClearRuns {
+    static constexpr int kMax = 5;
+    uint32_t *p[kMax] = {};
+    int64_t n[kMax] = {};
+};
+hipError_t launch_clear(const ClearRuns &r, hipStream_t st);
 // Per-node meta-meshing (counts and node records), FP32 over all nodes or
 // FP64 over the hand-over list.
 // With src_rec set, the meta-mesh of each node is read from its record in
@@ -377,10 +382,16 @@ hipError_t launch_node(const Inputs &in, const Work &w, int k, float kappa_max, 
                        const int64_t *cls_est = nullptr);
 // Node records -> meta-mesh, mesh vertices and hole fans.
 hipError_t launch_expand(const Inputs &in, const Work &w, const FillOut &o, hipStream_t st);
-hipError_t launch_band_count(const Inputs &in, const Work &w, hipStream_t st);
+// Band counts, prefix sums of the node counts and bands (also into `out`),
+// totals; with o, capacity flags.
+struct OffsetsOut {  // caller's copies, each may be null
+    int64_t *node_off, *strut_off;
+    uint8_t *status;
+};
+hipError_t launch_sizes(const Inputs &in, const Work &w, const FillOut *o, const OffsetsOut &out, hipStream_t st);
+hipError_t launch_copy_offsets(const Inputs &in, const Work &w, const OffsetsOut &out, hipStream_t st);
 // bands; k (the resolution) sizes the groups of struts per wave
 hipError_t launch_zip(const Inputs &in, const Work &w, const FillOut &o, int k, hipStream_t st);
-hipError_t launch_totals(const Inputs &in, const Work &w, const FillOut *o, hipStream_t st);
 // Loss terms (area, volume about p0, sum of squared norms) of the last mesh
 // and their gradient dldx [cap_mesh][3]; then the adjoint to the inputs.
 hipError_t launch_loss(const Inputs &in, const Work &w, const FillOut &o, float3 p0, float w_area, float w_vol,
@@ -393,20 +404,22 @@ int64_t sink_slots_words();  // per chunk or per part
 hipError_t launch_parts_reduce(const unsigned long long *slots, int64_t n_parts, uint64_t *out, hipStream_t st);
 hipError_t launch_part_map(int64_t N, const int64_t *part_off, const int32_t *part_k, int64_t n_parts,
                            int32_t *node_part, int16_t *node_k, hipStream_t st);
+// (info, zeroed by the caller: list sizes, then starts)
 hipError_t launch_chunk_list(const Work &w, int64_t n0, int64_t n1, int32_t *mark, int32_t epoch, int32_t *lists,
-                             int64_t cap, int32_t *cnt, int64_t *info, int t16, int t32, hipStream_t st);
+                             int64_t cap, int64_t *info, int t16, int t32, hipStream_t st);
 // The struts a range owns (lower end in [n0, n1), both ends meshed) and their
 // bands, hashed into `so`'s slots; k_max: the largest resolution among the
-// range's nodes (sizes the groups of struts per wave).
+// range's nodes (sizes the groups of struts per wave).  The node pass is over:
+// *fail says whether its records overflowed (the range is run again), flags[0]
+// is cleared for the next range.
 hipError_t launch_sink_bands(const Inputs &in, const Work &w, int64_t n0, int64_t n1, int k_max, int32_t *strut_list,
-                             int32_t *strut_cnt, const SinkOut &so, hipStream_t st);
+                             int32_t *strut_cnt, int32_t *fail, const SinkOut &so, hipStream_t st);
 // chunk slots -> out[kSinkWords]; clears the slots
 hipError_t launch_sink_reduce(unsigned long long *slots, uint64_t *out, hipStream_t st);
-// after range r's node pass: fail[r] = records overflowed; flags cleared
-hipError_t launch_range_done(int32_t *flags, int32_t *fail, int64_t r, hipStream_t st);
 // zero the per-part slots of parts [p0, p1)
 hipError_t launch_clear_parts(unsigned long long *slots, int64_t p0, int64_t p1, hipStream_t st);
 
-int64_t scan_tmp_needed(int64_t n, int ncols);
+// words of Work::scan_tmp, with or without room for the sizes of a stored mesh
+int64_t scan_tmp_needed(int64_t n_nodes, int64_t n_struts, bool sizes);
 
 }  // namespace lm

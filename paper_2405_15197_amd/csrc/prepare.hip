@@ -1,5 +1,5 @@
-// Lattice preparation (validation and node adjacency) and the device-wide
-// exclusive scans used for every offset array.
+// Lattice preparation (validation, node adjacency, valence queues) and the
+// sizes of a mesh (band counts, prefix sums of every count, totals).
 #include "common.h"
 
 namespace lm {
@@ -8,9 +8,10 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kSortReg = 16;  // rows up to this length are sorted in registers
 
-__global__ void k_pack(Inputs in, float4 *node4, int32_t *deg)
+__global__ void k_pack(Inputs in, float4 *node4, int32_t *deg, int32_t *flags)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) flags[1] = 0;  // what is found below
     if (i >= in.n_nodes) return;
     node4[i] = make_float4(in.x[i], in.y[i], in.z[i], in.r[i]);
     deg[i] = 0;
@@ -64,12 +65,6 @@ __global__ void k_degree(Inputs in, int32_t *deg, int32_t *flags)
     const Run ra = wave_run(ka), rb = wave_run(kb);
     if (ka >= 0 && ra.rank == 0) atomicAdd(&deg[ka], ra.len);
     if (kb >= 0 && rb.rank == 0) atomicAdd(&deg[kb], rb.len);
-}
-
-__global__ void k_zero(int32_t *p, int64_t n)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
 }
 
 __global__ void k_scatter(Inputs in, const int64_t *row, int32_t *cursor, int2 *he)
@@ -172,12 +167,24 @@ __global__ void k_sort_rows(int64_t n_nodes, const int64_t *row, int2 *he, int64
 }
 
 // ---------------------------------------------------------------------------
-// Multi-column exclusive scan, int32 -> int64: reduce, scan partials, scan
-// tiles.  Column c of the source starts at src + c*src_stride, of the
-// destination at dst + c*dst_stride; dst[c][n] receives the column total.
+// Prefix sums, int32 -> int64, in tiles of kTile elements: one launch leaves
+// every tile's sum of every column, one writes the prefix sums.  In the second
+// each block sums up the tiles before its own where a wave can (at most kFew
+// tiles, one per lane); above that a launch between the two scans the tiles'
+// sums.  Small lattices are bound by their launches (one costs 2 to 5 us,
+// whatever it does), so whatever is counted over the same elements shares
+// them: BCC 64^3, k = 16: preparation and sizes 23 launches -> 10; cubic 6^3:
+// 21 -> 8, step 152 -> 118 us.
 
 constexpr int kScanItems = 8;
 constexpr int kTile = kBlock * kScanItems;
+constexpr int kFew = 64;
+
+inline __host__ __device__ int64_t tiles_of(int64_t n)
+{
+    const int64_t nb = (n + kTile - 1) / kTile;
+    return nb < 1 ? 1 : nb;
+}
 
 __device__ inline int64_t wave_incl_scan(int64_t x)
 {
@@ -210,96 +217,291 @@ __device__ inline int64_t block_excl_scan(int64_t x, int64_t *total)
     return base + inc - x;
 }
 
-__global__ void __launch_bounds__(kBlock) k_scan_reduce(const int32_t *src, int64_t n, int64_t src_stride, int64_t *part,
-                                                        int64_t nb)
+// sums over the block of up to kBlock / 64 waves' worth of several values;
+// thread 0 gets them
+template <int NV>
+__device__ inline void block_sums(int64_t (&x)[NV])
 {
-    const int32_t *s = src + blockIdx.y * src_stride;
-    int64_t base = (int64_t)blockIdx.x * kTile;
-    int64_t acc = 0;
+    __shared__ int64_t s_x[kBlock / 64][NV];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        int64_t i = base + (int64_t)j * kBlock + threadIdx.x;
-        if (i < n) acc += s[i];
+    for (int v = 0; v < NV; ++v) {
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) x[v] += __shfl_xor(x[v], d, 64);
+        if (lane == 0) s_x[wid][v] = x[v];
     }
-    int64_t tot;
-    block_excl_scan(acc, &tot);
-    if (threadIdx.x == 0) part[blockIdx.y * nb + blockIdx.x] = tot;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            x[v] = 0;
+            for (int w = 0; w < kBlock / 64; ++w) x[v] += s_x[w][v];
+        }
+    }
 }
 
-__global__ void __launch_bounds__(kBlock) k_scan_partials(int64_t *part, int64_t nb, int64_t *dst, int64_t n,
-                                                          int64_t dst_stride)
+// Column sums of nb tiles, p[0 .. nb): their total, and the sum of those
+// before tile b.  At most kFew: summed here by the calling wave; otherwise
+// scanned already, with the total at p[nb].
+__device__ inline int64_t tiles_before(const int64_t *p, int64_t nb, int64_t b, int64_t *total)
 {
-    int64_t *p = part + blockIdx.y * nb;
+    if (nb > kFew) {
+        *total = p[nb];
+        return p[b];
+    }
+    const int lane = threadIdx.x & 63;
+    const int64_t x = lane < nb ? p[lane] : 0, inc = wave_incl_scan(x);
+    *total = __shfl(inc, 63, 64);
+    return __shfl(inc - x, (int)b, 64);
+}
+
+// the tiles' sums of each column scanned in place, the total after them; one
+// block per column, columns `stride` apart
+__global__ void __launch_bounds__(kBlock) k_scan_tile_sums(int64_t *part, int64_t nb, int64_t stride)
+{
+    int64_t *p = part + blockIdx.x * stride;
     int64_t carry = 0;
     for (int64_t b0 = 0; b0 < nb; b0 += kBlock) {
-        int64_t i = b0 + threadIdx.x;
-        int64_t x = i < nb ? p[i] : 0;
+        const int64_t i = b0 + threadIdx.x;
+        const int64_t x = i < nb ? p[i] : 0;
         int64_t tot;
-        int64_t ex = block_excl_scan(x, &tot);
+        const int64_t ex = block_excl_scan(x, &tot);
         if (i < nb) p[i] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0) dst[blockIdx.y * dst_stride + n] = carry;
+    if (threadIdx.x == 0) p[nb] = carry;
 }
 
-__global__ void __launch_bounds__(kBlock) k_scan_tiles(const int32_t *src, int64_t n, int64_t src_stride,
-                                                       const int64_t *part, int64_t nb, int64_t *dst,
-                                                       int64_t dst_stride)
+// Adjacency rows and valence queues: columns degree, then one per class.
+constexpr int kRowCols = 1 + kClasses;
+__global__ void __launch_bounds__(kBlock) k_rows_reduce(int64_t N, const int32_t *deg, int64_t *part, int64_t stride)
 {
-    const int32_t *s = src + blockIdx.y * src_stride;
-    int64_t *d = dst + blockIdx.y * dst_stride;
-    int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kScanItems;
-    int32_t v[kScanItems];
-    int64_t acc = 0;
+    const int64_t base = (int64_t)blockIdx.x * kTile;
+    int64_t x[kRowCols] = {};
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
-        int64_t i = base + j;
-        v[j] = i < n ? s[i] : 0;
-        acc += v[j];
-    }
-    int64_t tot;
-    int64_t ex = block_excl_scan(acc, &tot) + part[blockIdx.y * nb + blockIdx.x];
+        const int64_t n = base + (int64_t)j * kBlock + threadIdx.x;
+        if (n >= N) continue;
+        const int d = deg[n], c = valence_class(d);
+        x[0] += d;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        int64_t i = base + j;
-        if (i < n) d[i] = ex;
-        ex += v[j];
+        for (int k = 0; k < kClasses; ++k) x[1 + k] += k == c;
     }
+    block_sums(x);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < kRowCols; ++c) part[c * stride + blockIdx.x] = x[c];
 }
 
-// Valence buckets: one 0/1 column per class, scanned, then node ids are
-// placed class by class (in node order within a class).
-__global__ void k_class_flags(int64_t N, const int64_t *row, int32_t *flags)
+// row offsets, the queue (nodes class by class, in node order) and the class
+// sizes and starts; deg is cleared for k_scatter
+__global__ void __launch_bounds__(kBlock) k_rows_tiles(int64_t N, int32_t *deg, const int64_t *part, int64_t nb,
+                                                       int64_t stride, int64_t *row, int32_t *queue,
+                                                       int64_t *cls_info)
 {
-    int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    const int c = valence_class(row[n + 1] - row[n]);
-#pragma unroll
-    for (int k = 0; k < kClasses; ++k) flags[k * N + n] = k == c;
-}
-
-__global__ void k_class_scatter(int64_t N, const int64_t *row, const int64_t *off, int32_t *queue,
-                                int64_t *cls_info)
-{
-    int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t Np1 = N + 1;
-    int64_t base[kClasses];
-    int64_t b = 0;
+    static_assert(kClasses * 16 <= 64 && kTile < 65536, "class counts of a tile are 16-bit fields of one word");
+    const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kScanItems;
+    int64_t total, start[kClasses], at = 0;
+    int64_t before = tiles_before(part, nb, blockIdx.x, &total);
+    if (blockIdx.x == 0 && threadIdx.x == 0) row[N] = total;
 #pragma unroll
     for (int k = 0; k < kClasses; ++k) {
-        base[k] = b;
-        b += off[k * Np1 + N];
-    }
-    if (n == 0) {
-#pragma unroll
-        for (int k = 0; k < kClasses; ++k) {
-            cls_info[k] = off[k * Np1 + N];
-            cls_info[4 + k] = base[k];
+        const int64_t b = tiles_before(part + (1 + k) * stride, nb, blockIdx.x, &total);
+        start[k] = at + b;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            cls_info[k] = total;
+            cls_info[kClasses + k] = at;
         }
+        at += total;
     }
-    if (n >= N) return;
-    const int c = valence_class(row[n + 1] - row[n]);
-    queue[base[c] + off[c * Np1 + n]] = (int32_t)n;
+    int32_t d[kScanItems];
+    int64_t acc = 0;
+    uint64_t cls = 0;
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        const int64_t n = base + j;
+        d[j] = n < N ? deg[n] : 0;
+        acc += d[j];
+        if (n < N) cls += 1ull << (16 * valence_class(d[j]));
+    }
+    int64_t tot;
+    int64_t ex = before + block_excl_scan(acc, &tot);
+    uint64_t exc = (uint64_t)block_excl_scan((int64_t)cls, &tot);
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        const int64_t n = base + j;
+        if (n >= N) break;
+        row[n] = ex;
+        deg[n] = 0;
+        ex += d[j];
+        const int c = valence_class(d[j]);
+        int64_t s = start[0];
+#pragma unroll
+        for (int k = 1; k < kClasses; ++k) s = c == k ? start[k] : s;
+        queue[s + (int64_t)((exc >> (16 * c)) & 0xffff)] = (int32_t)n;
+        exc += 1ull << (16 * c);
+    }
+}
+
+// Sizes: the node counts' columns over nodes, the band counts over struts.
+// Tiles of nodes come first in the grid, then tiles of struts.
+struct SizesParams {
+    Inputs in;
+    Work w;
+    FillOut o;
+    int check;          // o's capacities are checked
+    OffsetsOut out;
+    int64_t nbn, nbs;   // tiles of nodes, of struts
+    int64_t stride;     // of the node columns in scan_tmp; the bands' sums follow them
+};
+
+__global__ void __launch_bounds__(kBlock) k_sizes_reduce(SizesParams P)
+{
+    const Work &W = P.w;
+    const int64_t N = P.in.n_nodes, S = P.in.n_struts;
+    const int32_t *status = W.node_cnt + (int64_t)NC_STATUS * N;
+    int64_t x[kNodeScanCols + 1] = {};
+    if (blockIdx.x < P.nbn) {
+        const int64_t base = (int64_t)blockIdx.x * kTile;
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) {
+            const int64_t n = base + (int64_t)j * kBlock + threadIdx.x;
+            if (n >= N) continue;
+#pragma unroll
+            for (int c = 0; c < kNodeScanCols; ++c) x[c] += W.node_cnt[c * N + n];
+            x[kNodeScanCols] += status[n] != 0;
+        }
+        block_sums(x);
+        if (threadIdx.x == 0) {
+            for (int c = 0; c < kNodeScanCols; ++c) W.scan_tmp[c * P.stride + blockIdx.x] = x[c];
+            if (x[kNodeScanCols]) atomicAdd((unsigned long long *)&W.totals[8], (unsigned long long)x[kNodeScanCols]);
+        }
+        return;
+    }
+    const int64_t b = blockIdx.x - P.nbn, base = b * kTile;
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        const int64_t s = base + (int64_t)j * kBlock + threadIdx.x;
+        if (s >= S) continue;
+        const int32_t u = P.in.sa[s], v = P.in.sb[s];
+        int32_t c = 0;
+        if (u != v && (uint64_t)(int64_t)u < (uint64_t)N && (uint64_t)(int64_t)v < (uint64_t)N && status[u] == 0 &&
+            status[v] == 0)
+            c = W.he_len[W.strut_he[2 * s]] + W.he_len[W.strut_he[2 * s + 1]];
+        else
+            ++x[1];
+        x[0] += c;
+        W.band_cnt[s] = c;
+    }
+    block_sums(x);
+    if (threadIdx.x == 0) {
+        W.scan_tmp[kNodeScanCols * P.stride + b] = x[0];
+        if (x[1]) atomicAdd((unsigned long long *)&W.totals[9], (unsigned long long)x[1]);
+    }
+}
+
+// grid y: the node columns, then the bands, then (one block) the totals
+__global__ void __launch_bounds__(kBlock) k_sizes_tiles(SizesParams P)
+{
+    const Work &W = P.w;
+    const int64_t N = P.in.n_nodes, S = P.in.n_struts;
+    const int col = blockIdx.y;
+    const int64_t *part = W.scan_tmp + (int64_t)col * P.stride;
+    if (col <= kNodeScanCols) {
+        const bool nodes = col < kNodeScanCols;
+        const int64_t n = nodes ? N : S, nb = nodes ? P.nbn : P.nbs;
+        if (blockIdx.x >= nb) return;
+        const int32_t *src = nodes ? W.node_cnt + col * N : W.band_cnt;
+        int64_t *dst = nodes ? W.node_off + col * (N + 1) : W.band_off;
+        int64_t *dst2 = nodes ? P.out.node_off : P.out.strut_off;
+        if (nodes && dst2) dst2 += col * (N + 1);
+        const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kScanItems;
+        int64_t total;
+        const int64_t before = tiles_before(part, nb, blockIdx.x, &total);
+        int32_t v[kScanItems];
+        int64_t acc = 0;
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) {
+            v[j] = base + j < n ? src[base + j] : 0;
+            acc += v[j];
+        }
+        int64_t tot;
+        int64_t ex = before + block_excl_scan(acc, &tot);
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) {
+            if (base + j < n) {
+                dst[base + j] = ex;
+                if (dst2) dst2[base + j] = ex;
+            }
+            ex += v[j];
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            dst[n] = total;
+            if (dst2) dst2[n] = total;
+        }
+        if (col == 0 && P.out.status) {
+            // int32 status column -> uint8 (values fit in 8 bits)
+#pragma unroll
+            for (int j = 0; j < kScanItems; ++j) {
+                const int64_t i = (int64_t)blockIdx.x * kTile + (int64_t)j * kBlock + threadIdx.x;
+                if (i < N) P.out.status[i] = (uint8_t)W.node_cnt[(int64_t)NC_STATUS * N + i];
+            }
+        }
+        return;
+    }
+    // totals and capacity checks, by one wave
+    if (blockIdx.x != 0 || threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    int64_t tot[kNodeScanCols + 1];
+#pragma unroll
+    for (int c = 0; c <= kNodeScanCols; ++c)
+        tiles_before(W.scan_tmp + c * P.stride, c < kNodeScanCols ? P.nbn : P.nbs, 0, &tot[c]);
+    // record words: the fullest region times the region count
+    unsigned long long top = 0;
+    for (int g = lane; g < kRecRegions; g += 64) top = W.rec_top[g] > top ? W.rec_top[g] : top;
+    int64_t handed = lane < 2 * kSub ? *sched_ctr(W.sched, SCHED_HAND + lane / kSub, lane % kSub) : 0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const unsigned long long y = __shfl_xor(top, d, 64);
+        top = y > top ? y : top;
+        handed += __shfl_xor(handed, d, 64);
+    }
+    if (lane != 0) return;
+    const int64_t nv = tot[NC_VERT], na = tot[NC_ARC], nm = tot[NC_MESH], nf = tot[NC_FAN], nb = tot[kNodeScanCols];
+    W.totals[0] = nv;
+    W.totals[1] = na;
+    W.totals[2] = tot[NC_HOLE];
+    W.totals[3] = nm;
+    W.totals[4] = nb + nf;
+    W.totals[5] = nb;
+    W.totals[6] = nf;
+    W.totals[7] = (int64_t)top * kRecRegions * 4;
+    W.totals[10] = handed;
+    if (nm > 0x7fffffffLL) atomicOr(W.flags, DF_RECCAP);
+    if (P.check) {
+        const FillOut &o = P.o;
+        bool bad = nm > o.cap_mesh || nb + nf > o.cap_tri;
+        if (o.vert_name && nv > o.cap_vert) bad = true;
+        if (o.arc_f32 && na > o.cap_arc) bad = true;
+        if (bad) atomicOr(W.flags, DF_CAPACITY);
+    }
+}
+
+// offsets and status of the last count, where they were not written with it
+__global__ void __launch_bounds__(kBlock) k_copy_offsets(int64_t N, int64_t S, Work W, OffsetsOut out)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, n5 = kNodeScanCols * (N + 1);
+    if (out.node_off && i < n5) out.node_off[i] = W.node_off[i];
+    if (out.strut_off && i <= S) out.strut_off[i] = W.band_off[i];
+    if (out.status && i < N) out.status[i] = (uint8_t)W.node_cnt[(int64_t)NC_STATUS * N + i];
+}
+
+// up to five runs of 32-bit words cleared in one launch
+__global__ void __launch_bounds__(kBlock) k_clear(ClearRuns r)
+{
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+#pragma unroll
+    for (int j = 0; j < ClearRuns::kMax; ++j)
+        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < r.n[j]; i += stride) r.p[j][i] = 0u;
 }
 
 // Node radius from per-strut end radii (Sec. 4.1: a strut is tangent to the
@@ -359,38 +561,64 @@ hipError_t launch_end_grad(const Inputs &in, const Work &w, const float *grad_r,
     return hipGetLastError();
 }
 
-int64_t scan_tmp_needed(int64_t n, int ncols) { return ((n + kTile - 1) / kTile + 1) * ncols; }
-
-hipError_t launch_scan(const int32_t *src, int64_t *dst, int64_t n, int ncols, int64_t src_stride,
-                       int64_t dst_stride, int64_t *tmp, int64_t tmp_len, hipStream_t st)
+// columns of tile sums, each with room for its total: five over the nodes
+// (adjacency, then sizes), and the bands'
+int64_t scan_tmp_needed(int64_t n_nodes, int64_t n_struts, bool sizes)
 {
-    int64_t nb = (n + kTile - 1) / kTile;
-    if (nb < 1) nb = 1;
-    if (nb * ncols > tmp_len) return hipErrorInvalidValue;
-    dim3 g((unsigned)nb, (unsigned)ncols);
-    k_scan_reduce<<<g, kBlock, 0, st>>>(src, n, src_stride, tmp, nb);
-    k_scan_partials<<<dim3(1, ncols), kBlock, 0, st>>>(tmp, nb, dst, n, dst_stride);
-    k_scan_tiles<<<g, kBlock, 0, st>>>(src, n, src_stride, tmp, nb, dst, dst_stride);
+    static_assert(kRowCols <= kNodeScanCols, "the adjacency's columns fit the sizes'");
+    const int64_t nodes = kNodeScanCols * (tiles_of(n_nodes) + 1), struts = tiles_of(n_struts) + 1;
+    return sizes ? nodes + struts : (nodes > struts ? nodes : struts);
+}
+
+hipError_t launch_clear(const ClearRuns &r, hipStream_t st)
+{
+    int64_t most = 1;
+    for (int j = 0; j < ClearRuns::kMax; ++j) most = r.n[j] > most ? r.n[j] : most;
+    const int64_t blocks = (most + kBlock - 1) / kBlock;
+    k_clear<<<(unsigned)(blocks < 1024 ? blocks : 1024), kBlock, 0, st>>>(r);
+    return hipGetLastError();
+}
+
+hipError_t launch_sizes(const Inputs &in, const Work &w, const FillOut *o, const OffsetsOut &out, hipStream_t st)
+{
+    SizesParams P;
+    P.in = in;
+    P.w = w;
+    P.o = o ? *o : FillOut{};
+    P.check = o ? 1 : 0;
+    P.out = out;
+    P.nbn = tiles_of(in.n_nodes);
+    P.nbs = tiles_of(in.n_struts);
+    P.stride = P.nbn + 1;
+    if (scan_tmp_needed(in.n_nodes, in.n_struts, true) > w.scan_tmp_len) return hipErrorInvalidValue;
+    k_sizes_reduce<<<(unsigned)(P.nbn + P.nbs), kBlock, 0, st>>>(P);
+    if (P.nbn > kFew) k_scan_tile_sums<<<kNodeScanCols, kBlock, 0, st>>>(w.scan_tmp, P.nbn, P.stride);
+    if (P.nbs > kFew)
+        k_scan_tile_sums<<<1, kBlock, 0, st>>>(w.scan_tmp + kNodeScanCols * P.stride, P.nbs, 0);
+    k_sizes_tiles<<<dim3((unsigned)(P.nbn > P.nbs ? P.nbn : P.nbs), kNodeScanCols + 2), kBlock, 0, st>>>(P);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_offsets(const Inputs &in, const Work &w, const OffsetsOut &out, hipStream_t st)
+{
+    if (!out.node_off && !out.strut_off && !out.status) return hipSuccess;
+    const int64_t n5 = kNodeScanCols * (in.n_nodes + 1), n = n5 > in.n_struts + 1 ? n5 : in.n_struts + 1;
+    k_copy_offsets<<<grid_for(n, kBlock), kBlock, 0, st>>>(in.n_nodes, in.n_struts, w, out);
     return hipGetLastError();
 }
 
 hipError_t launch_prepare(const Inputs &in, const Work &w, hipStream_t st)
 {
-    int64_t N = in.n_nodes, S = in.n_struts;
-    if (N > 0) k_pack<<<grid_for(N, kBlock), kBlock, 0, st>>>(in, w.node4, w.deg);
+    const int64_t N = in.n_nodes, S = in.n_struts, nb = tiles_of(N), stride = nb + 1;
+    if (kRowCols * stride > w.scan_tmp_len) return hipErrorInvalidValue;
+    // (at least one block: it clears the flags)
+    k_pack<<<grid_for(N > 0 ? N : 1, kBlock), kBlock, 0, st>>>(in, w.node4, w.deg, w.flags);
     if (S > 0) k_degree<<<grid_for(S, kBlock), kBlock, 0, st>>>(in, w.deg, w.flags);
-    hipError_t e = launch_scan(w.deg, w.row, N, 1, 0, 0, w.scan_tmp, w.scan_tmp_len, st);
-    if (e != hipSuccess) return e;
-    if (N > 0) k_zero<<<grid_for(N, kBlock), kBlock, 0, st>>>(w.deg, N);
+    k_rows_reduce<<<(unsigned)nb, kBlock, 0, st>>>(N, w.deg, w.scan_tmp, stride);
+    if (nb > kFew) k_scan_tile_sums<<<kRowCols, kBlock, 0, st>>>(w.scan_tmp, nb, stride);
+    k_rows_tiles<<<(unsigned)nb, kBlock, 0, st>>>(N, w.deg, w.scan_tmp, nb, stride, w.row, w.queue, w.cls_info);
     if (S > 0) k_scatter<<<grid_for(S, kBlock), kBlock, 0, st>>>(in, w.row, w.deg, w.he);
     if (N > 0) k_sort_rows<<<grid_for(N, kBlock), kBlock, 0, st>>>(N, w.row, w.he, w.strut_he, in.sa, in.sb);
-    // valence buckets (the count columns and offsets are free until the node pass)
-    if (N > 0) {
-        k_class_flags<<<grid_for(N, kBlock), kBlock, 0, st>>>(N, w.row, w.node_cnt);
-        e = launch_scan(w.node_cnt, w.node_off, N, kClasses, N, N + 1, w.scan_tmp, w.scan_tmp_len, st);
-        if (e != hipSuccess) return e;
-        k_class_scatter<<<grid_for(N, kBlock), kBlock, 0, st>>>(N, w.row, w.node_off, w.queue, w.cls_info);
-    }
     return hipGetLastError();
 }
 

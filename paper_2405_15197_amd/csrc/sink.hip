@@ -22,7 +22,8 @@ constexpr int kWords = kSinkWords;
 
 // Wave-aggregated append of `value` to list `k` (when active): one atomic
 // per list and wave.  All lanes of the wave must call it.
-__device__ inline void append(bool active, int k, int32_t value, int32_t *lists, int64_t cap, int32_t *cnt)
+__device__ inline void append(bool active, int k, int32_t value, int32_t *lists, int64_t cap,
+                              unsigned long long *cnt)
 {
     const int lane = threadIdx.x & 63;
     for (int c = 0; c < kClasses; ++c) {
@@ -30,7 +31,7 @@ __device__ inline void append(bool active, int k, int32_t value, int32_t *lists,
         if (m == 0) continue;
         const int leader = __ffsll((long long)m) - 1;
         int base = 0;
-        if (lane == leader) base = atomicAdd(&cnt[c], __popcll(m));
+        if (lane == leader) base = (int)atomicAdd(&cnt[c], (unsigned long long)__popcll(m));
         base = __shfl(base, leader, 64);
         if (active && k == c) lists[c * cap + base + __popcll(m & ((1ull << lane) - 1ull))] = value;
     }
@@ -79,10 +80,12 @@ __device__ inline T block_excl_sum(T x, T &total)
 // halo node is listed once; few nodes, appended per wave).
 __global__ void __launch_bounds__(kListBlock) k_chunk_list(int64_t n0, int64_t n1, const int64_t *row, const int2 *he,
                                                            int32_t *mark, int32_t epoch, int32_t *lists, int64_t cap,
-                                                           int32_t *cnt, int t16, int t32)
+                                                           int64_t *info, int t16, int t32)
 {
     static_assert(kClasses * 16 <= 64 && kListBlock < 65536, "class counts are 16-bit fields of one word");
     __shared__ int32_t s_base[kClasses];
+    unsigned long long *cnt = (unsigned long long *)info;
+    if (blockIdx.x == 0 && threadIdx.x < kClasses) info[kClasses + threadIdx.x] = (int64_t)threadIdx.x * cap;
     const int64_t n = n0 + (int64_t)blockIdx.x * kListBlock + threadIdx.x;
     const bool in = n < n1;
     int64_t r0 = 0, r1 = 0;
@@ -96,7 +99,7 @@ __global__ void __launch_bounds__(kListBlock) k_chunk_list(int64_t n0, int64_t n
     const uint64_t ex = block_excl_sum(one, tot);
     if (threadIdx.x < kClasses) {
         const int c = (int)((tot >> (16 * threadIdx.x)) & 0xffff);
-        s_base[threadIdx.x] = c ? atomicAdd(&cnt[threadIdx.x], c) : 0;
+        s_base[threadIdx.x] = c ? (int)atomicAdd(&cnt[threadIdx.x], (unsigned long long)c) : 0;
     }
     __syncthreads();
     if (in) lists[cls * cap + s_base[cls] + (int64_t)((ex >> (16 * cls)) & 0xffff)] = (int32_t)n;
@@ -118,23 +121,19 @@ __global__ void __launch_bounds__(kListBlock) k_chunk_list(int64_t n0, int64_t n
     }
 }
 
-__global__ void k_chunk_info(const int32_t *cnt, int64_t cap, int64_t *info)
-{
-    if (threadIdx.x < kClasses) {
-        info[threadIdx.x] = cnt[threadIdx.x];
-        info[4 + threadIdx.x] = (int64_t)threadIdx.x * cap;
-    }
-}
-
 // Struts whose lower end is in the range and whose ends both have a mesh:
 // each thread counts its node's, the block reserves its entries with one
 // atomic, and the thread writes them (the first 64 half-edges' verdicts are
 // kept as a mask, later ones tested again).
 __global__ void __launch_bounds__(kListBlock) k_chunk_struts(int64_t n0, int64_t n1, const int64_t *row,
                                                              const int2 *he, const int64_t *node_rec, int32_t *list,
-                                                             int32_t *cnt)
+                                                             int32_t *cnt, int32_t *flags, int32_t *fail)
 {
     __shared__ int32_t s_base;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *fail = flags[0] & DF_RECCAP;
+        flags[0] = 0;
+    }
     const int64_t n = n0 + (int64_t)blockIdx.x * kListBlock + threadIdx.x;
     int64_t r0 = 0, r1 = 0;
     if (n < n1 && node_rec[n] >= 0) {
@@ -310,15 +309,6 @@ __global__ void k_sink_reduce(unsigned long long *slots, uint64_t *out)
     out[w] = s;
 }
 
-// A range's node pass is over: keep whether its records overflowed (the
-// range is run again) and clear the flag for the next range.
-__global__ void k_range_done(int32_t *flags, int32_t *fail, int64_t r)
-{
-    if (threadIdx.x != 0) return;
-    fail[r] = flags[0] & DF_RECCAP;
-    flags[0] = 0;
-}
-
 // zero the per-part slots of parts [p0, p1)
 __global__ void k_clear_parts(unsigned long long *slots, int64_t p0, int64_t p1)
 {
@@ -374,21 +364,20 @@ hipError_t launch_parts_reduce(const unsigned long long *slots, int64_t n_parts,
 }
 
 hipError_t launch_chunk_list(const Work &w, int64_t n0, int64_t n1, int32_t *mark, int32_t epoch, int32_t *lists,
-                             int64_t cap, int32_t *cnt, int64_t *info, int t16, int t32, hipStream_t st)
+                             int64_t cap, int64_t *info, int t16, int t32, hipStream_t st)
 {
     if (n1 > n0)
         k_chunk_list<<<grid_for(n1 - n0, kListBlock), kListBlock, 0, st>>>(n0, n1, w.row, w.he, mark, epoch, lists,
-                                                                           cap, cnt, t16, t32);
-    k_chunk_info<<<1, 64, 0, st>>>(cnt, cap, info);
+                                                                           cap, info, t16, t32);
     return hipGetLastError();
 }
 
 hipError_t launch_sink_bands(const Inputs &in, const Work &w, int64_t n0, int64_t n1, int k_max, int32_t *strut_list,
-                             int32_t *strut_cnt, const SinkOut &so, hipStream_t st)
+                             int32_t *strut_cnt, int32_t *fail, const SinkOut &so, hipStream_t st)
 {
     if (n1 > n0) {
         k_chunk_struts<<<grid_for(n1 - n0, kListBlock), kListBlock, 0, st>>>(n0, n1, w.row, w.he, w.node_rec,
-                                                                             strut_list, strut_cnt);
+                                                                             strut_list, strut_cnt, w.flags, fail);
         // a fixed grid of waves (enough to fill the chip) walks the strut
         // list; no more groups than the lattice has struts
         auto grid = [&](int g) {
@@ -411,12 +400,6 @@ hipError_t launch_sink_bands(const Inputs &in, const Work &w, int64_t n0, int64_
 hipError_t launch_sink_reduce(unsigned long long *slots, uint64_t *out, hipStream_t st)
 {
     k_sink_reduce<<<1, 64, 0, st>>>(slots, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_range_done(int32_t *flags, int32_t *fail, int64_t r, hipStream_t st)
-{
-    k_range_done<<<1, 64, 0, st>>>(flags, fail, r);
     return hipGetLastError();
 }
 

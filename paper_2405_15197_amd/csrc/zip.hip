@@ -1,5 +1,5 @@
 // Strut bands (Sec. 5: a strut is triangulated by connecting the vertices of
-// its two arc loops) and the device-side totals.
+// its two arc loops).
 //
 // Each strut end loop arrives in its node's record as a list of (node-local
 // mesh vertex, phi) in loop order, phi increasing cyclically about the strut
@@ -15,29 +15,6 @@
 
 namespace lm {
 namespace {
-
-constexpr int kBlock = 256;
-
-__global__ void k_band_count(int64_t S, const int32_t *sa, const int32_t *sb, const int64_t *strut_he,
-                             const int32_t *he_len, const int32_t *node_status, int32_t *band_cnt,
-                             int64_t *totals)
-{
-    int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-    int32_t a = sa[s], b = sb[s];
-    int32_t c = 0;
-    if (a != b && node_status[a] == 0 && node_status[b] == 0)
-        c = he_len[strut_he[2 * s]] + he_len[strut_he[2 * s + 1]];
-    else
-        atomicAdd((unsigned long long *)&totals[9], 1ull);
-    band_cnt[s] = c;
-}
-
-__global__ void k_bad_nodes(int64_t N, const int32_t *node_status, int64_t *totals)
-{
-    int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n < N && node_status[n] != 0) atomicAdd((unsigned long long *)&totals[8], 1ull);
-}
 
 // One wave per G consecutive struts.  Lanes load the struts' loop
 // descriptors, the loops are staged in LDS in sorted (phi) order when they
@@ -202,53 +179,7 @@ __global__ void __launch_bounds__(64) k_zip(int64_t S, const int64_t *band_off, 
     }
 }
 
-// Totals (device) and capacity checks for the fill pass.
-__global__ void k_totals(int64_t N, int64_t S, const int64_t *node_off, const unsigned long long *rec_top,
-                         int32_t *sched, const int64_t *band_off, FillOut o, int check, int64_t *totals,
-                         int32_t *flags)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int64_t Np1 = N + 1;
-    int64_t nv = node_off[0 * Np1 + N], na = node_off[1 * Np1 + N], nh = node_off[2 * Np1 + N];
-    int64_t nm = node_off[3 * Np1 + N], nf = node_off[4 * Np1 + N];
-    int64_t nb = band_off[S];
-    unsigned long long top = 0;  // record words: the fullest region times the region count
-    for (int g = 0; g < kRecRegions; ++g) top = rec_top[g] > top ? rec_top[g] : top;
-    const int64_t nl = (int64_t)top * kRecRegions * 4;
-    totals[0] = nv;
-    totals[1] = na;
-    totals[2] = nh;
-    totals[3] = nm;
-    totals[4] = nb + nf;
-    totals[5] = nb;
-    totals[6] = nf;
-    totals[7] = nl;
-    int64_t handed = 0;
-    for (int c = 0; c < 2 * kSub; ++c) handed += *sched_ctr(sched, SCHED_HAND + c / kSub, c % kSub);
-    totals[10] = handed;
-    if (nm > 0x7fffffffLL) atomicOr(flags, DF_RECCAP);
-    if (check) {
-        bool bad = nm > o.cap_mesh || nb + nf > o.cap_tri;
-        if (o.vert_name && nv > o.cap_vert) bad = true;
-        if (o.arc_f32 && na > o.cap_arc) bad = true;
-        if (bad) atomicOr(flags, DF_CAPACITY);
-    }
-}
-
-inline unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
-
 }  // namespace
-
-hipError_t launch_band_count(const Inputs &in, const Work &w, hipStream_t st)
-{
-    const int64_t N = in.n_nodes, S = in.n_struts;
-    const int32_t *status = w.node_cnt + (int64_t)NC_STATUS * N;
-    if (N > 0) k_bad_nodes<<<grid_for(N), kBlock, 0, st>>>(N, status, w.totals);
-    if (S > 0)
-        k_band_count<<<grid_for(S), kBlock, 0, st>>>(S, in.sa, in.sb, w.strut_he, w.he_len, status, w.band_cnt,
-                                                     w.totals);
-    return hipGetLastError();
-}
 
 hipError_t launch_zip(const Inputs &in, const Work &w, const FillOut &o, int k, hipStream_t st)
 {
@@ -267,14 +198,6 @@ hipError_t launch_zip(const Inputs &in, const Work &w, const FillOut &o, int k, 
     else if (k <= 32) go(std::integral_constant<int, 6>{});
     else if (k <= 56) go(std::integral_constant<int, 4>{});
     else go(std::integral_constant<int, 2>{});
-    return hipGetLastError();
-}
-
-hipError_t launch_totals(const Inputs &in, const Work &w, const FillOut *o, hipStream_t st)
-{
-    FillOut oo = o ? *o : FillOut{};
-    k_totals<<<1, 64, 0, st>>>(in.n_nodes, in.n_struts, w.node_off, w.rec_top, w.sched, w.band_off, oo, o ? 1 : 0,
-                               w.totals, w.flags);
     return hipGetLastError();
 }
 
