@@ -11,6 +11,13 @@
 // Phases timed with HIP events when profiling is on (lm_set_profiling).
 enum Phase { PH_PREPARE, PH_NODE32, PH_NODE64, PH_SIZES, PH_EXPAND, PH_ZIP, PH_LOSS, PH_BACKWARD, PH_N };
 
+// A piece of device memory the library allocated.
+struct DevMem {
+    void *p = nullptr;
+    size_t n = 0;   // its size (at least what was asked for)
+    int dev = -1;
+};
+
 struct lm_plan {
     lm::Inputs in;
     lm::Work w;
@@ -19,9 +26,10 @@ struct lm_plan {
     // first use of a part) or all carved from the caller's workspace
     bool caller_ws = false;
     int32_t ws_flags = 0;       // LM_WS_* parts carved (caller workspace)
-    void *ws = nullptr;         // fixed workspace (library-owned plans)
+    DevMem ws;                  // fixed workspace (library-owned plans)
+    DevMem rec_mem, alt_rec_mem;  // node records: w.rec, alt_rec
     // sink mode (LM_WS_SINK)
-    void *sink_mem = nullptr;
+    DevMem sink_mem;
     int32_t *sk_mark = nullptr;     // [N] epoch of the last range listing the node
     int32_t *sk_lists = nullptr;    // [kClasses][N + 1] range node lists
     int32_t *sk_cnt = nullptr;      // [8] the range's strut count
@@ -31,7 +39,7 @@ struct lm_plan {
     unsigned long long *sk_slots = nullptr;  // chunk-mode slots
     int32_t sk_epoch = 0;
     // batched parts (with the sink part)
-    void *batch_mem = nullptr, *batch_parts_mem = nullptr;
+    DevMem batch_mem, batch_parts_mem;
     int16_t *bt_node_k = nullptr;   // [N + 1] resolution of each node
     int32_t *bt_node_part = nullptr;// [N + 1] part of each node
     int64_t *bt_part_base = nullptr;// [cap + 1] first node of each part
@@ -48,13 +56,13 @@ struct lm_plan {
     // the allocation behind the second node record index and counters (the
     // pointers above swap with the workspace's own at every switch), and the
     // redo lists [N] and their counters [8]
-    void *alt_index_mem = nullptr;
+    DevMem alt_index_mem;
     int32_t *redo = nullptr;
     int32_t *redo_cnt = nullptr;
     unsigned long long *codec_ctr = nullptr;  // fallback counter of lm_arc_encode
-    void *grad_mem = nullptr;                 // adjoint scratch (library-owned)
+    DevMem grad_mem;                          // adjoint scratch (library-owned)
     int schedule = LM_SCHEDULE_WAVE;          // FP32 node pass of lm_count / lm_forward
-    void *thread_scratch = nullptr;           // per-node scratch of the thread-centric pass
+    DevMem thread_scratch;                    // per-node scratch of the thread-centric pass
     int64_t cls_est[4];        // nodes per valence class when the plan was made (grid sizes only)
     bool has_cls_est = false;
     int k;          // resolution of the last count (0: none)
@@ -108,6 +116,119 @@ struct PhaseTimer {
         if (e_ != hipSuccess) return LM_ERR_HIP;    \
     } while (0)
 
+// Device memory of finished plans, kept for the next ones: hipMalloc and
+// hipFree map and unmap memory and wait for the device (a new plan for BCC 21^3,
+// sized, meshed and given back, spent most of its 0.8 ms in four of them, and
+// now and then twice that).  A piece enters when its owner's stream has been
+// waited for, so whoever takes it may use it at once on any stream; it goes
+// back to the system when the pieces together would exceed kKeepBytes or
+// kKeepPieces, when kKeepCalls further ones were asked for or returned, or when
+// an allocation fails.  One lock for all threads; never throws.
+constexpr size_t kKeepBytes = (size_t)256 << 20;
+constexpr int kKeepPieces = 16;
+constexpr uint64_t kKeepCalls = 64;
+struct MemKeep {
+    std::mutex mu;
+    DevMem piece[kKeepPieces];
+    uint64_t since[kKeepPieces];
+    int count = 0;
+    uint64_t calls = 0;
+    size_t bytes = 0;
+
+    DevMem drop(int i)
+    {
+        const DevMem m = piece[i];
+        bytes -= m.n;
+        --count;
+        piece[i] = piece[count];
+        since[i] = since[count];
+        return m;
+    }
+    int oldest() const
+    {
+        int o = 0;
+        for (int i = 1; i < count; ++i)
+            if (since[i] < since[o]) o = i;
+        return o;
+    }
+    // pieces that have to go, into out; keep: bytes that may stay
+    int expire(DevMem *out, size_t keep, int keep_count)
+    {
+        int n = 0;
+        while (count > 0) {
+            const int o = oldest();
+            if (bytes <= keep && count <= keep_count && calls - since[o] < kKeepCalls) break;
+            out[n++] = drop(o);
+        }
+        return n;
+    }
+};
+MemKeep g_keep;
+
+void mem_release(const DevMem *m, int n)
+{
+    for (int i = 0; i < n; ++i) (void)hipFree(m[i].p);
+}
+
+bool mem_alloc(DevMem *m, size_t n)
+{
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    if (n == 0) n = 1;
+    DevMem old[kKeepPieces];
+    int drop = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_keep.mu);
+        ++g_keep.calls;
+        int best = -1;
+        for (int i = 0; i < g_keep.count; ++i) {
+            const DevMem &k = g_keep.piece[i];
+            if (k.dev == dev && k.n >= n && k.n <= 2 * n && (best < 0 || k.n < g_keep.piece[best].n)) best = i;
+        }
+        if (best >= 0) *m = g_keep.drop(best);
+        else m->p = nullptr;
+        drop = g_keep.expire(old, kKeepBytes, kKeepPieces);
+    }
+    mem_release(old, drop);
+    if (m->p) return true;
+    if (hipMalloc(&m->p, n) != hipSuccess) {
+        (void)hipGetLastError();
+        {
+            std::lock_guard<std::mutex> lock(g_keep.mu);
+            drop = g_keep.expire(old, 0, 0);
+        }
+        mem_release(old, drop);
+        m->p = nullptr;
+        if (drop == 0 || hipMalloc(&m->p, n) != hipSuccess) {
+            m->p = nullptr;
+            return false;
+        }
+    }
+    m->n = n;
+    m->dev = dev;
+    return true;
+}
+
+// idle: the stream that used the memory has been waited for
+void mem_free(DevMem *m, bool idle)
+{
+    if (!m->p) return;
+    DevMem old[kKeepPieces + 1];
+    int drop = 0;
+    if (!idle || m->n > kKeepBytes / 2) {
+        old[drop++] = *m;
+    } else {
+        std::lock_guard<std::mutex> lock(g_keep.mu);
+        ++g_keep.calls;
+        drop = g_keep.expire(old, kKeepBytes - m->n, kKeepPieces - 1);
+        g_keep.piece[g_keep.count] = *m;
+        g_keep.since[g_keep.count++] = g_keep.calls;
+        g_keep.bytes += m->n;
+    }
+    mem_release(old, drop);
+    *m = DevMem{};
+}
+
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Hands out 256-byte aligned pieces of one buffer; with base == nullptr it
@@ -124,6 +245,9 @@ struct Carver {
         return (T *)p;
     }
 };
+
+// int64 words of the piece that holds totals, flags and class sizes
+constexpr int kFlagsAt = 16, kClassAt = 18, kHostWords = 26;
 
 // The fixed workspace: adjacency, counts, offsets, queues, flags.  Without
 // `sizes`, for sink mode only.
@@ -146,13 +270,15 @@ void carve_fixed(lm_plan *P, Carver &c, int64_t N, int64_t S, bool sizes = true)
     const int64_t tl = lm::scan_tmp_needed(N, S, sizes);
     w.scan_tmp = c.take<int64_t>(tl);
     w.scan_tmp_len = tl;
-    w.flags = c.take<int32_t>(4);
-    w.totals = c.take<int64_t>(16);
+    // totals, flags and class sizes side by side: each pair that the host
+    // reads is one copy
+    w.totals = c.take<int64_t>(kHostWords);
+    w.flags = (int32_t *)(w.totals + kFlagsAt);
+    w.cls_info = w.totals + kClassAt;
     w.fb_list = c.take<int32_t>(N + 1);
     w.node_rec = c.take<int64_t>(N + 1);
     w.rec_top = c.take<unsigned long long>(lm::kRecRegions);
     w.queue = c.take<int32_t>(N + 1);
-    w.cls_info = c.take<int64_t>(8);
     P->codec_ctr = c.take<unsigned long long>(1);
     w.node_k = nullptr;
 }
@@ -277,8 +403,9 @@ int run_count(lm_plan *P, int k, const lm::FillOut *out, const lm::OffsetsOut &o
     {
         PhaseTimer t(P, PH_NODE32);
         if (P->schedule == LM_SCHEDULE_THREAD && !src_rec) {
-            if (!P->thread_scratch) HIPCHK(hipMalloc(&P->thread_scratch, lm::node_thread_scratch_bytes()));
-            HIPCHK(lm::launch_node_thread(P->in, w, k, P->kappa_max, P->thread_scratch, P->st));
+            if (!P->thread_scratch.p && !mem_alloc(&P->thread_scratch, lm::node_thread_scratch_bytes()))
+                return LM_ERR_HIP;
+            HIPCHK(lm::launch_node_thread(P->in, w, k, P->kappa_max, P->thread_scratch.p, P->st));
         } else {
             HIPCHK(lm::launch_node(P->in, w, k, P->kappa_max, 0, P->st, src_rec, src_node_rec, redo, redo_cnt,
                                    nullptr, P->has_cls_est ? P->cls_est : nullptr));
@@ -295,11 +422,11 @@ int run_count(lm_plan *P, int k, const lm::FillOut *out, const lm::OffsetsOut &o
 
 int read_totals(lm_plan *P, lm_totals *t, int32_t *flags_out)
 {
-    int64_t tv[16];
-    int32_t fl[4];
+    int64_t tv[kFlagsAt + 1];
+    int32_t fl[2];
     HIPCHK(hipMemcpyAsync(tv, P->w.totals, sizeof(tv), hipMemcpyDeviceToHost, P->st));
-    HIPCHK(hipMemcpyAsync(fl, P->w.flags, sizeof(fl), hipMemcpyDeviceToHost, P->st));
     HIPCHK(hipStreamSynchronize(P->st));
+    memcpy(fl, tv + kFlagsAt, sizeof(fl));
     t->n_vertices = tv[0];
     t->n_arcs = tv[1];
     t->n_holes = tv[2];
@@ -325,10 +452,11 @@ int ensure_rec(lm_plan *P, int64_t words)
     if (words <= P->w.rec_words) return LM_OK;
     if (P->caller_ws) return LM_ERR_CAPACITY;
     HIPCHK(hipStreamSynchronize(P->st));
-    if (P->w.rec) HIPCHK(hipFree(P->w.rec));
+    mem_free(&P->rec_mem, true);
     P->w.rec = nullptr;
     P->w.rec_words = 0;
-    HIPCHK(hipMalloc((void **)&P->w.rec, sizeof(uint32_t) * words));
+    if (!mem_alloc(&P->rec_mem, sizeof(uint32_t) * (size_t)words)) return LM_ERR_HIP;
+    P->w.rec = (uint32_t *)P->rec_mem.p;
     P->w.rec_words = words;
     return LM_OK;
 }
@@ -389,12 +517,11 @@ lm_plan *new_plan(const lm_lattice *lat, void *stream)
 // flag of range 0).
 int first_prepare(lm_plan *P, bool sink = false)
 {
-    int32_t fl = 0;
+    int64_t tv[kHostWords - kFlagsAt];
+    int32_t fl[2];
     lm::ClearRuns c;
-    c.p[0] = (uint32_t *)P->w.flags;
-    c.n[0] = 4;
-    c.p[1] = (uint32_t *)P->w.totals;
-    c.n[1] = 2 * 16;
+    c.p[0] = (uint32_t *)P->w.totals;
+    c.n[0] = 2 * kClassAt;  // and the flags
     if (sink) {
         c.p[2] = (uint32_t *)P->sk_mark;
         c.n[2] = P->in.n_nodes + 1;
@@ -405,11 +532,12 @@ int first_prepare(lm_plan *P, bool sink = false)
     }
     if (lm::launch_clear(c, P->st) != hipSuccess ||
         lm::launch_prepare(P->in, P->w, P->st) != hipSuccess ||
-        hipMemcpyAsync(&fl, P->w.flags + 1, sizeof(int32_t), hipMemcpyDeviceToHost, P->st) != hipSuccess ||
-        hipMemcpyAsync(P->cls_est, P->w.cls_info, sizeof(P->cls_est), hipMemcpyDeviceToHost, P->st) != hipSuccess ||
+        hipMemcpyAsync(tv, P->w.totals + kFlagsAt, sizeof(tv), hipMemcpyDeviceToHost, P->st) != hipSuccess ||
         hipStreamSynchronize(P->st) != hipSuccess)
         return LM_ERR_HIP;
-    if (fl & lm::DF_BADLAT) return LM_ERR_BAD_LATTICE;  // set in flags[1]
+    memcpy(fl, tv, sizeof(fl));
+    memcpy(P->cls_est, tv + (kClassAt - kFlagsAt), sizeof(P->cls_est));
+    if (fl[1] & lm::DF_BADLAT) return LM_ERR_BAD_LATTICE;
     P->has_cls_est = true;
     return LM_OK;
 }
@@ -420,7 +548,7 @@ size_t ws_layout(lm_plan *P, void *base, int64_t N, int64_t S, const lm_options 
 {
     Carver c(base);
     carve_fixed(P, c, N, S, !fixed_array);
-    if (fixed_array) (void)c.take<int32_t>(8);  // the array's published sizes: its counters are beside it
+    if (fixed_array) (void)c.take<char>(3 * 256);  // up to the array's published sizes
     else carve_sched(P, c);
     if (o.flags & LM_WS_GRADIENT) carve_grad(P, c, N, S);
     if (o.flags & LM_WS_SINK) {
@@ -514,15 +642,15 @@ int lm_plan_create(lm_plan **plan, const lm_lattice *lat, void *stream)
     Carver c0(nullptr);
     carve_fixed(P, c0, lat->n_nodes, lat->n_struts);
     carve_sched(P, c0);
-    if (hipMalloc(&P->ws, c0.off) != hipSuccess) {
+    if (!mem_alloc(&P->ws, c0.off)) {
         delete P;
         return LM_ERR_HIP;
     }
-    Carver c(P->ws);
+    Carver c(P->ws.p);
     carve_fixed(P, c, lat->n_nodes, lat->n_struts);
     carve_sched(P, c);
     if ((rc = first_prepare(P))) {
-        (void)hipFree(P->ws);
+        mem_free(&P->ws, rc != LM_ERR_HIP);
         delete P;
         return rc;
     }
@@ -638,8 +766,8 @@ int grad_alloc(lm_plan *P)
     if (P->caller_ws) return LM_ERR_UNSUPPORTED;
     Carver c0(nullptr);
     carve_grad(P, c0, P->in.n_nodes, P->in.n_struts);
-    HIPCHK(hipMalloc(&P->grad_mem, c0.off));
-    Carver c(P->grad_mem);
+    if (!mem_alloc(&P->grad_mem, c0.off)) return LM_ERR_HIP;
+    Carver c(P->grad_mem.p);
     carve_grad(P, c, P->in.n_nodes, P->in.n_struts);
     return LM_OK;
 }
@@ -691,8 +819,8 @@ int sink_alloc(lm_plan *P)
     const int64_t N = P->in.n_nodes, S = P->in.n_struts;
     Carver c0(nullptr);
     carve_sink(P, c0, N, S);
-    HIPCHK(hipMalloc(&P->sink_mem, c0.off));
-    Carver c(P->sink_mem);
+    if (!mem_alloc(&P->sink_mem, c0.off)) return LM_ERR_HIP;
+    Carver c(P->sink_mem.p);
     carve_sink(P, c, N, S);
     HIPCHK(hipMemsetAsync(P->sk_mark, 0, sizeof(int32_t) * (N + 1), P->st));
     HIPCHK(hipMemsetAsync(P->sk_slots, 0, sizeof(unsigned long long) * lm::sink_slots_words(), P->st));
@@ -704,22 +832,21 @@ int sink_alloc(lm_plan *P)
 int batch_alloc(lm_plan *P, int64_t n_parts)
 {
     if (P->caller_ws) return n_parts <= P->bt_cap ? LM_OK : LM_ERR_CAPACITY;
-    if (!P->batch_mem) {
+    if (!P->batch_mem.p) {
         Carver c0(nullptr);
         carve_batch_nodes(P, c0, P->in.n_nodes);
-        HIPCHK(hipMalloc(&P->batch_mem, c0.off));
-        Carver c(P->batch_mem);
+        if (!mem_alloc(&P->batch_mem, c0.off)) return LM_ERR_HIP;
+        Carver c(P->batch_mem.p);
         carve_batch_nodes(P, c, P->in.n_nodes);
     }
     if (n_parts > P->bt_cap) {
         HIPCHK(hipStreamSynchronize(P->st));
-        if (P->batch_parts_mem) HIPCHK(hipFree(P->batch_parts_mem));
-        P->batch_parts_mem = nullptr;
+        mem_free(&P->batch_parts_mem, true);
         P->bt_cap = 0;
         Carver c0(nullptr);
         carve_batch_parts(P, c0, n_parts);
-        HIPCHK(hipMalloc(&P->batch_parts_mem, c0.off));
-        Carver c(P->batch_parts_mem);
+        if (!mem_alloc(&P->batch_parts_mem, c0.off)) return LM_ERR_HIP;
+        Carver c(P->batch_parts_mem.p);
         carve_batch_parts(P, c, n_parts);
     }
     return LM_OK;
@@ -937,8 +1064,8 @@ int lm_retriangulate(lm_plan *P, int k, const lm_outputs *out)
     if (!P->alt_node_rec) {
         Carver c0(nullptr);
         carve_retri_index(P, c0, N);
-        HIPCHK(hipMalloc(&P->alt_index_mem, c0.off));
-        Carver c(P->alt_index_mem);
+        if (!mem_alloc(&P->alt_index_mem, c0.off)) return LM_ERR_HIP;
+        Carver c(P->alt_index_mem.p);
         carve_retri_index(P, c, N);
     }
     // the slot that does not hold the meta-mesh receives the new records
@@ -960,9 +1087,11 @@ int lm_retriangulate(lm_plan *P, int k, const lm_outputs *out)
     if (base_in_w) {
         if (need > P->alt_rec_words && !P->caller_ws) {
             HIPCHK(hipStreamSynchronize(P->st));
-            if (P->alt_rec) HIPCHK(hipFree(P->alt_rec));
+            mem_free(&P->alt_rec_mem, true);
             P->alt_rec = nullptr;
-            HIPCHK(hipMalloc((void **)&P->alt_rec, sizeof(uint32_t) * need));
+            P->alt_rec_words = 0;
+            if (!mem_alloc(&P->alt_rec_mem, sizeof(uint32_t) * (size_t)need)) return LM_ERR_HIP;
+            P->alt_rec = (uint32_t *)P->alt_rec_mem.p;
             P->alt_rec_words = need;
         }
         wd.rec = P->alt_rec;
@@ -981,6 +1110,7 @@ int lm_retriangulate(lm_plan *P, int k, const lm_outputs *out)
     if (rc) return rc;
     if (base_in_w) {  // the new records become current; the meta-mesh moves to the other slot
         std::swap(P->w.rec, P->alt_rec);
+        std::swap(P->rec_mem, P->alt_rec_mem);
         std::swap(P->w.rec_words, P->alt_rec_words);
         std::swap(P->w.node_rec, P->alt_node_rec);
         std::swap(P->w.rec_top, P->alt_rec_top);
@@ -1096,18 +1226,16 @@ int lm_set_precision(lm_plan *P, float kappa_max)
 void lm_plan_destroy(lm_plan *P)
 {
     if (!P) return;
-    (void)hipStreamSynchronize(P->st);
+    const bool idle = hipStreamSynchronize(P->st) == hipSuccess;
     for (auto &e : P->ev) {
         (void)hipEventDestroy(e.second.first);
         (void)hipEventDestroy(e.second.second);
     }
     for (auto e : P->pool) (void)hipEventDestroy(e);
-    if (!P->caller_ws) {
-        for (void *p : {(void *)P->w.rec, P->ws, P->sink_mem, P->batch_mem, P->batch_parts_mem, (void *)P->alt_rec,
-                        P->alt_index_mem, P->grad_mem})
-            if (p) (void)hipFree(p);
-    }
-    if (P->thread_scratch) (void)hipFree(P->thread_scratch);
+    // (all empty in a plan on a caller-owned workspace)
+    for (DevMem *m : {&P->ws, &P->rec_mem, &P->alt_rec_mem, &P->sink_mem, &P->batch_mem, &P->batch_parts_mem,
+                      &P->alt_index_mem, &P->grad_mem, &P->thread_scratch})
+        mem_free(m, idle);
     delete P;
 }
 

@@ -174,7 +174,7 @@ __global__ void k_sort_rows(int64_t n_nodes, const int64_t *row, int2 *he, int64
 // sums.  Small lattices are bound by their launches (one costs 2 to 5 us,
 // whatever it does), so whatever is counted over the same elements shares
 // them: BCC 64^3, k = 16: preparation and sizes 23 launches -> 10; cubic 6^3:
-// 21 -> 8, step 152 -> 118 us.
+// 21 -> 8, step 152 -> 114 us.
 
 constexpr int kScanItems = 8;
 constexpr int kTile = kBlock * kScanItems;
