@@ -83,9 +83,23 @@ __device__ inline void add3(float *p, float3 v, float s)
 // own mesh vertices, gathered over the triangles that touch them (its hole
 // fans and the bands of its incident struts) in LDS and written once; the
 // loss terms count each band at its lower end node and each fan at its
-// node.  Nodes with more mesh vertices than the LDS holds add through
-// global atomics instead.
-constexpr int kLossLds = 1024;
+// node.
+//
+// A band lists the triangles of the edges of one end loop, then those of the
+// other, each in loop order; an edge triangle's apex is on the other loop.
+// So the wave adds without LDS atomics, in three steps of distinct addresses:
+// the edges of the node's own loop add their first ends, then their second
+// ends, and the other loop's edges, whose apexes on this one come in runs of
+// neighbouring lanes, add each run's sum.  (With an atomic per corner and
+// coordinate the kernel was bound by them, some 60 cycles of the compute
+// unit's LDS per instruction.)  The bands' bookkeeping is read for all struts
+// at once, a lane per strut.  Octet 32^3, k = 16: 1.45 -> 0.70 ms.
+//
+// kLossLds vertices at a time; a node with more of them takes up to
+// kLossPasses passes over its triangles, beyond that it adds through global
+// atomics.
+constexpr int kLossLds = 512;
+constexpr int kLossPasses = 4;
 
 struct LParams {
     Inputs in;
@@ -99,10 +113,29 @@ struct LParams {
     double *terms;
 };
 
+// The mesh of the last pass must be complete and fit the buffers given here
+// (tri, xyz and dldx): otherwise nothing is read, and zeros are written.
+__device__ inline bool mesh_fits(const LParams &P)
+{
+    const Work &W = P.w;
+    const int64_t N = P.in.n_nodes, Np1 = N + 1;
+    const int64_t m_all = W.node_off[(int64_t)NC_MESH * Np1 + N];
+    const int64_t t_all = W.band_off[P.in.n_struts] + W.node_off[(int64_t)NC_FAN * Np1 + N];
+    return !(W.flags[0] & (DF_CAPACITY | DF_RECCAP)) && m_all <= P.cap_mesh && t_all <= P.cap_tri;
+}
+
+// dldx beyond the mesh's vertices (which their nodes write), or all of it
+__global__ void k_loss_rest(LParams P)
+{
+    const int64_t end = 3 * P.cap_mesh, Np1 = P.in.n_nodes + 1;
+    const int64_t i0 = mesh_fits(P) ? 3 * P.w.node_off[(int64_t)NC_MESH * Np1 + P.in.n_nodes] : 0;
+    for (int64_t i = i0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < end; i += (int64_t)gridDim.x * blockDim.x)
+        P.dldx[i] = 0.f;
+}
+
 __global__ void __launch_bounds__(64) k_loss_node(LParams P)
 {
-    __shared__ float g[kLossLds][3];
-    __shared__ double s_terms[3];
+    __shared__ float gx[kLossLds], gy[kLossLds], gz[kLossLds];
     const Work &W = P.w;
     const int64_t N = P.in.n_nodes, S = P.in.n_struts;
     const int64_t n = blockIdx.x;
@@ -110,43 +143,49 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
     if (n >= N) return;
     const int64_t Np1 = N + 1;
     double *nt = W.loss_node + 3 * n;  // this node's share of the loss terms
-    // the mesh of the last pass must be complete and fit the buffers given
-    // here (tri, xyz and dldx): otherwise nothing is read or written
-    const int64_t m_all = W.node_off[(int64_t)NC_MESH * Np1 + N];
-    const int64_t t_all = W.band_off[S] + W.node_off[(int64_t)NC_FAN * Np1 + N];
-    if ((W.flags[0] & (DF_CAPACITY | DF_RECCAP)) || m_all > P.cap_mesh || t_all > P.cap_tri) {
+    const int64_t r0 = W.row[n], r1 = W.row[n + 1];
+    const int64_t m0 = W.node_off[(int64_t)NC_MESH * Np1 + n], m1 = W.node_off[(int64_t)NC_MESH * Np1 + n + 1];
+    const int64_t f0 = W.band_off[S] + W.node_off[(int64_t)NC_FAN * Np1 + n];
+    const int64_t f1 = W.band_off[S] + W.node_off[(int64_t)NC_FAN * Np1 + n + 1];
+    if (!mesh_fits(P)) {
         if (lane == 0) {
             atomicOr(&W.flags[0], DF_CAPACITY);
             nt[0] = nt[1] = nt[2] = 0.0;
         }
         return;
     }
-    const int64_t m0 = W.node_off[(int64_t)NC_MESH * Np1 + n], m1 = W.node_off[(int64_t)NC_MESH * Np1 + n + 1];
     const int M = (int)(m1 - m0);
     if (M == 0) {
         if (lane == 0) nt[0] = nt[1] = nt[2] = 0.0;
         return;
     }
-    const bool lds = M <= kLossLds;
-    for (int i = lane; i < (lds ? M : 0); i += 64) g[i][0] = g[i][1] = g[i][2] = 0.f;
-    if (lane < 3) s_terms[lane] = 0.0;
-    __syncthreads();
+    // strut `lane`: its band, the samples of the own loop, which end this is
+    const int v = (int)(r1 - r0);  // at most kVmaxBig = 64: the node has a mesh
+    int64_t my_b0 = 0;
+    int my_nb = 0, my_own = 0, my_lower = 0;
+    if (lane < v) {
+        const int2 he = W.he[r0 + lane];
+        my_own = W.he_len[r0 + lane];
+        my_lower = (int64_t)he.x > n;
+        my_b0 = W.band_off[he.y];
+        my_nb = (int)(W.band_off[he.y + 1] - my_b0);
+    }
     double area = 0.0, vol = 0.0, sq = 0.0;
-    auto add = [&](int32_t vi, float3 d, float sc) {
-        if (vi < m0 || vi >= m1) return;
-        if (lds) {
-            atomicAdd(&g[vi - m0][0], d.x * sc);
-            atomicAdd(&g[vi - m0][1], d.y * sc);
-            atomicAdd(&g[vi - m0][2], d.z * sc);
-        } else {
-            add3(P.dldx + 3 * (int64_t)vi, d, sc);
-        }
+    const bool lds = M <= kLossLds * kLossPasses;
+    int c0 = 0;  // vertices [c0, c0 + kLossLds) of the node are in LDS
+    // a triangle's corners and the gradient on each; its terms when counted
+    struct Tri {
+        int32_t i0, i1, i2;
+        float3 g0, g1, g2;
     };
-    // one triangle: gradient on this node's corners; terms when counted here
+    const bool grad = P.w_area != 0.f || P.w_vol != 0.f;
     auto tri_do = [&](int64_t t, bool count) {
-        const int32_t i0 = P.tri[3 * t], i1 = P.tri[3 * t + 1], i2 = P.tri[3 * t + 2];
-        const float3 a = sub3(f3(P.xyz + 3 * (int64_t)i0), P.p0), b = sub3(f3(P.xyz + 3 * (int64_t)i1), P.p0),
-                     c = sub3(f3(P.xyz + 3 * (int64_t)i2), P.p0);
+        Tri T;
+        T.i0 = P.tri[3 * t];
+        T.i1 = P.tri[3 * t + 1];
+        T.i2 = P.tri[3 * t + 2];
+        const float3 a = sub3(f3(P.xyz + 3 * (int64_t)T.i0), P.p0), b = sub3(f3(P.xyz + 3 * (int64_t)T.i1), P.p0),
+                     c = sub3(f3(P.xyz + 3 * (int64_t)T.i2), P.p0);
         const float3 Nn = crs3(sub3(b, a), sub3(c, a));
         const float nl = sqrtf(Nn.x * Nn.x + Nn.y * Nn.y + Nn.z * Nn.z);
         const float3 bc = crs3(b, c), ca = crs3(c, a), ab = crs3(a, b);
@@ -154,57 +193,136 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
             area += 0.5 * (double)nl;
             vol += ((double)a.x * bc.x + (double)a.y * bc.y + (double)a.z * bc.z) / 6.0;
         }
-        // both terms' gradients summed per corner first: one add per corner
-        // (same-address LDS atomics of neighbouring lanes serialise)
         const float wa = (P.w_area != 0.f && nl > 0.f) ? 0.5f * P.w_area / nl : 0.f, wv = P.w_vol / 6.f;
         auto corner = [&](float3 e, float3 vterm) {
             const float3 ga = crs3(Nn, e);
             return make_float3(wa * ga.x + wv * vterm.x, wa * ga.y + wv * vterm.y, wa * ga.z + wv * vterm.z);
         };
-        if (P.w_area != 0.f || P.w_vol != 0.f) {
-            add(i0, corner(sub3(c, b), bc), 1.f);
-            add(i1, corner(sub3(a, c), ca), 1.f);
-            add(i2, corner(sub3(b, a), ab), 1.f);
+        T.g0 = corner(sub3(c, b), bc);
+        T.g1 = corner(sub3(a, c), ca);
+        T.g2 = corner(sub3(b, a), ab);
+        return T;
+    };
+    // place of a vertex in LDS, -1: not the node's, or of another pass
+    auto place = [&](int32_t vi) {
+        const int64_t i = vi - m0;
+        return vi >= m0 && vi < m1 && i >= c0 && i < c0 + kLossLds ? (int)i - c0 : -1;
+    };
+    // adds of one step go to distinct places
+    auto add = [&](int i, float3 d) {
+        gx[i] += d.x;
+        gy[i] += d.y;
+        gz[i] += d.z;
+    };
+    auto add_any = [&](int32_t vi, float3 d) {
+        if (vi < m0 || vi >= m1) return;
+        if (!lds) {
+            add3(P.dldx + 3 * (int64_t)vi, d, 1.f);
+        } else if (const int i = place(vi); i >= 0) {
+            atomicAdd(&gx[i], d.x);
+            atomicAdd(&gy[i], d.y);
+            atomicAdd(&gz[i], d.z);
         }
     };
-    // hole fans of the node
-    const int64_t f0 = W.band_off[S] + W.node_off[(int64_t)NC_FAN * Np1 + n];
-    const int64_t f1 = W.band_off[S] + W.node_off[(int64_t)NC_FAN * Np1 + n + 1];
-    for (int64_t t = f0 + lane; t < f1; t += 64) tri_do(t, true);
-    // bands of the incident struts (terms at the lower end)
-    const int64_t r0 = W.row[n], r1 = W.row[n + 1];
-    for (int64_t h = r0; h < r1; ++h) {
-        const int2 he = W.he[h];
-        const int64_t b0 = W.band_off[he.y], b1 = W.band_off[he.y + 1];
-        const bool lower = (int64_t)he.x > n;
-        // even triangles on the first lanes, odd ones after: neighbouring
-        // lanes then share fewer corners
-        const int64_t nb = b1 - b0, half = (nb + 1) / 2;
-        for (int64_t l = lane; l < nb; l += 64) tri_do(b0 + (l < half ? 2 * l : 2 * (l - half) + 1), lower);
+    if (!lds) {
+        for (int64_t i = 3 * m0 + lane; i < 3 * m1; i += 64) P.dldx[i] = 0.f;
+        __threadfence();
     }
-    // sum of squared norms over the node's vertices
-    for (int i = lane; i < M; i += 64) {
-        const float3 x = f3(P.xyz + 3 * (m0 + i));
-        sq += (double)x.x * x.x + (double)x.y * x.y + (double)x.z * x.z;
+    for (c0 = 0; c0 < M; c0 += lds ? kLossLds : M) {
+        const bool first = c0 == 0;
+        const int mc = M - c0 < kLossLds ? M - c0 : kLossLds;
+        if (lds)
+            for (int i = lane; i < mc; i += 64) gx[i] = gy[i] = gz[i] = 0.f;
+        __syncthreads();
+        // hole fans of the node
+        for (int64_t t = f0 + lane; t < f1; t += 64) {
+            const Tri T = tri_do(t, first);
+            if (grad) {
+                add_any(T.i0, T.g0);
+                add_any(T.i1, T.g1);
+                add_any(T.i2, T.g2);
+            }
+        }
+        // bands of the incident struts (terms at the lower end)
+        for (int h = 0; h < v; ++h) {
+            const int64_t b0 = ((int64_t)__builtin_amdgcn_readlane((int)(my_b0 >> 32), h) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)my_b0, h);
+            const int nb = __builtin_amdgcn_readlane(my_nb, h), own = __builtin_amdgcn_readlane(my_own, h);
+            const bool lower = __builtin_amdgcn_readlane(my_lower, h) != 0;
+            for (int base = 0; base < nb; base += 64) {
+                const int l = base + lane;
+                const bool act = l < nb;
+                // the lower end's edges come first, run u, u'; then the
+                // upper end's, u', u
+                const bool edge = act && (lower ? l < own : l >= nb - own);
+                Tri T;
+                T.i0 = T.i1 = T.i2 = -1;
+                T.g0 = T.g1 = T.g2 = make_float3(0.f, 0.f, 0.f);
+                if (act) T = tri_do(b0 + l, lower && first);
+                if (!grad) continue;
+                if (!lds) {
+                    if (act) {
+                        add_any(T.i0, T.g0);
+                        add_any(T.i1, T.g1);
+                        add_any(T.i2, T.g2);
+                    }
+                    continue;
+                }
+                const int p0 = edge ? place(lower ? T.i0 : T.i1) : -1, p1 = edge ? place(lower ? T.i1 : T.i0) : -1;
+                if (p0 >= 0) add(p0, lower ? T.g0 : T.g1);
+                __syncthreads();
+                if (p1 >= 0) add(p1, lower ? T.g1 : T.g0);
+                __syncthreads();
+                // runs of equal apexes among the other loop's edges
+                const bool other = act && !edge;
+                const int pa = other ? place(T.i2) : -1;
+                const int pp = __shfl_up(pa, 1, 64);
+                const bool head = lane == 0 || pa != pp;
+                const unsigned long long hm = __ballot(head);
+                const int lead = 63 - __clzll(hm & ((2ull << lane) - 1)), rank = lane - lead;
+                float3 x = T.g2;
+                for (int d = 1; __ballot(pa >= 0 && rank >= d) != 0; d <<= 1) {
+                    const float3 y = make_float3(__shfl_up(x.x, d, 64), __shfl_up(x.y, d, 64), __shfl_up(x.z, d, 64));
+                    if (rank >= d) {
+                        x.x += y.x;
+                        x.y += y.y;
+                        x.z += y.z;
+                    }
+                }
+                // the run's last lane has its sum; the loop closes, so the
+                // first run and the last one may be of one vertex
+                const bool tail = pa >= 0 && (lane == 63 || ((hm >> lane) >> 1 & 1));
+                const unsigned long long om = __ballot(pa >= 0);
+                const int lead0 = om ? __builtin_ctzll(om) : 0;
+                if (tail && lead != lead0) add(pa, x);
+                __syncthreads();
+                if (tail && lead == lead0) add(pa, x);
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+        // sum of squared norms over the node's vertices
+        const int done = lds ? mc : M;
+        for (int i = lane; i < done; i += 64) {
+            const float3 x = f3(P.xyz + 3 * (m0 + c0 + i));
+            sq += (double)x.x * x.x + (double)x.y * x.y + (double)x.z * x.z;
+            float *d = P.dldx + 3 * (m0 + c0 + i);
+            if (lds) {
+                d[0] = gx[i] + 2.f * P.w_sq * x.x;
+                d[1] = gy[i] + 2.f * P.w_sq * x.y;
+                d[2] = gz[i] + 2.f * P.w_sq * x.z;
+            } else {
+                atomicAdd(d, 2.f * P.w_sq * x.x);
+                atomicAdd(d + 1, 2.f * P.w_sq * x.y);
+                atomicAdd(d + 2, 2.f * P.w_sq * x.z);
+            }
+        }
+        __syncthreads();
     }
     for (int o = 32; o > 0; o >>= 1) {
         area += __shfl_xor(area, o, 64);
         vol += __shfl_xor(vol, o, 64);
         sq += __shfl_xor(sq, o, 64);
-    }
-    __syncthreads();
-    for (int i = lane; i < M; i += 64) {
-        const float3 x = f3(P.xyz + 3 * (m0 + i));
-        float *d = P.dldx + 3 * (m0 + i);
-        if (lds) {
-            d[0] = g[i][0] + 2.f * P.w_sq * x.x;
-            d[1] = g[i][1] + 2.f * P.w_sq * x.y;
-            d[2] = g[i][2] + 2.f * P.w_sq * x.z;
-        } else {
-            atomicAdd(d, 2.f * P.w_sq * x.x);
-            atomicAdd(d + 1, 2.f * P.w_sq * x.y);
-            atomicAdd(d + 2, 2.f * P.w_sq * x.z);
-        }
     }
     if (lane == 0) {  // the node's terms; summed in a fixed order by k_loss_reduce
         nt[0] = area;
@@ -261,12 +379,6 @@ __global__ void __launch_bounds__(256) k_loss_reduce(const double *partial, doub
         c += partial[3 * i + 2];
     }
     block_tree3(a, b, c, terms);
-}
-
-__global__ void k_zero_f(float *p, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.f;
 }
 
 __global__ void k_zero_d(double *p, int n)
@@ -901,8 +1013,6 @@ hipError_t launch_loss(const Inputs &in, const Work &w, const FillOut &o, float3
         k_zero_d<<<1, 64, 0, st>>>(terms, 3);
         return hipGetLastError();
     }
-    // nodes whose vertices do not fit the LDS add with atomics: start from 0
-    if (o.cap_mesh > 0) k_zero_f<<<grid_for(3 * o.cap_mesh), kBlock, 0, st>>>(dldx, 3 * o.cap_mesh);
     LParams P;
     P.in = in;
     P.w = w;
@@ -916,6 +1026,11 @@ hipError_t launch_loss(const Inputs &in, const Work &w, const FillOut &o, float3
     P.w_sq = w_sq;
     P.dldx = dldx;
     P.terms = terms;
+    // (before the nodes: they set the flag that it reads)
+    if (o.cap_mesh > 0) {
+        const unsigned g = grid_for(3 * o.cap_mesh);
+        k_loss_rest<<<g < 2048 ? g : 2048, kBlock, 0, st>>>(P);
+    }
     k_loss_node<<<(unsigned)in.n_nodes, 64, 0, st>>>(P);
     double *partial = w.loss_node + 3 * (in.n_nodes + 1);  // kLossParts x 3 after the node terms
     k_loss_partial<<<kLossParts, kBlock, 0, st>>>(in.n_nodes, w.loss_node, partial);
