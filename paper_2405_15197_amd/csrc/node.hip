@@ -2076,6 +2076,7 @@ __device__ inline int drain_class(const Params &P, int cls, Shared<float, C> *sh
     constexpr int NPW = C::W <= 64 ? 64 / C::W : 1;
     const int slot = C::W <= 64 ? threadIdx.x / C::W : 0;
     const int64_t cnt = MODE == kModeRedo ? (int64_t)P.redo_cnt[cls] : P.w.cls_info[cls];
+    if (cnt == 0) return 0;  // most launches for the rarer classes: as short as can be
     const int64_t base = P.w.cls_info[4 + cls];
     const int32_t *list = MODE == kModeRedo ? P.redo : P.w.queue;
     const int64_t items = (cnt + NPW - 1) / NPW;
@@ -2164,6 +2165,7 @@ __global__ void __launch_bounds__(C::W) __attribute__((amdgpu_waves_per_eu(2))) 
     constexpr int cls = C::VM <= kVmax ? 0 : (C::VM <= kVmaxMid ? 1 : 2);
     const int64_t N = P.in.n_nodes;
     const List q{sched_ctr(P.w.sched, SCHED_FP64 + cls, 0), sched_ctr(P.w.sched, SCHED_HAND + (cls ? 1 : 0), 0), 0, 0};
+    if (__ballot(sub_len(q, threadIdx.x & 63) != 0) == 0) return;
     drain(q, blockIdx.x, s_grab, [&](int c, int i) {
         const int64_t at = cls ? hand_base(N, c + 1) - 1 - i : hand_base(N, c) + i;
         // an entry the two-wave kernel could not hold is stored negated
