@@ -15,45 +15,10 @@
 //           differentiated implicitly;
 //   strut table  g_m, h_m, e_m from the two node centres and radii.
 //
-// Conics and strut-table entries are differentiated in forward mode with
-// dual numbers (one input direction at a time), everything else in reverse.
+// Everything is taken in reverse.
 #include "geom.h"
 
 namespace lm {
-namespace geo {
-
-// Dual number: value and derivative along one input direction.
-struct Dual {
-    float v, d;
-    __device__ Dual() : v(0.f), d(0.f) {}
-    __device__ Dual(double x) : v((float)x), d(0.f) {}
-    __device__ Dual(float x) : v(x), d(0.f) {}
-    __device__ Dual(int x) : v((float)x), d(0.f) {}
-    __device__ Dual(float x, float dx) : v(x), d(dx) {}
-};
-__device__ inline Dual operator+(Dual a, Dual b) { return Dual(a.v + b.v, a.d + b.d); }
-__device__ inline Dual operator-(Dual a, Dual b) { return Dual(a.v - b.v, a.d - b.d); }
-__device__ inline Dual operator-(Dual a) { return Dual(-a.v, -a.d); }
-__device__ inline Dual operator*(Dual a, Dual b) { return Dual(a.v * b.v, a.d * b.v + a.v * b.d); }
-__device__ inline Dual operator/(Dual a, Dual b)
-{
-    const float q = a.v / b.v;
-    return Dual(q, (a.d - q * b.d) / b.v);
-}
-__device__ inline bool operator<(Dual a, Dual b) { return a.v < b.v; }
-__device__ inline bool operator>(Dual a, Dual b) { return a.v > b.v; }
-__device__ inline bool operator<=(Dual a, Dual b) { return a.v <= b.v; }
-__device__ inline bool operator>=(Dual a, Dual b) { return a.v >= b.v; }
-__device__ inline Dual m_sqrt(Dual a)
-{
-    const float r = sqrtf(a.v);
-    return Dual(r, r > 0.f ? 0.5f * a.d / r : 0.f);
-}
-__device__ inline Dual m_abs(Dual a) { return a.v < 0.f ? -a : a; }
-__device__ inline Dual m_max(Dual a, Dual b) { return a.v >= b.v ? a : b; }
-
-}  // namespace geo
-
 namespace {
 
 using namespace geo;
@@ -402,21 +367,35 @@ struct BParams {
 template <int VM, int AC, int VC>
 struct BwdLds {
     SL<float> S[VM + 1];
-    float lam_v[VC][3];
-    float lam_arc[AC][11];  // o, a, b, t1, t2
-    float lam_g[VM + 1][3], lam_h[VM + 1], lam_e[VM + 1][3];
-    // circle adjoints per strut: sigma, kappa, frame q, frame r
-    float lam_sig[VM + 1], lam_kap[VM + 1], lam_qf[VM + 1][3], lam_rf[VM + 1][3];
-    float lam_node[4];      // this node's x, y, z, radius
-    float own[VM][4];       // strut-table terms of this node's inputs, per strut
-    int s_mbase[AC];
+    uint4 v[VC];            // name, x, y, z
+    float vert[VC][9];      // adjoint parts left by the vertex's three arc ends; then
+                            // the weights of its three labels, x, y, z, -1
+    float arc[AC][9];       // circular arcs: part of their contour's barycentre, number of
+                            // segments; then circles: adjoint of o, a, b; ellipses: of
+                            // g_p, h_p, g_q, h_q
+    float hole[AC][4];      // per contour: barycentre sum, segments; then mu
+    float gh[VM][4];        // per strut: adjoint of g, h
+    float conic[VM][9];     // per strut: sums of its circles' o, a, b
+    uint32_t ent[2 * AC];   // loop entries: arc | start vertex << 8 | its label's place << 16 | kEnt*
+    int base[VM + 1];       // first loop entry of each strut, and their number
 };
+constexpr uint32_t kEntCircle = 1u << 20, kEntSideQ = 1u << 21, kEntVertex = 1u << 22;
 
-// the 4 inputs (x, y, z, radius) of node `node` as dual seeds: direction k
-__device__ inline void seed(const float4 c4, int k, V3<Dual> &c, Dual &r)
+template <int CTRL, int ROWS = 0xf>
+__device__ inline float dpp_add(float x)
 {
-    c = v3(Dual(c4.x, k == 0 ? 1.f : 0.f), Dual(c4.y, k == 1 ? 1.f : 0.f), Dual(c4.z, k == 2 ? 1.f : 0.f));
-    r = Dual(c4.w, k == 3 ? 1.f : 0.f);
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, true));
+}
+// sum of x over the wave, in every lane (row_shr 1, 2, 4, 8, row_bcast 15, 31)
+__device__ inline float wave_sum(float x)
+{
+    x = dpp_add<0x111>(x);
+    x = dpp_add<0x112>(x);
+    x = dpp_add<0x114>(x);
+    x = dpp_add<0x118>(x);
+    x = dpp_add<0x142, 0xa>(x);
+    x = dpp_add<0x143, 0xc>(x);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
 __device__ inline float dotf(const float *a, const float *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
@@ -432,21 +411,21 @@ __device__ inline void crs(const float *a, const float *b, float *c)
 // belongs to the far node's inputs to grad_he at the strut's half-edge here;
 // k_grad_gather adds them up per node in a fixed order (no atomics between
 // nodes, so the gradient's bits do not depend on scheduling).
+//
+// Lanes go over arcs, contours, vertices, (strut, input) pairs and struts in
+// turn, and what one of them adds to another is stored at a place of its own
+// and gathered: the forward pass leaves every vertex with the ends of three
+// arcs, one for each pair of its labels, and every strut's end loop with all
+// arcs and vertices that carry its label.  (Adding through LDS atomics, some
+// 50 instructions of 60 cycles of the compute unit's LDS each, the kernel
+// kept that unit busy for 82 % of its time.)  The strut table is taken in
+// reverse too, a lane per strut.  Octet 32^3, k = 16: 654 -> 401 us.
 template <int VM, int AC, int VC>
 __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const int64_t n)
 {
+    static_assert(VM <= 64 && AC <= 256 && VC <= 256, "a lane per strut; entries hold 8-bit arcs and vertices");
+    constexpr int NA = (AC + 63) / 64, NV = (VC + 63) / 64;
     auto &S = sm.S;
-    auto &lam_v = sm.lam_v;
-    auto &lam_arc = sm.lam_arc;
-    auto &lam_g = sm.lam_g;
-    auto &lam_h = sm.lam_h;
-    auto &lam_e = sm.lam_e;
-    auto &lam_sig = sm.lam_sig;
-    auto &lam_kap = sm.lam_kap;
-    auto &lam_qf = sm.lam_qf;
-    auto &lam_rf = sm.lam_rf;
-    auto &lam_node = sm.lam_node;
-    auto &s_mbase = sm.s_mbase;
     const Work &W = P.w;
     const int64_t N = P.in.n_nodes;
     const int lane = threadIdx.x;
@@ -457,345 +436,296 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
     if (rb < 0) return;
     const uint32_t *R = W.rec + rb;
     const int V = (int)R[0], E = (int)R[1], NC = (int)R[2], ncirc = (int)R[3];
-    const int wsum = (int)R[4];
+    const int wsum = (int)R[4], M = (int)R[5];
+    const int nent = (int)((R[7] >> 8) & 0xffffu);
+    const bool wide = (R[7] & kRecWide) != 0;
     const uint32_t *RV = R + kRecHead;
     const uint32_t *RA = RV + 4 * V;
     const uint32_t *RH = RA + kRecArcFields * E;
+    const uint32_t *RT = R + rec_table_word(V, E, NC + wsum - V);
     const int64_t row = W.row[n];
     const int v = (int)(W.row[n + 1] - row);
     const int64_t moff = W.node_off[(int64_t)NC_MESH * (N + 1) + n];
     const float4 c4 = W.node4[n];
     const float rho = c4.w;
-    const V3<float> cen = v3(c4.x, c4.y, c4.z);
     const float *L = P.dldx + 3 * moff;
-    auto af = [&](int f, int j) { return __uint_as_float(RA[kRecArcFields * j + f]); };
-    auto vpos = [&](int i, float *w) {
-        w[0] = __uint_as_float(RV[4 * i + 1]);
-        w[1] = __uint_as_float(RV[4 * i + 2]);
-        w[2] = __uint_as_float(RV[4 * i + 3]);
-    };
+    // adjoint of this node's x, y, z and radius: this lane's share
+    float own[4] = {0.f, 0.f, 0.f, 0.f};
 
-    // ---- strut table, cleared adjoints ------------------------------------
+    // ---- strut table, vertices, arcs ---------------------------------------
     if (lane < v) {
         const int2 he = W.he[row + lane];
         const float4 f4 = W.node4[he.x];
         bool bad;
-        SL<float> s = strut_entry(cen, rho, v3(f4.x, f4.y, f4.z), f4.w, (int)((int64_t)he.x > n), bad);
+        SL<float> s = strut_entry(v3(c4.x, c4.y, c4.z), rho, v3(f4.x, f4.y, f4.z), f4.w, (int)((int64_t)he.x > n), bad);
         s.far = he.x;
         S[lane + 1] = s;
     }
-    for (int i = lane; i <= VM; i += 64) {
-        lam_g[i][0] = lam_g[i][1] = lam_g[i][2] = 0.f;
-        lam_h[i] = 0.f;
-        lam_e[i][0] = lam_e[i][1] = lam_e[i][2] = 0.f;
-        lam_sig[i] = lam_kap[i] = 0.f;
-        lam_qf[i][0] = lam_qf[i][1] = lam_qf[i][2] = 0.f;
-        lam_rf[i][0] = lam_rf[i][1] = lam_rf[i][2] = 0.f;
-    }
-    if (lane < 4) lam_node[lane] = 0.f;
-    for (int j = lane; j < E; j += 64) {
-        s_mbase[j] = (int)RA[kRecArcFields * j + 14];
+    for (int i = lane; i < V; i += 64) sm.v[i] = *(const uint4 *)(RV + 4 * i);
+    auto tab = [&](int i) { return wide ? (int)((const uint16_t *)RT)[i] : (int)((const uint8_t *)RT)[i]; };
+    for (int i = lane; i <= v; i += 64) sm.base[i] = tab(i);
+    float o[NA][3], a[NA][3], b[NA][3], t1[NA], dt[NA];
+    uint32_t w11[NA], w12[NA], w13[NA];
+    int mb[NA];
 #pragma unroll
-        for (int f = 0; f < 11; ++f) lam_arc[j][f] = 0.f;
+    for (int t = 0; t < NA; ++t) {
+        const int j = lane + 64 * t;
+        w11[t] = w12[t] = 0;
+        w13[t] = 0xffff0001u;  // one segment, no contour
+        mb[t] = 0;
+        t1[t] = dt[t] = 0.f;
+        for (int d = 0; d < 3; ++d) o[t][d] = a[t][d] = b[t][d] = 0.f;
+        if (j >= E) continue;
+        const uint4 *q = (const uint4 *)(RA + kRecArcFields * j);
+        const uint4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+        auto f = [](uint32_t x) { return __uint_as_float(x); };
+        o[t][0] = f(q0.x); o[t][1] = f(q0.y); o[t][2] = f(q0.z);
+        a[t][0] = f(q0.w); a[t][1] = f(q1.x); a[t][2] = f(q1.y);
+        b[t][0] = f(q1.z); b[t][1] = f(q1.w); b[t][2] = f(q2.x);
+        t1[t] = f(q2.y); dt[t] = f(q2.z);
+        w11[t] = q2.w; w12[t] = q3.x; w13[t] = q3.y;
+        mb[t] = (int)q3.z;
     }
-    for (int i = lane; i < V; i += 64) {
-        lam_v[i][0] = L[3 * i];
-        lam_v[i][1] = L[3 * i + 1];
-        lam_v[i][2] = L[3 * i + 2];
-    }
+    // absolute positions are c + w: every mesh vertex of the node moves with c
+#pragma unroll 4
+    for (int i = lane; i < M; i += 64)
+        for (int d = 0; d < 3; ++d) own[d] += L[3 * i + d];
     __syncthreads();
 
-    // absolute positions are c + w: every mesh vertex of the node moves with c
-    {
-        const int M = (int)R[5];
-        float sx = 0.f, sy = 0.f, sz = 0.f;
-#pragma unroll 4
-        for (int i = lane; i < M; i += 64) {
-            sx += L[3 * i];
-            sy += L[3 * i + 1];
-            sz += L[3 * i + 2];
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            sx += __shfl_xor(sx, o, 64);
-            sy += __shfl_xor(sy, o, 64);
-            sz += __shfl_xor(sz, o, 64);
-        }
-        if (lane == 0) {
-            lam_node[0] += sx;
-            lam_node[1] += sy;
-            lam_node[2] += sz;
-        }
+    // what the gather over the end loops reads of each entry
+    for (int e = lane; e < nent; e += 64) {
+        const uint32_t ea = (uint32_t)tab(v + 1 + e);
+        const int j = (int)(ea & (wide ? 0x7fffu : 0x7fu));
+        const bool along = (ea & (wide ? 0x8000u : 0x80u)) != 0;
+        const uint32_t pq = RA[kRecArcFields * j + 11], ends = RA[kRecArcFields * j + 12];
+        int m = 1;
+        while (sm.base[m] <= e) ++m;  // entries of strut m: base[m - 1] .. base[m] - 1
+        const uint32_t vi = along ? ends & 0xffffu : ends >> 16, name = sm.v[vi].x;
+        const uint32_t place = (name >> 24) == (uint32_t)m ? 0u : (((name >> 16) & 0xffu) == (uint32_t)m ? 1u : 2u);
+        sm.ent[e] = (uint32_t)j | (vi << 8) | (place << 16) | (j < ncirc ? kEntCircle : 0u) |
+                    (((pq >> 8) & 0xffu) == (uint32_t)m ? kEntSideQ : 0u) | (((pq >> 16) & 1u) ? 0u : kEntVertex);
     }
 
-    // Eq. 12 point ii of arc j and its derivative along t
-    auto arc_point = [&](int j, float t, float *x, float *dx) {
-        float s, c;
-        sincos_f32(t, &s, &c);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            x[d] = af(d, j) + af(3 + d, j) * s + af(6 + d, j) * c;
-            dx[d] = af(3 + d, j) * c - af(6 + d, j) * s;
-        }
-    };
-    // adds weight lam (a 3-vector) on interior point ii of arc j
-    auto add_interior = [&](int j, int ii, const float *lam) {
-        const int nseg = (int)(RA[kRecArcFields * j + 13] & 0xffffu);
-        const float t1 = af(9, j), t2 = t1 + af(10, j);  // the record keeps dt = t2 - t1
-        const float f = (float)ii / (float)nseg;
-        const float t = t1 + (t2 - t1) * (float)ii / (float)nseg;
-        float s, c;
-        sincos_f32(t, &s, &c);
-        float g = 0.f;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            atomicAdd(&lam_arc[j][d], lam[d]);
-            atomicAdd(&lam_arc[j][3 + d], lam[d] * s);
-            atomicAdd(&lam_arc[j][6 + d], lam[d] * c);
-            g += lam[d] * (af(3 + d, j) * c - af(6 + d, j) * s);
-        }
-        atomicAdd(&lam_arc[j][9], (1.f - f) * g);
-        atomicAdd(&lam_arc[j][10], f * g);
-    };
-
     // ---- interior points ----------------------------------------------------
-    // lane j alone writes arc j's adjoint here: sums in registers, one store
-    for (int j = lane; j < E; j += 64) {
-        const int nseg = (int)(RA[kRecArcFields * j + 13] & 0xffffu);
-        const bool fwd = (RA[kRecArcFields * j + 11] >> 17) & 1u;
-        const float t1 = af(9, j), t2 = t1 + af(10, j);  // the record keeps dt = t2 - t1
-        float ca[3], cb[3];
+    // x_i = o + a sin t_i + b cos t_i, t_i = t1 + f dt, f = i / nseg.  For the
+    // circular arcs also what the contour's mu will add: it is the same at
+    // all of their points.
+    float acc[NA][9], lt1[NA], lt2[NA], sn1[NA], cs1[NA], snf[NA], csf[NA];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            ca[d] = af(3 + d, j);
-            cb[d] = af(6 + d, j);
-        }
-        float acc[11];
-#pragma unroll
-        for (int f = 0; f < 11; ++f) acc[f] = 0.f;
-        const int mb = s_mbase[j];
-#pragma unroll 2
-        for (int ii = 1; ii < nseg; ++ii) {
-            const int li = mb + (fwd ? ii - 1 : nseg - 1 - ii);
-            const float lam[3] = {L[3 * li], L[3 * li + 1], L[3 * li + 2]};
+    for (int t = 0; t < NA; ++t) {
+        const int j = lane + 64 * t;
+        for (int f = 0; f < 9; ++f) acc[t][f] = 0.f;
+        lt1[t] = lt2[t] = sn1[t] = cs1[t] = snf[t] = csf[t] = 0.f;
+        if (j >= E) continue;
+        const int nseg = (int)(w13[t] & 0xffffu);
+        const bool fwd = (w11[t] >> 17) & 1u;
+        const float *Li = L + 3 * (mb[t] + (fwd ? 0 : nseg - 2));
+        const int step = fwd ? 3 : -3;
+        for (int ii = 1; ii < nseg; ++ii, Li += step) {
+            const float lam[3] = {Li[0], Li[1], Li[2]};
             const float f = (float)ii / (float)nseg;
-            const float t = t1 + (t2 - t1) * (float)ii / (float)nseg;
             float sn, cs;
-            sincos_f32(t, &sn, &cs);
+            sincos_f32(t1[t] + dt[t] * f, &sn, &cs);
             float g = 0.f;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                acc[d] += lam[d];
-                acc[3 + d] += lam[d] * sn;
-                acc[6 + d] += lam[d] * cs;
-                g += lam[d] * (ca[d] * cs - cb[d] * sn);
+                acc[t][d] += lam[d];
+                acc[t][3 + d] += lam[d] * sn;
+                acc[t][6 + d] += lam[d] * cs;
+                g += lam[d] * (a[t][d] * cs - b[t][d] * sn);
             }
-            acc[9] += (1.f - f) * g;
-            acc[10] += f * g;
+            lt1[t] += (1.f - f) * g;
+            lt2[t] += f * g;
+            sn1[t] += sn;
+            cs1[t] += cs;
+            snf[t] += f * sn;
+            csf[t] += f * cs;
         }
-#pragma unroll
-        for (int f = 0; f < 11; ++f) lam_arc[j][f] = acc[f];
+        if (j < ncirc) {
+            const uint4 vs = sm.v[w12[t] & 0xffffu], ve = sm.v[w12[t] >> 16];
+            const float es[3] = {__uint_as_float(vs.y), __uint_as_float(vs.z), __uint_as_float(vs.w)};
+            const float ee[3] = {__uint_as_float(ve.y), __uint_as_float(ve.z), __uint_as_float(ve.w)};
+            for (int d = 0; d < 3; ++d)
+                sm.arc[j][d] = 0.5f * (es[d] + ee[d]) + ((float)(nseg - 1) * o[t][d] + a[t][d] * sn1[t] + b[t][d] * cs1[t]);
+            sm.arc[j][3] = (float)nseg;
+        }
     }
     __syncthreads();
 
     // ---- hole centres (Eq. 13) ----------------------------------------------
-    for (int c = lane; c < NC; c += 64) {
-        const int li = wsum + c;
-        const float lh[3] = {L[3 * li], L[3 * li + 1], L[3 * li + 2]};
-        // barycentre as in the forward pass
-        float b[3] = {0.f, 0.f, 0.f};
-        int cnt = 0;
-        for (int j = 0; j < ncirc; ++j) {
-            if ((int)(RA[kRecArcFields * j + 13] >> 16) != c) continue;
-            const int vs = (int)(RA[kRecArcFields * j + 12] & 0xffffu), ve = (int)(RA[kRecArcFields * j + 12] >> 16);
-            float ws[3], we[3];
-            vpos(vs, ws);
-            vpos(ve, we);
-            const int nseg = (int)(RA[kRecArcFields * j + 13] & 0xffffu);
-            for (int d = 0; d < 3; ++d) b[d] += 0.5f * (ws[d] + we[d]);
-            for (int ii = 1; ii < nseg; ++ii) {
-                float x[3], dx[3];
-                arc_point(j, af(9, j) + af(10, j) * (float)ii / (float)nseg, x, dx);
-                for (int d = 0; d < 3; ++d) b[d] += x[d];
+    // sums over the arcs of each contour: four lanes per contour
+    for (int c0 = 0; c0 < NC; c0 += 16) {
+        const int ci = lane >> 2, d = lane & 3, nc = NC - c0 < 16 ? NC - c0 : 16;
+        float sum = 0.f;
+#pragma unroll
+        for (int t = 0; t < NA; ++t) {
+            const int rel = (int)(w13[t] >> 16) - c0;  // 0xffff: no contour
+            unsigned long long mine = 0;
+            for (int i = 0; i < nc; ++i) {
+                const unsigned long long m = __ballot(rel == i);
+                if (ci == i) mine = m;
             }
-            cnt += nseg;
+            while (mine) {
+                sum += sm.arc[64 * t + __ffsll(mine) - 1][d];
+                mine &= mine - 1;
+            }
         }
-        for (int d = 0; d < 3; ++d) b[d] /= (float)cnt;
-        const float bl = sqrtf(dotf(b, b));
-        float dir[3];
-        float se[3] = {0.f, 0.f, 0.f}, sl = 1.f;
-        const bool use_b = bl >= 1e-3f * rho;
-        if (use_b) {
-            for (int d = 0; d < 3; ++d) dir[d] = b[d] / bl;
-        } else {
+        if (ci < nc) sm.hole[c0 + ci][d] = sum;
+    }
+    __syncthreads();
+    float lse[3] = {0.f, 0.f, 0.f};  // adjoint of the sum of the struts' e
+    bool any_se = false;
+    for (int c = lane; c < NC; c += 64) {
+        const float *lp = L + 3 * (wsum + c);
+        const float lh[3] = {lp[0], lp[1], lp[2]};
+        const float hc[3] = {__uint_as_float(RH[3 * c]), __uint_as_float(RH[3 * c + 1]), __uint_as_float(RH[3 * c + 2])};
+        const float sum[3] = {sm.hole[c][0], sm.hole[c][1], sm.hole[c][2]}, cnt = sm.hole[c][3];
+        const float sl = sqrtf(dotf(sum, sum));
+        const bool use_b = sl >= 1e-3f * rho * cnt;
+        // dir = sgn b / |b|, or -sgn se / |se|: the sign is that of the
+        // forward pass's centre
+        float base[3], len = sl;
+        for (int d = 0; d < 3; ++d) base[d] = sum[d];
+        if (!use_b) {
+            float se[3] = {0.f, 0.f, 0.f};
             for (int m = 1; m <= v; ++m) {
                 se[0] += S[m].ex;
                 se[1] += S[m].ey;
                 se[2] += S[m].ez;
             }
-            sl = sqrtf(dotf(se, se));
-            for (int d = 0; d < 3; ++d) dir[d] = -se[d] / sl;
+            len = sqrtf(dotf(se, se));
+            for (int d = 0; d < 3; ++d) base[d] = se[d];
         }
-        float sgn = 1.f;
-        for (int flip = 0; flip < 2; ++flip) {
-            float pm = -1e30f;
-            for (int m = 1; m <= v; ++m)
-                pm = fmaxf(pm, (S[m].gx * dir[0] + S[m].gy * dir[1] + S[m].gz * dir[2]) * rho - S[m].h);
-            if (pm <= 0.f) break;
-            for (int d = 0; d < 3; ++d) dir[d] = -dir[d];
-            sgn = -sgn;
+        const float sgn = dotf(hc, base) < 0.f ? -1.f : 1.f;
+        float dir[3], mu[3];
+        for (int d = 0; d < 3; ++d) dir[d] = sgn * base[d] / len;
+        const float dl = dotf(dir, lh);
+        own[3] += dl;  // apex rho * dir
+        for (int d = 0; d < 3; ++d) mu[d] = sgn * rho * (lh[d] - dir[d] * dl) / len;
+        for (int d = 0; d < 3; ++d) {
+            // the sum's length is cnt |b|, so this is 1 / cnt per vertex
+            sm.hole[c][d] = use_b ? mu[d] : 0.f;
+            if (!use_b) lse[d] += mu[d];
         }
-        // apex rho * dir
-        atomicAdd(&lam_node[3], dotf(lh, dir));
-        float ld[3];
-        for (int d = 0; d < 3; ++d) ld[d] = rho * lh[d];
-        const float dl = dotf(dir, ld);
-        if (use_b) {
-            // dir = sgn b / |b|: lam_b = sgn (ld - dir (dir . ld)) / |b|, then 1/cnt per vertex
-            float mu[3];
-            for (int d = 0; d < 3; ++d) mu[d] = sgn * (ld[d] - dir[d] * dl) / bl / (float)cnt;
-            for (int j = 0; j < ncirc; ++j) {
-                if ((int)(RA[kRecArcFields * j + 13] >> 16) != c) continue;
-                const int vs = (int)(RA[kRecArcFields * j + 12] & 0xffffu), ve = (int)(RA[kRecArcFields * j + 12] >> 16);
-                for (int d = 0; d < 3; ++d) {
-                    atomicAdd(&lam_v[vs][d], 0.5f * mu[d]);
-                    atomicAdd(&lam_v[ve][d], 0.5f * mu[d]);
-                }
-                const int nseg = (int)(RA[kRecArcFields * j + 13] & 0xffffu);
-                for (int ii = 1; ii < nseg; ++ii) add_interior(j, ii, mu);
-            }
-        } else {
-            // dir = -sgn se / |se|
-            for (int m = 1; m <= v; ++m)
-                for (int d = 0; d < 3; ++d) {
-                    const float g = -sgn * (ld[d] - (-sgn * dir[d]) * (-sgn * dl)) / sl;
-                    atomicAdd(&lam_e[m][d], g);
-                }
-        }
+        any_se |= !use_b;
     }
+    if (__ballot(any_se))
+        for (int d = 0; d < 3; ++d) lse[d] = wave_sum(lse[d]);
     __syncthreads();
 
     // ---- arc ends: t1, t2 are the parameters of the end vertices ------------
-    // (lane j alone writes arc j's adjoint; vertices are shared: atomics)
-    for (int j = lane; j < E; j += 64) {
-        const uint32_t u0 = RA[kRecArcFields * j + 11];
-        const bool full = (u0 >> 16) & 1u;
-        const int vs = (int)(RA[kRecArcFields * j + 12] & 0xffffu), ve = (int)(RA[kRecArcFields * j + 12] >> 16);
-        if (full) {
-            // the start vertex is the conic point at t = 0: o + b
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+        const int j = lane + 64 * t;
+        if (j >= E) continue;
+        const int p = (int)(w11[t] & 0xffu), q = (int)((w11[t] >> 8) & 0xffu);
+        const int vs = (int)(w12[t] & 0xffffu), ve = (int)(w12[t] >> 16);
+        float mu[3] = {0.f, 0.f, 0.f};
+        if (j < ncirc) {
+            // mu at every interior point
+            const float *h = sm.hole[w13[t] >> 16];
+            const float cnt = (float)((w13[t] & 0xffffu) - 1u);
+            float g = 0.f, gf = 0.f;
             for (int d = 0; d < 3; ++d) {
-                lam_arc[j][d] += lam_v[vs][d];
-                lam_arc[j][6 + d] += lam_v[vs][d];
+                mu[d] = h[d];
+                acc[t][d] += cnt * mu[d];
+                acc[t][3 + d] += mu[d] * sn1[t];
+                acc[t][6 + d] += mu[d] * cs1[t];
+                g += mu[d] * (a[t][d] * cs1[t] - b[t][d] * sn1[t]);
+                gf += mu[d] * (a[t][d] * csf[t] - b[t][d] * snf[t]);
             }
+            lt1[t] += g - gf;
+            lt2[t] += gf;
+        }
+        if ((w11[t] >> 16) & 1u) {
+            // whole conic: the start vertex is its point at t = 0, o + b
+            for (int d = 0; d < 3; ++d) {
+                const float l = L[3 * vs + d] + mu[d];
+                acc[t][d] += l;
+                acc[t][6 + d] += l;
+            }
+        } else {
+            const float iaa = 1.f / dotf(a[t], a[t]), ibb = 1.f / dotf(b[t], b[t]);
+#pragma unroll
+            for (int end = 0; end < 2; ++end) {
+                const float Lt = end ? lt2[t] : lt1[t];
+                const int vi = end ? ve : vs;
+                const uint4 w = sm.v[vi];
+                const float r[3] = {__uint_as_float(w.y) - o[t][0], __uint_as_float(w.z) - o[t][1],
+                                    __uint_as_float(w.w) - o[t][2]};
+                const float u = dotf(r, a[t]) * iaa, vv = dotf(r, b[t]) * ibb;
+                const float k = Lt / (u * u + vv * vv);
+                const float lu = k * vv * iaa, lv = -k * u * ibb;
+                // the place of the arc's pair of labels among the vertex's
+                const uint32_t np = w.x >> 24, nq = (w.x >> 16) & 0xffu;
+                const int place = (uint32_t)q == nq ? 0 : ((uint32_t)p == np ? 1 : 2);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    const float lw = lu * a[t][d] + lv * b[t][d];
+                    sm.vert[vi][3 * place + d] = lw + 0.5f * mu[d];
+                    acc[t][d] -= lw;
+                    // u = (r . a) / (a . a): du/da = (r - 2 u a) / aa
+                    acc[t][3 + d] += lu * (r[d] - 2.f * u * a[t][d]);
+                    acc[t][6 + d] += lv * (r[d] - 2.f * vv * b[t][d]);
+                }
+            }
+        }
+        if (j < ncirc) {
+            for (int f = 0; f < 9; ++f) sm.arc[j][f] = acc[t][f];
             continue;
         }
-        float o[3], a[3], bb[3], acc[9];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            o[d] = af(d, j);
-            a[d] = af(3 + d, j);
-            bb[d] = af(6 + d, j);
-        }
-#pragma unroll
-        for (int f = 0; f < 9; ++f) acc[f] = 0.f;
-        const float aa = dotf(a, a), bb2 = dotf(bb, bb);
-#pragma unroll
-        for (int end = 0; end < 2; ++end) {
-            const float Lt = lam_arc[j][9 + end];
-            const int vi = end ? ve : vs;
-            float w[3], r[3];
-            vpos(vi, w);
-            for (int d = 0; d < 3; ++d) r[d] = w[d] - o[d];
-            const float u = dotf(r, a) / aa, vv = dotf(r, bb) / bb2, den = u * u + vv * vv;
-            const float lu = Lt * vv / den, lv = -Lt * u / den;
-            const float ra = dotf(r, a), rbv = dotf(r, bb);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const float lw = lu * a[d] / aa + lv * bb[d] / bb2;
-                atomicAdd(&lam_v[vi][d], lw);
-                acc[d] -= lw;
-                // u = (r . a) / (a . a): du/da = r / aa - 2 a (r . a) / aa^2
-                acc[3 + d] += lu * (r[d] / aa - 2.f * a[d] * ra / (aa * aa));
-                acc[6 + d] += lv * (r[d] / bb2 - 2.f * bb[d] * rbv / (bb2 * bb2));
-            }
-        }
-#pragma unroll
-        for (int f = 0; f < 9; ++f) lam_arc[j][f] += acc[f];
-    }
-    __syncthreads();
-
-    // ---- conics: (o, a, b) back to the strut table ----------------------------
-    // Tangency circle (0, q): o = rho sigma e, a = rho kappa q^, b = rho kappa r^.
-    for (int j = lane; j < ncirc; j += 64) {
-        const int q = (int)((RA[kRecArcFields * j + 11] >> 8) & 0xffu);
-        const SL<float> &sq = S[q];
-        float Lo[9];
-        for (int f = 0; f < 9; ++f) Lo[f] = lam_arc[j][f];
-        const float e[3] = {sq.ex, sq.ey, sq.ez}, qf[3] = {sq.qx, sq.qy, sq.qz}, rf[3] = {sq.rx, sq.ry, sq.rz};
-        const float lo_e = dotf(Lo, e), la_q = dotf(Lo + 3, qf), lb_r = dotf(Lo + 6, rf);
-        atomicAdd(&lam_node[3], sq.sig * lo_e + sq.kap * (la_q + lb_r));
-        atomicAdd(&lam_sig[q], rho * lo_e);
-        atomicAdd(&lam_kap[q], rho * (la_q + lb_r));
-        for (int d = 0; d < 3; ++d) {
-            atomicAdd(&lam_e[q][d], rho * sq.sig * Lo[d]);
-            atomicAdd(&lam_qf[q][d], rho * sq.kap * Lo[3 + d]);
-            atomicAdd(&lam_rf[q][d], rho * sq.kap * Lo[6 + d]);
-        }
-    }
-    // Ellipse (p, q), Eq. 7, in reverse mode, one lane per arc: the steps of
-    // the conic's construction (plane p = q, in-plane axis u1, the completed
-    // square) are recomputed, then their adjoints taken in reverse order.
-    // Inputs: g_p, h_p, g_q, h_q and rho (kappa_p and sigma_p follow from
-    // g_p, h_p and rho, so 1 - |in-plane g_p|^2 = (g_p . n)^2 - (h_p / rho)^2).
-    for (int j = ncirc + lane; j < E; j += 64) {
-        const uint32_t u0 = RA[kRecArcFields * j + 11];
-        const int p = (int)(u0 & 0xffu), q = (int)((u0 >> 8) & 0xffu);
+        // ---- ellipse (p, q), Eq. 7, in reverse mode: the steps of the
+        // conic's construction (plane p = q, in-plane axis u1, the completed
+        // square) are recomputed, then their adjoints taken in reverse order.
+        // Inputs: g_p, h_p, g_q, h_q and rho (kappa_p and sigma_p follow from
+        // g_p, h_p and rho, so 1 - |in-plane g_p|^2 = (g_p . n)^2 - (h_p / rho)^2).
         const SL<float> &Sp = S[p], &Sq = S[q];
         const float gp[3] = {Sp.gx, Sp.gy, Sp.gz}, gq[3] = {Sq.gx, Sq.gy, Sq.gz};
         const float hp = Sp.h, hq = Sq.h;
         float nv[3], nh[3];
         for (int d = 0; d < 3; ++d) nv[d] = gp[d] - gq[d];
-        const float nn = sqrtf(dotf(nv, nv));
-        for (int d = 0; d < 3; ++d) nh[d] = nv[d] * (1.f / nn);
-        const float d0 = (hp - hq) / nn;
+        const float inn = 1.f / sqrtf(dotf(nv, nv));
+        for (int d = 0; d < 3; ++d) nh[d] = nv[d] * inn;
+        const float d0 = (hp - hq) * inn;
         const float gpn = dotf(gp, nh);
         const float epn = fabsf(gpn * Sp.kap), as = fabsf(Sp.sig);
         const float om = (epn - as) * (epn + as) / (Sp.kap * Sp.kap);
-        if (!(om > 0.f)) continue;  // not an ellipse: the forward pass kept no arc of it
+        if (!(om > 0.f)) {  // not an ellipse: the forward pass kept no arc of it
+            for (int f = 0; f < 8; ++f) sm.arc[j][f] = 0.f;
+            continue;
+        }
+        const float iom = 1.f / om;
         float gam[3], u1[3], tv[3] = {0.f, 0.f, 0.f};
         for (int d = 0; d < 3; ++d) gam[d] = gp[d] - nh[d] * gpn;
         const float gl = sqrtf(dotf(gam, gam));
         const bool axis_from_g = gl > 1e-4f * sqrtf(dotf(gp, gp));
-        float ml = 1.f;
+        float il;  // 1 / length of the vector that u1 is normalised from
         if (axis_from_g) {
-            for (int d = 0; d < 3; ++d) u1[d] = gam[d] / gl;
+            il = 1.f / gl;
+            for (int d = 0; d < 3; ++d) u1[d] = gam[d] * il;
             const float un = dotf(u1, nh);
             for (int d = 0; d < 3; ++d) u1[d] -= nh[d] * un;
-            const float il = 1.f / sqrtf(dotf(u1, u1));
-            for (int d = 0; d < 3; ++d) u1[d] *= il;
+            const float iu = 1.f / sqrtf(dotf(u1, u1));
+            for (int d = 0; d < 3; ++d) u1[d] *= iu;
         } else {
             tv[fabsf(nh[0]) < 0.9f ? 0 : 1] = 1.f;
             crs(nh, tv, u1);
-            ml = sqrtf(dotf(u1, u1));
-            for (int d = 0; d < 3; ++d) u1[d] /= ml;
+            il = 1.f / sqrtf(dotf(u1, u1));
+            for (int d = 0; d < 3; ++d) u1[d] *= il;
         }
         const float k0 = d0 * gpn - hp;
-        const float al0 = gl * k0 / om;
-        const float R2 = rho * rho - d0 * d0 + k0 * k0 / om;
-        const float R = sqrtf(fmaxf(R2, 0.f)), som = sqrtf(om), A = R / som;
+        const float al0 = gl * k0 * iom;
+        const float R2 = rho * rho - d0 * d0 + k0 * k0 * iom;
+        const float Rr = sqrtf(fmaxf(R2, 0.f)), isom = 1.f / sqrtf(om), A = Rr * isom;
         float cv[3];
         crs(u1, nh, cv);
         // o = d0 nh + al0 u1, a = A u1, b = R (u1 x nh)
-        float Lo[3], La[3], Lb[3];
-        for (int d = 0; d < 3; ++d) {
-            Lo[d] = lam_arc[j][d];
-            La[d] = lam_arc[j][3 + d];
-            Lb[d] = lam_arc[j][6 + d];
-        }
+        const float *Lo = acc[t], *La = acc[t] + 3, *Lb = acc[t] + 6;
         float L_nh[3], L_u1[3], L_c[3], tmp[3];
         for (int d = 0; d < 3; ++d) {
             L_nh[d] = Lo[d] * d0;
             L_u1[d] = Lo[d] * al0 + La[d] * A;
-            L_c[d] = Lb[d] * R;
+            L_c[d] = Lb[d] * Rr;
         }
         float L_d0 = dotf(Lo, nh), L_al0 = dotf(Lo, u1), L_A = dotf(La, u1), L_R = dotf(Lb, cv);
         crs(nh, L_c, tmp);
@@ -803,30 +733,32 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         crs(L_c, u1, tmp);
         for (int d = 0; d < 3; ++d) L_nh[d] += tmp[d];
         // A = R / sqrt(om), R = sqrt(max(R2, 0))
-        L_R += L_A / som;
-        float L_om = -0.5f * L_A * A / om;
-        const float L_R2 = R > 0.f ? 0.5f * L_R / R : 0.f;
+        L_R += L_A * isom;
+        float L_om = -0.5f * L_A * A * iom;
+        const float L_R2 = Rr > 0.f ? 0.5f * L_R / Rr : 0.f;
         // R2 = rho^2 - d0^2 + k0^2 / om, al0 = gl k0 / om, k0 = d0 gpn - hp
+        const float ko = k0 * iom;
         float L_rho = 2.f * rho * L_R2;
         L_d0 -= 2.f * d0 * L_R2;
-        float L_k0 = 2.f * k0 / om * L_R2;
-        L_om -= (k0 / om) * (k0 / om) * L_R2;
-        const float L_gl = k0 / om * L_al0;
-        L_k0 += gl / om * L_al0;
-        L_om -= al0 / om * L_al0;
+        float L_k0 = 2.f * ko * L_R2;
+        L_om -= ko * ko * L_R2;
+        const float L_gl = ko * L_al0;
+        L_k0 += gl * iom * L_al0;
+        L_om -= al0 * iom * L_al0;
         L_d0 += gpn * L_k0;
         float L_gpn = d0 * L_k0, L_hp = -L_k0;
         // u1: gam / |gam| (the re-projection and renormalisation have zero
         // derivative: u1 stays a unit vector in the plane), else the unit
         // vector along nh x t
-        float L_gam[3];
-        for (int d = 0; d < 3; ++d) L_gam[d] = gl > 0.f ? gam[d] * (L_gl / gl) : 0.f;
+        float L_gam[3] = {0.f, 0.f, 0.f};
         const float uu = dotf(u1, L_u1);
         if (axis_from_g) {
-            for (int d = 0; d < 3; ++d) L_gam[d] += (L_u1[d] - u1[d] * uu) / gl;
+            for (int d = 0; d < 3; ++d) L_gam[d] = (gam[d] * L_gl + (L_u1[d] - u1[d] * uu)) * il;
         } else {
             float Pm[3];
-            for (int d = 0; d < 3; ++d) Pm[d] = (L_u1[d] - u1[d] * uu) / ml;
+            if (gl > 0.f)
+                for (int d = 0; d < 3; ++d) L_gam[d] = gam[d] * (L_gl / gl);
+            for (int d = 0; d < 3; ++d) Pm[d] = (L_u1[d] - u1[d] * uu) * il;
             crs(tv, Pm, tmp);
             for (int d = 0; d < 3; ++d) L_nh[d] += tmp[d];
         }
@@ -839,26 +771,26 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         }
         L_gpn -= gn;
         // om = gpn^2 - (h_p / rho)^2
+        const float ir2 = 1.f / (rho * rho);
         L_gpn += 2.f * gpn * L_om;
-        L_hp -= 2.f * hp / (rho * rho) * L_om;
-        L_rho += 2.f * hp * hp / (rho * rho * rho) * L_om;
+        L_hp -= 2.f * hp * ir2 * L_om;
+        L_rho += 2.f * hp * hp * ir2 / rho * L_om;
         // gpn = g_p . nh
         for (int d = 0; d < 3; ++d) {
             L_gp[d] += nh[d] * L_gpn;
             L_nh[d] += gp[d] * L_gpn;
         }
         // d0 = (h_p - h_q) / |n|, nh = n / |n|, n = g_p - g_q
-        L_hp += L_d0 / nn;
-        const float L_hq = -L_d0 / nn, L_nn = -d0 / nn * L_d0;
+        const float L_dn = L_d0 * inn, L_nn = -d0 * L_dn;
         const float nl = dotf(nh, L_nh);
         for (int d = 0; d < 3; ++d) {
-            const float L_n = (L_nh[d] - nh[d] * nl) / nn + nh[d] * L_nn;
-            atomicAdd(&lam_g[p][d], L_gp[d] + L_n);
-            atomicAdd(&lam_g[q][d], -L_n);
+            const float L_n = (L_nh[d] - nh[d] * nl) * inn + nh[d] * L_nn;
+            sm.arc[j][d] = L_gp[d] + L_n;
+            sm.arc[j][4 + d] = -L_n;
         }
-        atomicAdd(&lam_h[p], L_hp);
-        atomicAdd(&lam_h[q], L_hq);
-        atomicAdd(&lam_node[3], L_rho);
+        sm.arc[j][3] = L_hp + L_dn;
+        sm.arc[j][7] = -L_dn;
+        own[3] += L_rho;
     }
     __syncthreads();
 
@@ -867,12 +799,15 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
     // F3 = g_p . w - h_p - s, F4 = |w|^2 - rho^2 - s^2 (label 0: g = 0, h = 0).
     // J^T mu = (lam_w, 0) gives mu3 = -2 s mu4 and
     // [n1 | n2 | 2 (w - s g_p)] (mu1, mu2, mu4) = lam_w.
-    for (int i = lane; i < V; i += 64) {
-        const uint32_t name = RV[4 * i];
-        const int p = (int)(name >> 24), q = (int)((name >> 16) & 0xffu), r = (int)((name >> 8) & 0xffu);
+#pragma unroll
+    for (int t = 0; t < NV; ++t) {
+        const int i = lane + 64 * t;
+        if (i >= V) continue;
+        const uint4 vw = sm.v[i];
+        const int p = (int)(vw.x >> 24), q = (int)((vw.x >> 16) & 0xffu), r = (int)((vw.x >> 8) & 0xffu);
         if (r == 0xff) continue;  // start point of a whole conic (handled with its arc)
-        float w[3], gp[3] = {0.f, 0.f, 0.f}, gq[3], gr[3];
-        vpos(i, w);
+        const float w[3] = {__uint_as_float(vw.y), __uint_as_float(vw.z), __uint_as_float(vw.w)};
+        float gp[3] = {0.f, 0.f, 0.f}, gq[3], gr[3];
         float hp = 0.f;
         if (p) {
             gp[0] = S[p].gx; gp[1] = S[p].gy; gp[2] = S[p].gz;
@@ -881,74 +816,105 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         gq[0] = S[q].gx; gq[1] = S[q].gy; gq[2] = S[q].gz;
         gr[0] = S[r].gx; gr[1] = S[r].gy; gr[2] = S[r].gz;
         const float s = dotf(gp, w) - hp;
-        float n1[3], n2[3], n3[3];
+        float n1[3], n2[3], n3[3], lw[3];
         for (int d = 0; d < 3; ++d) {
             n1[d] = gp[d] - gq[d];
             n2[d] = gp[d] - gr[d];
             n3[d] = 2.f * (w[d] - s * gp[d]);
+            lw[d] = L[3 * i + d] + sm.vert[i][d] + sm.vert[i][3 + d] + sm.vert[i][6 + d];
         }
-        const float lw[3] = {lam_v[i][0], lam_v[i][1], lam_v[i][2]};
         // Cramer on columns n1, n2, n3
-        auto det3 = [](const float *a, const float *b, const float *c) {
-            return a[0] * (b[1] * c[2] - b[2] * c[1]) - a[1] * (b[0] * c[2] - b[2] * c[0]) +
-                   a[2] * (b[0] * c[1] - b[1] * c[0]);
-        };
-        // solve [n1 n2 n3] x = lw, with the matrix holding n1, n2, n3 as columns
-        float m1[3], m2[3], m3[3];
-        const float dt = det3(n1, n2, n3);  // det of rows n1, n2, n3 = det of columns
-        // x_k = det(matrix with column k replaced by lw) / det
-        // (the determinant of a matrix equals that of its transpose)
-        for (int d = 0; d < 3; ++d) {
-            m1[d] = n1[d];
-            m2[d] = n2[d];
-            m3[d] = n3[d];
-        }
-        const float mu1 = det3(lw, m2, m3) / dt;
-        const float mu2 = det3(m1, lw, m3) / dt;
-        const float mu4 = det3(m1, m2, lw) / dt;
+        float x23[3], x31[3], x12[3];
+        crs(n2, n3, x23);
+        crs(n3, n1, x31);
+        crs(n1, n2, x12);
+        const float idt = 1.f / dotf(n1, x23);
+        const float mu1 = dotf(lw, x23) * idt;
+        const float mu2 = dotf(lw, x31) * idt;
+        const float mu4 = dotf(lw, x12) * idt;
         const float mu3 = -2.f * s * mu4;
-        // dL/dtheta = -mu^T dF/dtheta
-        const float cp = mu1 + mu2 + mu3;
-        if (p) {
-            for (int d = 0; d < 3; ++d) atomicAdd(&lam_g[p][d], -cp * w[d]);
-            atomicAdd(&lam_h[p], cp);
+        // dL/dtheta = -mu^T dF/dtheta: label m's g gets weight * w, its h -weight
+        sm.vert[i][0] = -(mu1 + mu2 + mu3);
+        sm.vert[i][1] = mu1;
+        sm.vert[i][2] = mu2;
+        for (int d = 0; d < 3; ++d) sm.vert[i][3 + d] = w[d];
+        sm.vert[i][6] = -1.f;
+        own[3] += 2.f * rho * mu4;
+    }
+    __syncthreads();
+
+    // ---- sums over each strut's end loop: its arcs and their start vertices
+    for (int x = lane; x < 4 * v; x += 64) {
+        const int m = x >> 2, d = x & 3, dc = d < 3 ? d : 0;
+        float gh = 0.f, so = 0.f, sa = 0.f, sb = 0.f;
+        const int e1 = sm.base[m + 1];
+#pragma unroll 2
+        for (int e = sm.base[m]; e < e1; ++e) {
+            const uint32_t en = sm.ent[e];
+            const float *A = sm.arc[en & 0xffu], *X = sm.vert[(en >> 8) & 0xffu];
+            if (en & kEntCircle) {
+                so += A[dc];
+                sa += A[3 + dc];
+                sb += A[6 + dc];
+            } else {
+                gh += A[(en & kEntSideQ ? 4 : 0) + d];
+            }
+            if (en & kEntVertex) gh += X[(en >> 16) & 3u] * X[3 + d];
         }
-        for (int d = 0; d < 3; ++d) {
-            atomicAdd(&lam_g[q][d], mu1 * w[d]);
-            atomicAdd(&lam_g[r][d], mu2 * w[d]);
+        sm.gh[m][d] = gh;
+        if (d < 3) {
+            sm.conic[m][d] = so;
+            sm.conic[m][3 + d] = sa;
+            sm.conic[m][6 + d] = sb;
         }
-        atomicAdd(&lam_h[q], -mu1);
-        atomicAdd(&lam_h[r], -mu2);
-        atomicAdd(&lam_node[3], 2.f * rho * mu4);
     }
     __syncthreads();
 
     // ---- strut table: g, h, e, sigma, kappa, frame from the two nodes' inputs
-    // forward mode, lanes over (strut, input) pairs: 4 inputs of this node,
-    // 4 of the far node
-    for (int x = lane; x < v * 8; x += 64) {
-        const int m = x / 8 + 1, dir = x % 8;
-        const int far = S[m].far;
-        const float4 f4 = W.node4[far];
-        V3<Dual> cd = v3(Dual(c4.x), Dual(c4.y), Dual(c4.z)), cf = v3(Dual(f4.x), Dual(f4.y), Dual(f4.z));
-        Dual rd = Dual(c4.w), rf = Dual(f4.w);
-        if (dir < 4) seed(c4, dir, cd, rd);
-        else seed(f4, dir - 4, cf, rf);
-        bool bad;
-        const SL<Dual> s = strut_entry(cd, rd, cf, rf, S[m].lower, bad);
-        const float g = lam_g[m][0] * s.gx.d + lam_g[m][1] * s.gy.d + lam_g[m][2] * s.gz.d + lam_h[m] * s.h.d +
-                        lam_e[m][0] * s.ex.d + lam_e[m][1] * s.ey.d + lam_e[m][2] * s.ez.d + lam_sig[m] * s.sig.d +
-                        lam_kap[m] * s.kap.d + lam_qf[m][0] * s.qx.d + lam_qf[m][1] * s.qy.d +
-                        lam_qf[m][2] * s.qz.d + lam_rf[m][0] * s.rx.d + lam_rf[m][1] * s.ry.d + lam_rf[m][2] * s.rz.d;
-        if (dir < 4) sm.own[m - 1][dir] = g;
-        else W.grad_he[4 * (row + m - 1) + dir - 4] = g;
+    // Tangency circle (0, q): o = rho sigma e, a = rho kappa q^, b = rho kappa r^.
+    if (lane < v) {
+        const SL<float> s = S[lane + 1];
+        const float *gh = sm.gh[lane], *Lo = sm.conic[lane], *La = Lo + 3, *Lb = Lo + 6;
+        const float e[3] = {s.ex, s.ey, s.ez}, g[3] = {s.gx, s.gy, s.gz}, es[3] = {s.sx, s.sy, s.sz};
+        const float qf[3] = {s.qx, s.qy, s.qz}, rf[3] = {s.rx, s.ry, s.rz};
+        const float4 f4 = W.node4[s.far];
+        const float dv[3] = {f4.x - c4.x, f4.y - c4.y, f4.z - c4.z};
+        const float iL = 1.f / sqrtf(dotf(dv, dv)), ik = 1.f / s.kap;
+        const float lo_e = dotf(Lo, e), lab = dotf(La, qf) + dotf(Lb, rf);
+        const float lh = gh[3];
+        // h = rho sigma / kappa, g = e / kappa, kappa = sqrt(1 - sigma^2)
+        const float l_kap = rho * lab - (dotf(gh, g) + lh * s.h) * ik;
+        const float l_sig = rho * lo_e + (lh * rho - l_kap * s.sig) * ik;
+        own[3] += s.sig * lo_e + s.kap * lab + lh * s.sig * ik + l_sig * iL;
+        // frame: r = es x axis / |es x axis|, q = es x r
+        const float ax = fabsf(es[0]), ay = fabsf(es[1]), az = fabsf(es[2]);
+        const int ja = ay < ax ? (az < ay ? 2 : 1) : (az < ax ? 2 : 0);
+        const float axis[3] = {ja == 0 ? 1.f : 0.f, ja == 1 ? 1.f : 0.f, ja == 2 ? 1.f : 0.f};
+        float c[3], l_q[3], l_r[3], l_es[3], tmp[3];
+        crs(es, axis, c);
+        const float ic = 1.f / sqrtf(dotf(c, c)), rk = rho * s.kap;
+        for (int d = 0; d < 3; ++d) l_q[d] = rk * La[d];
+        crs(rf, l_q, l_es);
+        crs(l_q, es, tmp);
+        for (int d = 0; d < 3; ++d) l_r[d] = rk * Lb[d] + tmp[d];
+        const float rr = dotf(rf, l_r);
+        for (int d = 0; d < 3; ++d) l_r[d] = (l_r[d] - rf[d] * rr) * ic;
+        crs(axis, l_r, tmp);
+        // e and es = +-e along d = far - node, sigma = (rho - r_far) / |d|
+        float l_e[3];
+        for (int d = 0; d < 3; ++d)
+            l_e[d] = gh[d] * ik + rho * s.sig * Lo[d] + lse[d] + (s.lower ? l_es[d] + tmp[d] : -(l_es[d] + tmp[d]));
+        const float el = dotf(e, l_e) + s.sig * l_sig;
+        float *out = W.grad_he + 4 * (row + lane);
+        for (int d = 0; d < 3; ++d) {
+            const float l = (l_e[d] - e[d] * el) * iL;
+            out[d] = l;
+            own[d] -= l;
+        }
+        out[3] = -l_sig * iL;
     }
-    __syncthreads();
-    if (lane < 4) {
-        float acc = lam_node[lane];
-        for (int m = 0; m < v; ++m) acc += sm.own[m][lane];
-        W.grad_node[4 * n + lane] = acc;
-    }
+    for (int d = 0; d < 4; ++d) own[d] = wave_sum(own[d]);
+    if (lane == 0) *(float4 *)(W.grad_node + 4 * n) = make_float4(own[0], own[1], own[2], own[3]);
 }
 
 // nodes of up to kVmax struts, one block (wave) each
