@@ -58,7 +58,7 @@ __device__ inline void add3(float *p, float3 v, float s)
 // neighbouring lanes, add each run's sum.  (With an atomic per corner and
 // coordinate the kernel was bound by them, some 60 cycles of the compute
 // unit's LDS per instruction.)  The bands' bookkeeping is read for all struts
-// at once, a lane per strut.  Octet 32^3, k = 16: 1.45 -> 0.70 ms.
+// at once, a lane per strut.  Octet 32^3, k = 16: 1.45 -> 0.62 ms.
 //
 // kLossLds vertices at a time; a node with more of them takes up to
 // kLossPasses passes over its triangles, beyond that it adds through global
@@ -138,40 +138,44 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
     double area = 0.0, vol = 0.0, sq = 0.0;
     const bool lds = M <= kLossLds * kLossPasses;
     int c0 = 0;  // vertices [c0, c0 + kLossLds) of the node are in LDS
-    // a triangle's corners and the gradient on each; its terms when counted
+    // a triangle and its normal; its terms when counted (area twice, volume
+    // six times what they are: scaled once per node)
     struct Tri {
         int32_t i0, i1, i2;
-        float3 g0, g1, g2;
+        float3 a, b, c, n;
+        float wa;
     };
     const bool grad = P.w_area != 0.f || P.w_vol != 0.f;
-    auto tri_do = [&](int64_t t, bool count) {
+    const float wv = P.w_vol / 6.f;
+    // turn: its corners in the order 2, 0, 1
+    auto tri_at = [&](int64_t t, bool count, bool turn) {
         Tri T;
-        T.i0 = P.tri[3 * t];
-        T.i1 = P.tri[3 * t + 1];
-        T.i2 = P.tri[3 * t + 2];
-        const float3 a = sub3(f3(P.xyz + 3 * (int64_t)T.i0), P.p0), b = sub3(f3(P.xyz + 3 * (int64_t)T.i1), P.p0),
-                     c = sub3(f3(P.xyz + 3 * (int64_t)T.i2), P.p0);
-        const float3 Nn = crs3(sub3(b, a), sub3(c, a));
-        const float nl = sqrtf(Nn.x * Nn.x + Nn.y * Nn.y + Nn.z * Nn.z);
-        const float3 bc = crs3(b, c), ca = crs3(c, a), ab = crs3(a, b);
+        const int32_t j0 = P.tri[3 * t], j1 = P.tri[3 * t + 1], j2 = P.tri[3 * t + 2];
+        T.i0 = turn ? j2 : j0;
+        T.i1 = turn ? j0 : j1;
+        T.i2 = turn ? j1 : j2;
+        T.a = sub3(f3(P.xyz + 3 * (int64_t)T.i0), P.p0);
+        T.b = sub3(f3(P.xyz + 3 * (int64_t)T.i1), P.p0);
+        T.c = sub3(f3(P.xyz + 3 * (int64_t)T.i2), P.p0);
+        T.n = crs3(sub3(T.b, T.a), sub3(T.c, T.a));
+        const float nl = sqrtf(T.n.x * T.n.x + T.n.y * T.n.y + T.n.z * T.n.z);
         if (count) {
-            area += 0.5 * (double)nl;
-            vol += ((double)a.x * bc.x + (double)a.y * bc.y + (double)a.z * bc.z) / 6.0;
+            const float3 bc = crs3(T.b, T.c);
+            area += (double)nl;
+            vol += (double)T.a.x * bc.x + (double)T.a.y * bc.y + (double)T.a.z * bc.z;
         }
-        const float wa = (P.w_area != 0.f && nl > 0.f) ? 0.5f * P.w_area / nl : 0.f, wv = P.w_vol / 6.f;
-        auto corner = [&](float3 e, float3 vterm) {
-            const float3 ga = crs3(Nn, e);
-            return make_float3(wa * ga.x + wv * vterm.x, wa * ga.y + wv * vterm.y, wa * ga.z + wv * vterm.z);
-        };
-        T.g0 = corner(sub3(c, b), bc);
-        T.g1 = corner(sub3(a, c), ca);
-        T.g2 = corner(sub3(b, a), ab);
+        T.wa = (P.w_area != 0.f && nl > 0.f) ? 0.5f * P.w_area / nl : 0.f;
         return T;
+    };
+    // the gradient on the corner before the edge b -> c
+    auto corner = [&](const Tri &T, float3 b, float3 c) {
+        const float3 ga = crs3(T.n, sub3(c, b)), x = crs3(b, c);
+        return make_float3(T.wa * ga.x + wv * x.x, T.wa * ga.y + wv * x.y, T.wa * ga.z + wv * x.z);
     };
     // place of a vertex in LDS, -1: not the node's, or of another pass
     auto place = [&](int32_t vi) {
-        const int64_t i = vi - m0;
-        return vi >= m0 && vi < m1 && i >= c0 && i < c0 + kLossLds ? (int)i - c0 : -1;
+        const uint32_t i = (uint32_t)vi - (uint32_t)(m0 + c0);
+        return i < (uint32_t)(M - c0 < kLossLds ? M - c0 : kLossLds) ? (int)i : -1;
     };
     // adds of one step go to distinct places
     auto add = [&](int i, float3 d) {
@@ -201,11 +205,11 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
         __syncthreads();
         // hole fans of the node
         for (int64_t t = f0 + lane; t < f1; t += 64) {
-            const Tri T = tri_do(t, first);
+            const Tri T = tri_at(t, first, false);
             if (grad) {
-                add_any(T.i0, T.g0);
-                add_any(T.i1, T.g1);
-                add_any(T.i2, T.g2);
+                add_any(T.i0, corner(T, T.b, T.c));
+                add_any(T.i1, corner(T, T.c, T.a));
+                add_any(T.i2, corner(T, T.a, T.b));
             }
         }
         // bands of the incident struts (terms at the lower end)
@@ -220,32 +224,37 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
                 // the lower end's edges come first, run u, u'; then the
                 // upper end's, u', u
                 const bool edge = act && (lower ? l < own : l >= nb - own);
+                const bool other = act && !edge;
+                // an edge triangle adds at its edge's ends (corners 0 and 1),
+                // the other loop's at its apex: turned, its corner 0
                 Tri T;
-                T.i0 = T.i1 = T.i2 = -1;
-                T.g0 = T.g1 = T.g2 = make_float3(0.f, 0.f, 0.f);
-                if (act) T = tri_do(b0 + l, lower && first);
+                float3 g0 = make_float3(0.f, 0.f, 0.f), g1 = g0;
+                T.i0 = T.i1 = -1;
+                if (act) {
+                    T = tri_at(b0 + l, lower && first, other);
+                    g0 = corner(T, T.b, T.c);
+                    g1 = corner(T, T.c, T.a);
+                }
                 if (!grad) continue;
                 if (!lds) {
                     if (act) {
-                        add_any(T.i0, T.g0);
-                        add_any(T.i1, T.g1);
-                        add_any(T.i2, T.g2);
+                        add_any(T.i0, g0);
+                        if (edge) add_any(T.i1, g1);
                     }
                     continue;
                 }
                 const int p0 = edge ? place(lower ? T.i0 : T.i1) : -1, p1 = edge ? place(lower ? T.i1 : T.i0) : -1;
-                if (p0 >= 0) add(p0, lower ? T.g0 : T.g1);
+                if (p0 >= 0) add(p0, lower ? g0 : g1);
                 __syncthreads();
-                if (p1 >= 0) add(p1, lower ? T.g1 : T.g0);
+                if (p1 >= 0) add(p1, lower ? g1 : g0);
                 __syncthreads();
                 // runs of equal apexes among the other loop's edges
-                const bool other = act && !edge;
-                const int pa = other ? place(T.i2) : -1;
+                const int pa = other ? place(T.i0) : -1;
                 const int pp = __shfl_up(pa, 1, 64);
                 const bool head = lane == 0 || pa != pp;
                 const unsigned long long hm = __ballot(head);
                 const int lead = 63 - __clzll(hm & ((2ull << lane) - 1)), rank = lane - lead;
-                float3 x = T.g2;
+                float3 x = g0;
                 for (int d = 1; __ballot(pa >= 0 && rank >= d) != 0; d <<= 1) {
                     const float3 y = make_float3(__shfl_up(x.x, d, 64), __shfl_up(x.y, d, 64), __shfl_up(x.z, d, 64));
                     if (rank >= d) {
@@ -290,8 +299,8 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
         sq += __shfl_xor(sq, o, 64);
     }
     if (lane == 0) {  // the node's terms; summed in a fixed order by k_loss_reduce
-        nt[0] = area;
-        nt[1] = vol;
+        nt[0] = 0.5 * area;
+        nt[1] = vol / 6.0;
         nt[2] = sq;
     }
 }
