@@ -1133,8 +1133,6 @@ int lm_arc_encode(lm_plan *P, const float *d_arc_f32, const uint32_t *d_arc_u32,
     lm::ClearRuns cl;
     cl.p[0] = (uint32_t *)P->codec_ctr;
     cl.n[0] = 2;
-    cl.p[1] = c->d_fallback_mask;
-    cl.n[1] = (n_arcs + 31) / 32;
     HIPCHK(lm::launch_clear(cl, P->st));
     HIPCHK(lm::launch_arc_codec(P->in, P->w, true, d_arc_f32, d_arc_u32, n_arcs, ld, (double)r_min, (double)r_max,
                                 c->d_codes, c->d_fallback_mask, c->d_fallback, c->cap_fallback, P->codec_ctr,

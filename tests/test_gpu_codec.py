@@ -98,3 +98,71 @@ def test_codec_fallback_capacity():
         assert torch.equal(dec, r.arc_f32)
     finally:
         M.close()
+
+
+def test_decode_every_angle_code():
+    """Every code of an azimuth and of a polar angle, for both vectors: FP64
+    to a few rounding steps, then one rounding to FP32.  b's direction
+    a x d / |a x d| magnifies them by 1 / |a x d|."""
+    import types
+
+    import torch
+
+    from paper_2405_15197_amd import Mesher
+
+    lat = latgen.config(4, scale=2)
+    rng = np.random.default_rng(4)
+    n = 1 << 16
+    i = np.arange(n)
+    q = {name: rng.integers(0, 1 << bits, n) for name, bits in codec.FIELDS}
+    q["pha"], q["tha"] = i, i % (1 << codec.M_TH)
+    q["phc"], q["thc"] = (i * 40503 + 7) % n, (i // 2) ^ 1
+    codes = codec.pack(q)
+    M = Mesher(lat)
+    try:
+        r = M.run(8)
+        sel = torch.from_numpy(rng.integers(0, r.arc_u32.shape[1], n)).cuda()
+        u32 = r.arc_u32[:, sel].contiguous()
+        lo, hi = M.radius_range()
+        enc = {"codes": torch.from_numpy(codes.view(np.int32)).cuda(), "r_min": lo, "r_max": hi, "cap_fallback": 0,
+               "mask": torch.zeros(n // 32, dtype=torch.int32, device="cuda"), "_fb_full": torch.empty((1, 11), device="cuda")}
+        dec = M.decode_arcs(enc, types.SimpleNamespace(arc_u32=u32)).cpu().numpy().T.astype(np.float64)
+        u = u32.cpu().numpy().view(np.uint32)
+    finally:
+        M.close()
+    d = codec.reference_dirs(lat, u[2], u[0] & 0xFF, (u[0] >> 8) & 0xFF)
+    want = codec.decode(q, d, lo, hi)
+    ah = want[:, 3:6] / np.linalg.norm(want[:, 3:6], axis=1)[:, None]
+    x = np.linalg.norm(np.cross(ah, d), axis=1)
+    tol = 2.0**-24 * np.abs(want) + 16 * 2.0**-52 * 4 * hi
+    tol[:, 6:9] += 16 * 2.0**-52 * hi / np.maximum(x, 1e-12)[:, None]
+    assert (np.abs(dec - want) <= tol * (1 + 1e-6)).all(), float(np.max(np.abs(dec - want) / tol))
+
+
+@pytest.mark.parametrize("quantile", [0.001, 0.3, 0.97])
+def test_arcs_kept_whole_between_coded_ones(quantile):
+    """Few, some and most arcs of a wave out of the radius range: every one
+    has a slot of its own and comes back bit for bit; a ragged last wave."""
+    from paper_2405_15197_amd import Mesher
+
+    M = Mesher(latgen.cubic(5, radius=("uniform", 0.05, 0.15), jitter=0.04, seed=5))
+    try:
+        r = M.run(8)
+        E = r.arc_f32.shape[1] - 37
+        r.arc_f32, r.arc_u32 = r.arc_f32[:, :E], r.arc_u32[:, :E]
+        arcs = r.arc_f32.cpu().numpy()
+        ra = np.linalg.norm(arcs[3:6].astype(np.float64), axis=0)
+        lo = float(np.quantile(ra, quantile))
+        hi = max(lo, M.radius_range()[1])
+        enc = M.encode_arcs(r, r_min=lo, r_max=hi, cap_fallback=E)
+        dec = M.decode_arcs(enc, r).cpu().numpy()
+        mask = enc["mask"].cpu().numpy().view(np.uint32)
+        codes = enc["codes"].cpu().numpy()
+    finally:
+        M.close()
+    i = np.arange(E)
+    fb = ((mask[i >> 5] >> (i & 31)) & 1).astype(bool)
+    assert fb[ra < np.float32(lo) * (1 - 1e-6)].all() and 0 < fb.sum() == enc["n_fallback"]
+    assert np.array_equal(np.sort(codes[fb, 0]), np.arange(fb.sum()))
+    assert np.array_equal(dec[:, fb], arcs[:, fb])
+    assert not np.array_equal(dec[:, ~fb], arcs[:, ~fb])
