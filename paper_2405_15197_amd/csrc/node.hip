@@ -2102,27 +2102,28 @@ __device__ inline int drain_class(const Params &P, int cls, Shared<float, C> *sh
 // 1,280-byte pieces) against four, six registers spilled: BCC 64^3, k = 16,
 // step 3.84 -> 3.37 ms; sink BCC 128^3, k = 12, 26.4 -> 22.3 ms; octet 32^3
 // forward + adjoint 4.20 -> 4.04 ms.
-template <typename C, int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_node32(Params P, int cls)
-{
-    __shared__ Shared<float, C> sh[64 / C::W];
-    drain_class<C, MODE>(P, cls, sh, nullptr, blockIdx.x);
-}
-
-// The classes v <= 4 (four nodes per wave) and 5..8 (two) in one persistent
-// launch, the heavier first: the light nodes fill the tail of the others
-// instead of running as a short launch of their own.  The two LDS layouts
-// share one block of LDS, used by one class at a time.
-union SharedV4V8 {
+//
+// The one-wave classes, 9..kVmax struts, 5..8 (two nodes per wave) and up to 4
+// (four), in one persistent launch, the heavier first: the lighter nodes fill
+// the tail of the others instead of running as launches of their own.  The
+// LDS layouts share one block of LDS, used by one class at a time.  With 9..16
+// in a launch of their own -> in this one: octet 13^3 271 -> 258 us, cubic 6^3
+// 109 -> 106 us, k-NN 19^3 406 -> 397 us, octet 32^3 forward + adjoint 2.75 ->
+// 2.70 ms, 24 mixed parts 2.26 -> 2.21 ms.
+union SharedOneWave {
+    Shared<float, CfgV16> c;
     Shared<float, CfgV8> b[2];
     Shared<float, CfgV4> a[4];
 };
 template <int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_node32_v8v4(Params P)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_node32(Params P)
 {
-    __shared__ SharedV4V8 sh;
-    const unsigned used = (unsigned)drain_class<CfgV8, MODE>(P, 1, sh.b, nullptr, blockIdx.x);
-    drain_class<CfgV4, MODE>(P, 0, sh.a, nullptr, (blockIdx.x + gridDim.x - used) % gridDim.x);
+    __shared__ SharedOneWave sh;
+    unsigned b = blockIdx.x;
+    auto after = [&](int used) { b = (b + gridDim.x - (unsigned)used) % gridDim.x; };
+    after(drain_class<CfgV16, MODE>(P, 2, &sh.c, nullptr, b));
+    after(drain_class<CfgV8, MODE>(P, 1, sh.b, nullptr, b));
+    drain_class<CfgV4, MODE>(P, 0, sh.a, nullptr, b);
 }
 
 // The multi-wave class: one node per block of kBigWaves waves, items from the
@@ -2259,27 +2260,22 @@ hipError_t launch_node(const Inputs &in, const Work &w, int k, float kappa_max, 
         items = items < lo ? lo : items;
         return (unsigned)(items < cap ? items : cap);
     };
-    // classes 0 and 1 share a launch: items of both
-    const int64_t light = items_of(0, 4) + items_of(1, 2);
-    const unsigned g01 = clampg(light, kNodeGrid), g01_redo = clampg(light, kRedoGrid);
-    const unsigned g2 = clampg(items_of(2, 1), kNodeGrid), g2_redo = clampg(items_of(2, 1), kRedoGrid);
+    // the one-wave classes share a launch: items of all
+    const int64_t items = items_of(0, 4) + items_of(1, 2) + items_of(2, 1);
+    const unsigned grid = clampg(items, kNodeGrid), redo_grid = clampg(items, kRedoGrid);
     const unsigned big_grid = clampg(items_of(3, 1), kBigGrid);
     if (src_rec) {
         if (!redo || !redo_cnt) return hipErrorInvalidValue;
-        k_node32_v8v4<kModeRetri><<<g01, 64, 0, st>>>(P);
-        k_node32<CfgV16, kModeRetri><<<g2, 64, 0, st>>>(P, 2);
+        k_node32<kModeRetri><<<grid, 64, 0, st>>>(P);
         k_node32_big<kModeRetri><<<big_grid, CfgBig::W, 0, st>>>(P);
         // the redo lists are short unless most nodes needed FP64 at the source
-        k_node32_v8v4<kModeRedo><<<g01_redo, 64, 0, st>>>(P);
-        k_node32<CfgV16, kModeRedo><<<g2_redo, 64, 0, st>>>(P, 2);
+        k_node32<kModeRedo><<<redo_grid, 64, 0, st>>>(P);
         k_node32_big<kModeRedo><<<big_grid, CfgBig::W, 0, st>>>(P);
     } else if (sink) {
-        k_node32_v8v4<kModeSink><<<g01, 64, 0, st>>>(P);
-        k_node32<CfgV16, kModeSink><<<g2, 64, 0, st>>>(P, 2);
+        k_node32<kModeSink><<<grid, 64, 0, st>>>(P);
         k_node32_big<kModeSink><<<big_grid, CfgBig::W, 0, st>>>(P);
     } else {
-        k_node32_v8v4<kModeMesh><<<g01, 64, 0, st>>>(P);
-        k_node32<CfgV16, kModeMesh><<<g2, 64, 0, st>>>(P, 2);
+        k_node32<kModeMesh><<<grid, 64, 0, st>>>(P);
         k_node32_big<kModeMesh><<<big_grid, CfgBig::W, 0, st>>>(P);
     }
     return hipGetLastError();
