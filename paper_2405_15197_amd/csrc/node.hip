@@ -366,6 +366,20 @@ __device__ inline uint64_t group_sum_u64(uint64_t x)
     }
 }
 
+// Between what the lanes of a group write to LDS and what they read of each
+// other.  A wave's LDS accesses are done in order, so within it only the
+// compiler must keep them so; __syncthreads() also waits for their end.
+template <int W>
+__device__ __forceinline__ void group_sync()
+{
+    if constexpr (W > 64) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // The node's status word as every lane of the group sees it at this point.
 // Within a wave the lanes read it together; a group of several waves reads
 // it between two barriers, so that no wave can already be setting bits of
@@ -939,7 +953,7 @@ __device__ __forceinline__ void node_tail(const Params &P, Shared<T, CF> &sh, co
                 sh.ncirc = nc;
             }
         }
-        __syncthreads();
+        group_sync<WL>();
         // Eq. 13: barycentre of each contour's vertices (each once: half of
         // both ends of every arc plus its interior points), projected on the
         // nodal sphere; the point opposite is used when the projection falls
@@ -981,7 +995,7 @@ __device__ __forceinline__ void node_tail(const Params &P, Shared<T, CF> &sh, co
             sh.hc[c][1] = dir.y * rho;
             sh.hc[c][2] = dir.z * rho;
         }
-        __syncthreads();
+        group_sync<WL>();
         if (group_status<WL>(sh)) goto finish;
         // record space: bump allocation in the node's region, asked for here
         // and needed after the loops are laid out (the atomic's way to memory
@@ -1034,7 +1048,7 @@ __device__ __forceinline__ void node_tail(const Params &P, Shared<T, CF> &sh, co
                 atomicOr(&W.flags[0], DF_RECCAP);
             }
         }
-        __syncthreads();
+        group_sync<WL>();
         // Lanes over the points of all arcs: a point is evaluated once for the
         // two loops that its arc is on (94 points for the 152 loop samples of
         // a BCC node at k = 16; with the record asked for before the loops
@@ -1164,7 +1178,7 @@ __device__ __forceinline__ void node_tail(const Params &P, Shared<T, CF> &sh, co
                     }
                 }
             }
-            __syncthreads();
+            group_sync<WL>();
             // from each entry's last sample to the next one's first, the last
             // of a loop to its first
             for (int e = lane; e < nent; e += WL) {
@@ -1178,16 +1192,16 @@ __device__ __forceinline__ void node_tail(const Params &P, Shared<T, CF> &sh, co
                 step(sh.ph_last[at(before)], sh.ph_first[x], m, e == b0 ? 0 : (so >= 0 ? so : ~so) - sh.lbase[m]);
             }
         }
-        __syncthreads();
+        group_sync<WL>();
         over_lanes<WL, CF::VM>(lane, 0, v - 1, [&](int l) {
             if (sh.loop_desc[l + 1] != 1) atomicOr(&sh.status, NS_LOOP);
             W.he_rot[row + l] = sh.loop_rot[l + 1];
         });
-        __syncthreads();
+        group_sync<WL>();
     }
 
 finish:
-    __syncthreads();
+    group_sync<WL>();
     {
         const int status = sh.status;
         const int E = sh.n_arc, V = sh.n_vert, NC = sh.n_contour;
@@ -1321,7 +1335,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         sh.rec = -1;
         sh.S[0].gx = sh.S[0].gy = sh.S[0].gz = sh.S[0].h = (T)0;
     }
-    __syncthreads();
+    group_sync<WL>();
     if (v == 0 || v > CF::VM) {
         if (lane == 0) {
             for (int c = 0; c < kNodeCols; ++c) W.node_cnt[c * N + n] = 0;
@@ -1345,13 +1359,13 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         if (bad || far == n) atomicOr(&sh.status, NS_INVALID_STRUT);
         sh.S[l + 1] = s;
     });
-    __syncthreads();
+    group_sync<WL>();
     over_lanes<WL, CF::VM>(lane, 0, v - 1, [&](int l) {
         for (int j = 0; j < v; ++j)
             if (j != l && sh.S[j + 1].far == sh.S[l + 1].far) atomicOr(&sh.status, NS_DUPLICATE);
     });
     if (F32 && lane == 0 && !(P.kappa_max > 0.f)) atomicOr(&sh.status, NS_PREC);  // all FP64
-    __syncthreads();
+    group_sync<WL>();
     if (group_status<WL>(sh)) goto tail;
 
     // ---- conics, trimming, arcs and owned vertices ------------------------
@@ -1443,9 +1457,9 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                     }
                 }
             }
-            __syncthreads();
+            group_sync<WL>();
             if (lane == 0 && fits) sh.n_arc = have + tot;
-            __syncthreads();
+            group_sync<WL>();
         }
     }
     if (group_status<WL>(sh) & (F32 ? ~0 : NS_CAPACITY)) goto tail;
@@ -1505,7 +1519,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             own_name[2 * j] = en.full || en.rs > en.q ? en.ns : kNoName;
             own_name[2 * j + 1] = !en.full && en.re > en.q ? en.ne : kNoName;
         }
-        __syncthreads();
+        group_sync<WL>();
         int vt = 0;
         for (int j0 = 0; j0 < E; j0 += WL) {
             const int j = j0 + lane;
@@ -1561,7 +1575,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                 }
             }
         }
-        __syncthreads();
+        group_sync<WL>();
         if (lane == 0) {
             sh.n_vert = vt;
             if (vt > CF::VC) atomicOr(&sh.status, NS_CAPACITY);
@@ -1581,7 +1595,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                     a1.ns = ns; a1.ne = ne; a1.t1 = t1; a1.dt = dt;
                 }
         }
-        __syncthreads();
+        group_sync<WL>();
     }
     if (group_status<WL>(sh)) goto tail;
 
@@ -1598,7 +1612,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
         }
         // segment counts (Eq. 11)
         for (int i = lane; i < V; i += WL) sh.vdeg[i] = 0;
-        __syncthreads();
+        group_sync<WL>();
         for (int j = lane; j < E; j += WL) {
             ArcL<T> &A = sh.A[j];
             if (A.full) {
@@ -1615,10 +1629,10 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             atomicAdd(&sh.vdeg[A.vs], 1);
             atomicAdd(&sh.vdeg[A.ve], 1);
         }
-        __syncthreads();
+        group_sync<WL>();
         for (int i = lane; i < V; i += WL)
             if ((sh.vname[i] & 0xff00u) != 0xff00u && sh.vdeg[i] != 3) atomicOr(&sh.status, NS_TOPOLOGY);
-        __syncthreads();
+        group_sync<WL>();
         if (group_status<WL>(sh)) goto tail;
     }
 
@@ -1635,13 +1649,13 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             sh.loop_len[l] = 0;
             sh.loop_full[l] = 0;
         });
-        __syncthreads();
+        group_sync<WL>();
         for (int j = lane; j < E; j += WL) {
             const ArcL<T> &A = sh.A[j];
             if (A.p) atomicAdd(&sh.loop_cnt[A.p], 1);
             atomicAdd(&sh.loop_cnt[A.q], 1);
         }
-        __syncthreads();
+        group_sync<WL>();
         if constexpr (WL > CF::VM + 1) {
             int c = (lane >= 1 && lane <= v) ? sh.loop_cnt[lane] : 0, tot;
             int base = group_excl_scan<WL>(c, &tot);
@@ -1655,9 +1669,9 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             }
             sh.loop_base[v + 1] = acc;
         }
-        __syncthreads();
+        group_sync<WL>();
         over_lanes<WL, CF::VM>(lane, 0, v, [&](int l) { sh.loop_cnt[l] = 0; });  // reused as fill cursor
-        __syncthreads();
+        group_sync<WL>();
         for (int j = lane; j < E; j += WL) {
             const ArcL<T> &A = sh.A[j];
             T tm = A.t1 + (T)0.5 * A.dt;
@@ -1683,7 +1697,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                 if (A.full) atomicAdd(&sh.loop_full[m], 1);
             }
         }
-        __syncthreads();
+        group_sync<WL>();
         const int tot = sh.loop_base[v + 1];
         auto sname = [&](int pp) { return (uint32_t)sh.entry_off[pp]; };
         auto ename = [&](int pp) {
@@ -1710,7 +1724,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             const int c = sh.loop_base[l + 1] - sh.loop_base[l];
             if (c == 0 || (sh.loop_full[l] && c != 1)) atomicOr(&sh.status, NS_LOOP);
         });
-        __syncthreads();
+        group_sync<WL>();
         if (group_status<WL>(sh)) goto tail;
         // position of each arc in its loop.  Every arc reached within c - 1
         // steps from the first makes the chain a path through all c arcs; it
@@ -1732,7 +1746,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             if (t == c - 1 && sh.loop_next[pp] != sh.loop_first[m]) atomicOr(&sh.status, NS_LOOP);
         }
         if (tot > 2 * CF::AC && lane == 0) atomicOr(&sh.status, NS_CAPACITY);
-        __syncthreads();
+        group_sync<WL>();
         if (group_status<WL>(sh)) goto tail;
     }
 
@@ -1764,7 +1778,7 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
             }
             sh.clabel[i] = lab;
         }
-        __syncthreads();
+        group_sync<WL>();
         for (int i = lane; i < ncirc; i += WL) {
             uint32_t lab = sh.clabel[i];
             int rank = 0;
@@ -1781,9 +1795,9 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
                 if (sh.clabel[t] == lab) first = false;
             if (first) atomicAdd(&sh.n_contour, 1);
         }
-        __syncthreads();
+        group_sync<WL>();
         if (lane == 0 && sh.n_vert - sh.n_arc + sh.n_contour != 2 - v) atomicOr(&sh.status, NS_TOPOLOGY);
-        __syncthreads();
+        group_sync<WL>();
         if (group_status<WL>(sh)) goto tail;
     }
 
@@ -1876,7 +1890,7 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
         sh.n_vert = V;
         sh.n_contour = NC;
     }
-    __syncthreads();
+    group_sync<WL>();
     if (lane < E) {
         ArcL<T> &A = sh.A[lane];
         for (int d = 0; d < 3; ++d) {
@@ -1917,13 +1931,13 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
         sh.loop_ord[e] = (uint8_t)(e - tbyte(m - 1));  // loop_base[m] = tbyte(m - 1)
         sh.entry_m[e] = (uint8_t)m;
     }
-    __syncthreads();
+    group_sync<WL>();
     if (lane >= 1 && lane <= v) {
         int len = 0;
         for (int e = sh.loop_base[lane]; e < sh.loop_base[lane + 1]; ++e) len += sh.A[sh.loop_arc[e]].nseg;
         sh.loop_len[lane] = len;
     }
-    __syncthreads();
+    group_sync<WL>();
     node_tail<T, CF, false>(P, sh, n, k, v, row, rho, cen);
 }
 
@@ -1959,10 +1973,11 @@ struct List {
     int32_t *ctr;         // the list's first work counter
     int32_t *hand;
     int items, t;
+    int teams;            // that drain it
 };
-__device__ inline List dealt_list(int32_t *sched, int list, int64_t items)
+__device__ inline List dealt_list(int32_t *sched, int list, int64_t items, int teams)
 {
-    return List{sched_ctr(sched, list, 0), nullptr, (int)items, items >= 32 * (int64_t)gridDim.x ? 4 : 0};
+    return List{sched_ctr(sched, list, 0), nullptr, (int)items, items >= 32 * (int64_t)teams ? 4 : 0, teams};
 }
 // length of sub-list l (0 from kSub on)
 __device__ inline int sub_len(const List &q, int l)
@@ -1979,16 +1994,16 @@ __device__ inline int64_t dealt_item(int t, int c, int i)
     return ((((int64_t)(i >> t) * kSub) + c) << t) + (i & ((1 << t) - 1));
 }
 
-// items of a first range, and of those of all blocks l, l + kSub, ... of the
-// grid, which start on sub-list l of n items
-__device__ inline int first_range(int n)
+// items of a first range, and of those of all teams l, l + kSub, ..., which
+// start on sub-list l of n items
+__device__ inline int first_range(const List &q, int n)
 {
-    const int g = n / (2 * (((int)gridDim.x + kSub - 1) / kSub));
+    const int g = n / (2 * ((q.teams + kSub - 1) / kSub));
     return g < 1 ? 1 : (g > kGrabMax ? kGrabMax : g);
 }
-__device__ inline int first_ranges(int n, int l)
+__device__ inline int first_ranges(const List &q, int n, int l)
 {
-    return l < kSub ? first_range(n) * (((int)gridDim.x - l + kSub - 1) / kSub) : 0;
+    return l < kSub ? first_range(q, n) * ((q.teams - l + kSub - 1) / kSub) : 0;
 }
 
 struct Grab {
@@ -1996,12 +2011,12 @@ struct Grab {
     int first, end;  // the range
 };
 
-// the block's first range; b: its rank in the grid
+// the team's first range; b: its rank
 __device__ inline Grab grab_first(const List &q, unsigned b)
 {
-    const int c = (int)(b % kSub), n = lane_value(sub_len(q, threadIdx.x & 63), c), g = first_range(n);
+    const int c = (int)(b % kSub), n = lane_value(sub_len(q, threadIdx.x & 63), c), g = first_range(q, n);
     const int first = (int)(b / kSub) * g;
-    return Grab{c, first_ranges(n, c), first, first + g < n ? first + g : n};
+    return Grab{c, first_ranges(q, n, c), first, first + g < n ? first + g : n};
 }
 
 // The next range, by one wave.  A function of its own: few calls per block,
@@ -2009,8 +2024,8 @@ __device__ inline Grab grab_first(const List &q, unsigned b)
 // computation.
 __device__ __attribute__((noinline)) Grab grab_more(List q, int c, int seen)
 {
-    const int lane = threadIdx.x & 63, blocks = ((int)gridDim.x + kSub - 1) / kSub;
-    const int mine = sub_len(q, lane), pre = first_ranges(mine, lane);
+    const int lane = threadIdx.x & 63, blocks = (q.teams + kSub - 1) / kSub;
+    const int mine = sub_len(q, lane), pre = first_ranges(q, mine, lane);
     for (;;) {
         const int n = lane_value(mine, c);
         if (seen < n) {
@@ -2033,18 +2048,19 @@ __device__ __attribute__((noinline)) Grab grab_more(List q, int c, int seen)
     }
 }
 
-// f(sub-list, place in it) for the items of the list that fall to this block,
-// whose every thread calls it; b: its rank in the grid
-template <typename F>
+// f(sub-list, place in it) for the items of the list that fall to this team, a
+// wave or, with s_grab (four words of LDS), a block, all of whose threads call
+// it; b: its rank
+template <bool BLOCK, typename F>
 __device__ __forceinline__ void drain(const List &q, unsigned b, int *s_grab, F &&f)
 {
     Grab G = grab_first(q, b);
     for (;;) {
         for (int i = G.first; i < G.end; ++i) {
             f(G.c, i);
-            __syncthreads();
+            group_sync<BLOCK ? 128 : 64>();
         }
-        if (blockDim.x == 64) {
+        if constexpr (!BLOCK) {
             G = grab_more(q, __builtin_amdgcn_readfirstlane(G.c), __builtin_amdgcn_readfirstlane(G.seen));
         } else {
             if (threadIdx.x < 64) {
@@ -2080,8 +2096,8 @@ __device__ inline int drain_class(const Params &P, int cls, Shared<float, C> *sh
     const int64_t base = P.w.cls_info[4 + cls];
     const int32_t *list = MODE == kModeRedo ? P.redo : P.w.queue;
     const int64_t items = (cnt + NPW - 1) / NPW;
-    const List q = dealt_list(P.w.sched, (MODE == kModeRedo ? SCHED_REDO : SCHED_CLASS) + cls, items);
-    drain(q, b, s_grab, [&](int c, int i) {
+    const List q = dealt_list(P.w.sched, (MODE == kModeRedo ? SCHED_REDO : SCHED_CLASS) + cls, items, (int)gridDim.x);
+    drain<(C::W > 64)>(q, b, s_grab, [&](int c, int i) {
         const int64_t qi = dealt_item(q.t, c, i) * NPW + slot;
         if (qi >= cnt) return;
         const int64_t node = list[base + qi];
@@ -2151,42 +2167,73 @@ __global__ void __launch_bounds__(64) k_node32_thread(Params P, Shared<float, Cf
         node_body<float, CfgT1>(P, sh, n);
 }
 
-// FP64: the nodes the FP32 pass handed over, looped over by a fixed grid
-// (also after a re-subdivision: these nodes are solved in full).  One
-// instantiation takes the nodes of up to kVmax struts (a wave per node), the
-// other the multi-wave class (a block of kBigWaves waves per node).
+// FP64: the nodes the FP32 pass handed over (also after a re-subdivision:
+// these nodes are solved in full), their lists drained by fixed grids.
 // At most 256 registers (VGPRs and AGPRs together): two waves per SIMD.
-template <typename C, bool SINK>
-__global__ void __launch_bounds__(C::W) __attribute__((amdgpu_waves_per_eu(2))) k_node64(Params P)
+__device__ inline List hand_list(const Params &P, int list, int large, int teams)
 {
-    __shared__ Shared<double, C> sh;
-    __shared__ int s_grab[4];
-    // the kernel's class: 0 one wave (v <= kVmax), 1 two waves (v <= kVmaxMid),
-    // 2 four waves; the launches run in that order
-    constexpr int cls = C::VM <= kVmax ? 0 : (C::VM <= kVmaxMid ? 1 : 2);
-    const int64_t N = P.in.n_nodes;
-    const List q{sched_ctr(P.w.sched, SCHED_FP64 + cls, 0), sched_ctr(P.w.sched, SCHED_HAND + (cls ? 1 : 0), 0), 0, 0};
+    return List{sched_ctr(P.w.sched, list, 0), sched_ctr(P.w.sched, SCHED_HAND + large, 0), 0, 0, teams};
+}
+
+// nodes of more than kVmax struts: CfgMid those of up to kVmaxMid, CfgBig the rest
+template <typename C, bool SINK>
+__device__ __forceinline__ void drain_large64(const Params &P, Shared<double, C> &sh, int *s_grab)
+{
+    constexpr bool MID = C::VM == kVmaxMid;
+    const List q = hand_list(P, SCHED_FP64 + (MID ? 1 : 2), 1, (int)gridDim.x);
     if (__ballot(sub_len(q, threadIdx.x & 63) != 0) == 0) return;
-    drain(q, blockIdx.x, s_grab, [&](int c, int i) {
-        const int64_t at = cls ? hand_base(N, c + 1) - 1 - i : hand_base(N, c) + i;
-        // an entry the two-wave kernel could not hold is stored negated
+    drain<true>(q, blockIdx.x, s_grab, [&](int c, int i) {
+        const int64_t at = hand_base(P.in.n_nodes, c + 1) - 1 - i;
+        // an entry the two-wave solve could not hold is stored negated
         // (~node): the four-wave kernel takes it whatever its valence
         const int32_t e = P.w.fb_list[at];
         const int64_t node = e < 0 ? ~e : e;
-        if constexpr (cls != 0) {
-            const int64_t v = P.w.row[node + 1] - P.w.row[node];
-            if ((e < 0 || v > kVmaxMid) != (cls == 2)) return;
-        }
+        const int64_t v = P.w.row[node + 1] - P.w.row[node];
+        if ((e >= 0 && v <= kVmaxMid) != MID) return;
         node_body<double, C, SINK>(P, sh, node);
-        if constexpr (cls == 1) {
+        if constexpr (MID) {
             __syncthreads();
             if (threadIdx.x == 0 && (sh.status & NS_CAPACITY)) P.w.fb_list[at] = ~(int32_t)node;
         }
     });
 }
 
-constexpr unsigned kFp64Grid = 2048;
-constexpr unsigned kFp64MidGrid = 1024;
+// Blocks of two waves: first nodes of kVmax + 1 .. kVmaxMid struts, one per
+// block; then those of up to kVmax, one per wave, each wave for itself.  The
+// few long solves start first and the others fill the chip beside them.  In
+// launches of their own, one after the other, k-NN 19^3 took 398 us per step
+// (its two solves of over 16 struts 50 us, alone on the chip) and 24 mixed
+// parts 2.21 ms; so 347 us and 2.17 ms.
+union SharedFp64 {
+    Shared<double, CfgMid> m;
+    Shared<double, CfgV16> w[2];
+};
+template <bool SINK>
+__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) k_node64(Params P)
+{
+    static_assert(CfgMid::W == 128 && CfgV16::W == 64, "two waves");
+    __shared__ SharedFp64 sh;
+    __shared__ int s_grab[4];
+    drain_large64<CfgMid, SINK>(P, sh.m, s_grab);  // (ends with a barrier)
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const List q = hand_list(P, SCHED_FP64, 0, 2 * (int)gridDim.x);
+    if (__ballot(sub_len(q, threadIdx.x & 63) != 0) == 0) return;
+    drain<false>(q, 2 * blockIdx.x + wave, nullptr, [&](int c, int i) {
+        const int64_t at = hand_base(P.in.n_nodes, c) + i;
+        node_body<double, CfgV16, SINK>(P, sh.w[wave], P.w.fb_list[at]);
+    });
+}
+
+// after it (it reads the other's marks): a block of kBigWaves waves per node
+template <bool SINK>
+__global__ void __launch_bounds__(CfgBig::W) __attribute__((amdgpu_waves_per_eu(2))) k_node64_big(Params P)
+{
+    __shared__ Shared<double, CfgBig> sh;
+    __shared__ int s_grab[4];
+    drain_large64<CfgBig, SINK>(P, sh, s_grab);
+}
+
+constexpr unsigned kFp64Grid = 1024;  // blocks of two waves
 constexpr unsigned kFp64BigGrid = 512;
 constexpr int64_t kBigGrid = 2048;  // blocks of a multi-wave class launch
 // waves of a one-wave-class launch: as many as the chip holds at once (256
@@ -2238,13 +2285,11 @@ hipError_t launch_node(const Inputs &in, const Work &w, int k, float kappa_max, 
     P.redo_cnt = redo_cnt;
     if (fp64) {
         if (sink) {
-            k_node64<CfgV16, true><<<kFp64Grid, 64, 0, st>>>(P);
-            k_node64<CfgMid, true><<<kFp64MidGrid, CfgMid::W, 0, st>>>(P);
-            k_node64<CfgBig, true><<<kFp64BigGrid, CfgBig::W, 0, st>>>(P);
+            k_node64<true><<<kFp64Grid, 128, 0, st>>>(P);
+            k_node64_big<true><<<kFp64BigGrid, CfgBig::W, 0, st>>>(P);
         } else {
-            k_node64<CfgV16, false><<<kFp64Grid, 64, 0, st>>>(P);
-            k_node64<CfgMid, false><<<kFp64MidGrid, CfgMid::W, 0, st>>>(P);
-            k_node64<CfgBig, false><<<kFp64BigGrid, CfgBig::W, 0, st>>>(P);
+            k_node64<false><<<kFp64Grid, 128, 0, st>>>(P);
+            k_node64_big<false><<<kFp64BigGrid, CfgBig::W, 0, st>>>(P);
         }
         return hipGetLastError();
     }
