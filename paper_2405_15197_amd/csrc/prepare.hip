@@ -84,15 +84,50 @@ __global__ void k_scatter(Inputs in, const int64_t *row, int32_t *cursor, int2 *
     if (kb >= 0) he[row[kb] + bb + rb.rank] = make_int2(ka, (int32_t)s);
 }
 
+// Half-edge i of strut s at node n, in the strut's two
+__device__ inline void put_half_edge(int64_t *strut_he, const int32_t *sa, const int32_t *sb, int32_t s, int64_t n,
+                                     int64_t i)
+{
+    const int32_t a = sa[s], c = sb[s];
+    const int64_t s2 = 2 * (int64_t)s;
+    if (a == c) {
+        strut_he[s2] = i;
+        strut_he[s2 + 1] = i;
+    } else {
+        strut_he[s2 + (n == (a < c ? a : c) ? 0 : 1)] = i;
+    }
+}
+
 // Incident struts of each node in increasing strut id (canonical labels
 // 1..v), then the half-edge index of every strut at its lower and higher
-// node id.
+// node id.  A lane per node; rows that its registers cannot hold but a wave
+// can are sorted by the wave, one after the other, each lane counting what
+// goes before its element.  (In memory, by one lane, the few such rows of
+// k-NN 19^3 took most of the kernel: 35 -> 12 us.)
 __global__ void k_sort_rows(int64_t n_nodes, const int64_t *row, int2 *he, int64_t *strut_he, const int32_t *sa,
                             const int32_t *sb)
 {
-    int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= n_nodes) return;
-    int64_t b = row[n], e = row[n + 1];
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    int64_t b = 0, e = 0;
+    if (n < n_nodes) {
+        b = row[n];
+        e = row[n + 1];
+    }
+    for (unsigned long long m = __ballot(e - b > kSortReg && e - b <= 64); m; m &= m - 1) {
+        const int r = __ffsll(m) - 1;
+        const int64_t rb = __shfl(b, r, 64);
+        const int v = __builtin_amdgcn_readlane((int)(e - b), r);
+        int2 x = make_int2(0, 0x7fffffff);
+        if (lane < v) x = he[rb + lane];
+        int rank = 0;
+        for (int i = 0; i < v; ++i) rank += __builtin_amdgcn_readlane(x.y, i) < x.y;
+        if (lane < v) {
+            he[rb + rank] = x;
+            put_half_edge(strut_he, sa, sb, x.y, n - lane + r, rb + rank);
+        }
+    }
+    if (n >= n_nodes || (e - b > kSortReg && e - b <= 64)) return;
     if (e - b <= kSortReg) {
         // in registers: bitonic network over kSortReg slots, empty slots last
         const int v = (int)(e - b);
@@ -153,17 +188,7 @@ __global__ void k_sort_rows(int64_t n_nodes, const int64_t *row, int2 *he, int64
             he[j + 1] = x;
         }
     }
-    for (int64_t i = b; i < e; ++i) {
-        int32_t s = he[i].y;
-        int32_t a = sa[s], c = sb[s];
-        int32_t lo = a < c ? a : c;
-        if (a == c) {
-            strut_he[2 * (int64_t)s] = i;
-            strut_he[2 * (int64_t)s + 1] = i;
-        } else {
-            strut_he[2 * (int64_t)s + (n == lo ? 0 : 1)] = i;
-        }
-    }
+    for (int64_t i = b; i < e; ++i) put_half_edge(strut_he, sa, sb, he[i].y, n, i);
 }
 
 // ---------------------------------------------------------------------------
@@ -300,19 +325,6 @@ __global__ void __launch_bounds__(kBlock) k_rows_tiles(int64_t N, int32_t *deg, 
 {
     static_assert(kClasses * 16 <= 64 && kTile < 65536, "class counts of a tile are 16-bit fields of one word");
     const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kScanItems;
-    int64_t total, start[kClasses], at = 0;
-    int64_t before = tiles_before(part, nb, blockIdx.x, &total);
-    if (blockIdx.x == 0 && threadIdx.x == 0) row[N] = total;
-#pragma unroll
-    for (int k = 0; k < kClasses; ++k) {
-        const int64_t b = tiles_before(part + (1 + k) * stride, nb, blockIdx.x, &total);
-        start[k] = at + b;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            cls_info[k] = total;
-            cls_info[kClasses + k] = at;
-        }
-        at += total;
-    }
     int32_t d[kScanItems];
     int64_t acc = 0;
     uint64_t cls = 0;
@@ -323,9 +335,25 @@ __global__ void __launch_bounds__(kBlock) k_rows_tiles(int64_t N, int32_t *deg, 
         acc += d[j];
         if (n < N) cls += 1ull << (16 * valence_class(d[j]));
     }
-    int64_t tot;
-    int64_t ex = before + block_excl_scan(acc, &tot);
-    uint64_t exc = (uint64_t)block_excl_scan((int64_t)cls, &tot);
+    // this tile's sums, and those of all (the same, of one tile: no sums are
+    // left by a launch before, then)
+    int64_t tile, tile_cls;
+    int64_t ex = block_excl_scan(acc, &tile);
+    uint64_t exc = (uint64_t)block_excl_scan((int64_t)cls, &tile_cls);
+    int64_t total = tile, start[kClasses], at = 0;
+    if (nb > 1) ex += tiles_before(part, nb, blockIdx.x, &total);
+    if (blockIdx.x == 0 && threadIdx.x == 0) row[N] = total;
+#pragma unroll
+    for (int k = 0; k < kClasses; ++k) {
+        total = (tile_cls >> (16 * k)) & 0xffff;
+        start[k] = at;
+        if (nb > 1) start[k] += tiles_before(part + (1 + k) * stride, nb, blockIdx.x, &total);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            cls_info[k] = total;
+            cls_info[kClasses + k] = at;
+        }
+        at += total;
+    }
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         const int64_t n = base + j;
@@ -614,7 +642,7 @@ hipError_t launch_prepare(const Inputs &in, const Work &w, hipStream_t st)
     // (at least one block: it clears the flags)
     k_pack<<<grid_for(N > 0 ? N : 1, kBlock), kBlock, 0, st>>>(in, w.node4, w.deg, w.flags);
     if (S > 0) k_degree<<<grid_for(S, kBlock), kBlock, 0, st>>>(in, w.deg, w.flags);
-    k_rows_reduce<<<(unsigned)nb, kBlock, 0, st>>>(N, w.deg, w.scan_tmp, stride);
+    if (nb > 1) k_rows_reduce<<<(unsigned)nb, kBlock, 0, st>>>(N, w.deg, w.scan_tmp, stride);
     if (nb > kFew) k_scan_tile_sums<<<kRowCols, kBlock, 0, st>>>(w.scan_tmp, nb, stride);
     k_rows_tiles<<<(unsigned)nb, kBlock, 0, st>>>(N, w.deg, w.scan_tmp, nb, stride, w.row, w.queue, w.cls_info);
     if (S > 0) k_scatter<<<grid_for(S, kBlock), kBlock, 0, st>>>(in, w.row, w.deg, w.he);
