@@ -405,20 +405,42 @@ __global__ void __launch_bounds__(kBlock) k_sizes_reduce(SizesParams P)
         }
         return;
     }
+    // all struts' loads of one kind at once: a chain of them per strut is what
+    // takes the time (k-NN 19^3 16 -> 12 us)
     const int64_t b = blockIdx.x - P.nbn, base = b * kTile;
+    int32_t u[kScanItems], v[kScanItems], c[kScanItems];
+    int64_t h0[kScanItems], h1[kScanItems];
+    bool ok[kScanItems];
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        const int64_t s = base + (int64_t)j * kBlock + threadIdx.x;
+        u[j] = v[j] = -1;
+        h0[j] = h1[j] = 0;
+        if (s >= S) continue;
+        u[j] = P.in.sa[s];
+        v[j] = P.in.sb[s];
+        h0[j] = W.strut_he[2 * s];
+        h1[j] = W.strut_he[2 * s + 1];
+    }
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        ok[j] = u[j] != v[j] && (uint64_t)(int64_t)u[j] < (uint64_t)N && (uint64_t)(int64_t)v[j] < (uint64_t)N;
+        if (ok[j]) {
+            u[j] = status[u[j]];
+            v[j] = status[v[j]];
+            c[j] = W.he_len[h0[j]];
+            h1[j] = W.he_len[h1[j]];
+        }
+    }
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         const int64_t s = base + (int64_t)j * kBlock + threadIdx.x;
         if (s >= S) continue;
-        const int32_t u = P.in.sa[s], v = P.in.sb[s];
-        int32_t c = 0;
-        if (u != v && (uint64_t)(int64_t)u < (uint64_t)N && (uint64_t)(int64_t)v < (uint64_t)N && status[u] == 0 &&
-            status[v] == 0)
-            c = W.he_len[W.strut_he[2 * s]] + W.he_len[W.strut_he[2 * s + 1]];
-        else
-            ++x[1];
-        x[0] += c;
-        W.band_cnt[s] = c;
+        ok[j] = ok[j] && u[j] == 0 && v[j] == 0;
+        c[j] = ok[j] ? c[j] + (int32_t)h1[j] : 0;
+        x[1] += !ok[j];
+        x[0] += c[j];
+        W.band_cnt[s] = c[j];
     }
     block_sums(x);
     if (threadIdx.x == 0) {
