@@ -1949,20 +1949,20 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
 // sink mode (end loops kept, vertices and fans hashed).
 enum { kModeMesh = 0, kModeRetri = 1, kModeRedo = 2, kModeSink = 3 };
 
-// Work distribution: a list in kSub sub-lists, each with its counter.  Block b
-// belongs to sub-list b mod kSub.  Its first range is given (no counter: a
-// list no longer than the grid takes no atomic at all), then it takes ranges
+// Work distribution: a list in kSub sub-lists, each with its counter, drained
+// by teams (waves or blocks), team b starting on sub-list b mod kSub.  A list
+// of nodes that makes few rounds over the teams is given out whole, without a
+// counter.  Of longer ones the first range is given, then a team takes ranges
 // by guided self-scheduling, half of what its last grab saw left over its
-// sub-list's blocks, at least one and at most kGrabMax.  When its own is used
+// sub-list's teams, at least one and at most kGrabMax.  When its own is used
 // up it helps with the others, which it finds by reading all counters at once.
 // With one counter for the list, every block's first grab, every further one
 // and a last, futile one stood in line for it: a pass over some 10^4 nodes was
 // bound by that: the launch for the 7.8 k nodes of 12 struts of octet 13^3
 // 163 -> 105 us, k-NN 19^3 (6.9 k nodes, most of them handed to FP64 through
 // one more counter) 677 -> 448 us per step, 24 mixed parts 2.78 -> 2.26 ms.
-// Every block reaches the end: a grab that fails has found its counter past
+// Every team reaches the end: a grab that fails has found its counter past
 // its sub-list's end, and counters only grow.
-// Block-uniform; every thread of the block calls it.
 constexpr int kGrabMax = 16;
 __device__ inline int lane_value(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
 
@@ -1994,8 +1994,19 @@ __device__ inline int64_t dealt_item(int t, int c, int i)
     return ((((int64_t)(i >> t) * kSub) + c) << t) + (i & ((1 << t) - 1));
 }
 
-// items of a first range, and of those of all teams l, l + kSub, ..., which
-// start on sub-list l of n items
+// A grab waits for the record that the team has just written, and the last
+// items grabbed end when most of the chip is idle already: together about one
+// solve's time, 30 us, whatever the list's length.  Against that stand the
+// differences between nodes.  Taken as grabbed -> given: cubic 20^3 (1.1
+// rounds) 105 -> 78 us, octet 13^3 step 251 -> 212, bcc 28^3 (5.7) 366 -> 327,
+// bcc 36^3 (12) 667 -> 626, k-NN 32^3 and 48^3 of 9, nodes of all valences,
+// 769 -> 750 and 2328 -> 2330; bcc 64^3 (64) would lose, 3.29 -> 3.41 ms.
+constexpr int kGivenRounds = 16;
+__device__ inline bool given(const List &q) { return !q.hand && q.items <= kGivenRounds * q.teams; }
+// teams that start on sub-list l: l, l + kSub, ...
+__device__ inline int teams_on(const List &q, int l) { return (q.teams - l + kSub - 1) / kSub; }
+// items of a first range, and of those of all teams that start on sub-list l
+// of n items
 __device__ inline int first_range(const List &q, int n)
 {
     const int g = n / (2 * ((q.teams + kSub - 1) / kSub));
@@ -2003,20 +2014,21 @@ __device__ inline int first_range(const List &q, int n)
 }
 __device__ inline int first_ranges(const List &q, int n, int l)
 {
-    return l < kSub ? first_range(q, n) * ((q.teams - l + kSub - 1) / kSub) : 0;
+    return given(q) ? n : (l < kSub ? first_range(q, n) * teams_on(q, l) : 0);
 }
 
 struct Grab {
     int c, seen;     // the sub-list worked on (-1: the list is used up), and what of it the last grab saw taken
-    int first, end;  // the range
+    int first, end, step;  // the range: first, first + step, ...
 };
 
 // the team's first range; b: its rank
 __device__ inline Grab grab_first(const List &q, unsigned b)
 {
     const int c = (int)(b % kSub), n = lane_value(sub_len(q, threadIdx.x & 63), c), g = first_range(q, n);
+    if (given(q)) return Grab{c, n, (int)(b / kSub), n, teams_on(q, c)};
     const int first = (int)(b / kSub) * g;
-    return Grab{c, first_ranges(q, n, c), first, first + g < n ? first + g : n};
+    return Grab{c, first_ranges(q, n, c), first, first + g < n ? first + g : n, 1};
 }
 
 // The next range, by one wave.  A function of its own: few calls per block,
@@ -2034,14 +2046,14 @@ __device__ __attribute__((noinline)) Grab grab_more(List q, int c, int seen)
             if (lane == 0) v = atomicAdd(q.ctr + c * kSchedLine, g);
             const int first = lane_value(pre, c) + __builtin_amdgcn_readfirstlane(v);
             seen = first + g;
-            if (first < n) return Grab{c, seen, first, seen < n ? seen : n};
+            if (first < n) return Grab{c, seen, first, seen < n ? seen : n, 1};
         }
         // what is left of every sub-list: none, where first ranges were all
         int left = mine - pre;
         if (left > 0)
             left -= __hip_atomic_load(q.ctr + lane * kSchedLine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned long long m = __ballot(left > 0);
-        if (m == 0) return Grab{-1, 0, 0, 0};
+        if (m == 0) return Grab{-1, 0, 0, 0, 1};
         const unsigned long long after = m & ~((2ull << c) - 1);
         c = __builtin_ctzll(after ? after : m);
         seen = lane_value(mine, c) - lane_value(left, c);
@@ -2056,10 +2068,11 @@ __device__ __forceinline__ void drain(const List &q, unsigned b, int *s_grab, F 
 {
     Grab G = grab_first(q, b);
     for (;;) {
-        for (int i = G.first; i < G.end; ++i) {
+        for (int i = G.first; i < G.end; i += G.step) {
             f(G.c, i);
             group_sync<BLOCK ? 128 : 64>();
         }
+        if (given(q)) return;
         if constexpr (!BLOCK) {
             G = grab_more(q, __builtin_amdgcn_readfirstlane(G.c), __builtin_amdgcn_readfirstlane(G.seen));
         } else {
@@ -2073,7 +2086,7 @@ __device__ __forceinline__ void drain(const List &q, unsigned b, int *s_grab, F 
                 }
             }
             __syncthreads();
-            G = Grab{s_grab[0], s_grab[1], s_grab[2], s_grab[3]};
+            G = Grab{s_grab[0], s_grab[1], s_grab[2], s_grab[3], 1};
             __syncthreads();
         }
         G.c = __builtin_amdgcn_readfirstlane(G.c);

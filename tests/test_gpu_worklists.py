@@ -82,3 +82,9 @@ def test_fp64_nodes_in_one_sub_list(n):
     t = check(part, n, 16 - part.n_nodes, 8, None)
     print(n, t, flush=True)
     assert t["n_fp64_nodes"] >= n
+
+
+@pytest.mark.parametrize("n", [65536, 65537])
+def test_longest_list_given_out_whole_and_shortest_grabbed(n):
+    # sixteen rounds over the 4,096 waves of a launch, and one node more
+    check(fan(9), n, 0, 3, None)
