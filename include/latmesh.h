@@ -328,8 +328,8 @@ int lm_forward_sink(lm_plan *plan, int k, int64_t chunk_nodes, uint64_t *d_out, 
  * chunk, every device buffer (adjacency, node lists, hash slots, node records)
  * carved from a fixed array that the library holds in device memory,
  * LM_STATIC_SCRATCH_BYTES on each GPU it runs on, kept until the process ends.
- * Nothing is allocated, on the device or the host.  The BCC lattice of 24^3
- * cells (29,449 nodes, 110,592 struts) at k = 16 needs 108 MiB;
+ * Nothing is allocated, on the device or the host.  The BCC lattice of 22^3
+ * cells (22,815 nodes, 85,184 struts) at k = 16 needs 106 MiB;
  * lm_static_scratch_size gives the exact need of a lattice. */
 #define LM_STATIC_SCRATCH_BYTES ((size_t)128 << 20)
 

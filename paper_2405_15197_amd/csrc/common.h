@@ -358,8 +358,8 @@ hipError_t launch_clear(const ClearRuns &r, hipStream_t st);
 // src_rec (src_node_rec) and only re-subdivided at resolution k.
 // src_rec / src_node_rec set: re-subdivision of the meta-mesh in those
 // records; nodes that must be solved in full go to redo ([N], partitioned
-// like the queue) with counts and work counters in redo_cnt [8], zeroed by
-// the caller.
+// like the queue) with their counts in redo_cnt [kClasses], zeroed by the
+// caller.
 // Thread-centric ablation of the FP32 node pass (one lane per node, node id
 // order, per-node scratch of node_thread_scratch_bytes() in global memory).
 size_t node_thread_scratch_bytes();

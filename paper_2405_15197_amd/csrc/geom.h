@@ -1,6 +1,5 @@
 // Node-local geometry shared by the meta-meshing and adjoint kernels:
-// scalar helpers over float / double (and the adjoint's dual numbers),
-// 3-vectors, the strut table of a node and its seam conics (Sec. 4.1,
+// scalar helpers over float / double, 3-vectors, the strut table of a node and its seam conics (Sec. 4.1,
 // Sec. 4.3.1, Eq. 7).  Not installed.
 #pragma once
 

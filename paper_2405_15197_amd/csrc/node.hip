@@ -1942,8 +1942,7 @@ __device__ __forceinline__ void node_retri(const Params &P, Shared<float, CF> &s
 }
 
 // FP32, one valence class: a persistent loop takes items of 64 / W queued
-// nodes from the class's work counter; every wave leaves once the counter has
-// passed the class's last item.  MODE 0: meta-meshing of the queue; 1:
+// nodes from the class's list (work distribution: below).  MODE 0: meta-meshing of the queue; 1:
 // re-subdivision of the queue; 2: meta-meshing of the redo list that mode 1
 // left (its length is read on the device); 3: meta-meshing of the queue in
 // sink mode (end loops kept, vertices and fans hashed).
@@ -2156,7 +2155,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_
 }
 
 // The multi-wave class: one node per block of kBigWaves waves, items from the
-// class's work counter as above.  Re-subdivision does not read these nodes'
+// class's list as above.  Re-subdivision does not read these nodes'
 // records: they are queued for a full solve (MODE 1), which MODE 2 runs.
 template <int MODE>
 __global__ void __launch_bounds__(64 * kBigWaves) __attribute__((amdgpu_waves_per_eu(4))) k_node32_big(Params P)
