@@ -464,25 +464,44 @@ __global__ void __launch_bounds__(kBlock) k_sizes_tiles(SizesParams P)
         int64_t *dst = nodes ? W.node_off + col * (N + 1) : W.band_off;
         int64_t *dst2 = nodes ? P.out.node_off : P.out.strut_off;
         if (nodes && dst2) dst2 += col * (N + 1);
-        const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kScanItems;
+        // Through LDS, so that neighbouring lanes load and store neighbouring
+        // elements while each thread sums eight in a row (BCC 64^3: 56 -> 21
+        // us).  A tile's sum fits 32 bits: at most kAcapBig = 192 arcs of 4,096
+        // segments at either end of each of its 2,048 struts, 3.2e9.
+        __shared__ uint32_t s_v[kTile + kTile / kScanItems];
+        auto slot = [](int i) { return i + i / kScanItems; };
+        const int64_t base = (int64_t)blockIdx.x * kTile;
         int64_t total;
         const int64_t before = tiles_before(part, nb, blockIdx.x, &total);
-        int32_t v[kScanItems];
-        int64_t acc = 0;
 #pragma unroll
         for (int j = 0; j < kScanItems; ++j) {
-            v[j] = base + j < n ? src[base + j] : 0;
+            const int i = j * kBlock + (int)threadIdx.x;
+            s_v[slot(i)] = base + i < n ? (uint32_t)src[base + i] : 0u;
+        }
+        __syncthreads();
+        uint32_t v[kScanItems];
+        uint32_t acc = 0;
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) {
+            v[j] = s_v[slot((int)threadIdx.x * kScanItems + j)];
             acc += v[j];
         }
         int64_t tot;
-        int64_t ex = before + block_excl_scan(acc, &tot);
+        uint32_t ex = (uint32_t)block_excl_scan((int64_t)acc, &tot);
 #pragma unroll
         for (int j = 0; j < kScanItems; ++j) {
-            if (base + j < n) {
-                dst[base + j] = ex;
-                if (dst2) dst2[base + j] = ex;
-            }
+            s_v[slot((int)threadIdx.x * kScanItems + j)] = ex;
             ex += v[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) {
+            const int i = j * kBlock + (int)threadIdx.x;
+            if (base + i < n) {
+                const int64_t x = before + s_v[slot(i)];
+                dst[base + i] = x;
+                if (dst2) dst2[base + i] = x;
+            }
         }
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             dst[n] = total;
