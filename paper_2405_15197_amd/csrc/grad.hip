@@ -963,12 +963,35 @@ __global__ void k_grad_gather(BParams P)
     }
     if (W.node_rec[n] >= 0)
         for (int d = 0; d < 4; ++d) g[d] = W.grad_node[4 * n + d];
-    for (int64_t h = W.row[n]; h < W.row[n + 1]; ++h) {
-        const int2 he = W.he[h];
-        if (W.node_rec[he.x] < 0) continue;
-        const int64_t h0 = W.strut_he[2 * (int64_t)he.y], h1 = W.strut_he[2 * (int64_t)he.y + 1];
-        const int64_t tw = h0 == h ? h1 : h0;
-        for (int d = 0; d < 4; ++d) g[d] += W.grad_he[4 * tw + d];
+    // four half-edges' loads of one kind at once: a chain of three per half-edge
+    // is what takes the time (octet 32^3: 40 -> 29 us)
+    constexpr int K = 4;
+    const int64_t end = W.row[n + 1];
+    for (int64_t h = W.row[n]; h < end; h += K) {
+        int2 he[K];
+        int64_t rec[K], tw[K];
+        float4 d[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) he[i] = W.he[h + i < end ? h + i : h];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            rec[i] = W.node_rec[he[i].x];
+            const int64_t h0 = W.strut_he[2 * (int64_t)he[i].y], h1 = W.strut_he[2 * (int64_t)he[i].y + 1];
+            tw[i] = h0 == h + i ? h1 : h0;
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const float *q = W.grad_he + 4 * tw[i];
+            d[i] = make_float4(q[0], q[1], q[2], q[3]);
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (h + i >= end || rec[i] < 0) continue;
+            g[0] += d[i].x;
+            g[1] += d[i].y;
+            g[2] += d[i].z;
+            g[3] += d[i].w;
+        }
     }
     P.grad_xyz[3 * n] = g[0];
     P.grad_xyz[3 * n + 1] = g[1];
