@@ -423,7 +423,13 @@ int lm_loss(lm_plan *plan, const lm_outputs *out, const lm_loss_weights *w, doub
  * Asynchronous. */
 int lm_backward(lm_plan *plan, const float *d_dl_dx, float *d_grad_xyz, float *d_grad_radius);
 
-/* Release the plan and its workspace (synchronises its stream). */
+/* Release the plan and its workspace.  Synchronises its stream and, where
+ * the plan allocated its own device memory, waits for all work on the device,
+ * since a graph that captured the plan's calls may still be running on another
+ * stream (like hipFree, not to be called while a stream is being captured).
+ * Such memory is kept for the next plans, at most 256 MiB in at most 16
+ * pieces, each until 64 further ones were asked for or returned or an
+ * allocation of the library fails. */
 void lm_plan_destroy(lm_plan *plan);
 
 /* Text for an LM_OK / LM_ERR_* code (static storage). */

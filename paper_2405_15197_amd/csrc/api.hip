@@ -119,11 +119,13 @@ struct PhaseTimer {
 // Device memory of finished plans, kept for the next ones: hipMalloc and
 // hipFree map and unmap memory and wait for the device (a new plan for BCC 21^3,
 // sized, meshed and given back, spent most of its 0.8 ms in four of them, and
-// now and then twice that).  A piece enters when its owner's stream has been
-// waited for, so whoever takes it may use it at once on any stream; it goes
-// back to the system when the pieces together would exceed kKeepBytes or
-// kKeepPieces, when kKeepCalls further ones were asked for or returned, or when
-// an allocation fails.  One lock for all threads; never throws.
+// now and then twice that).  A piece enters when its device has been waited
+// for, as hipFree would have done, so whoever takes it may use it at once on
+// any stream, also where another stream replayed a captured pass of its former
+// owner; it goes back to the system when the pieces together would exceed
+// kKeepBytes or kKeepPieces, when kKeepCalls further ones were asked for or
+// returned, or when an allocation of the library fails.  One lock for all
+// threads; never throws.
 constexpr size_t kKeepBytes = (size_t)256 << 20;
 constexpr int kKeepPieces = 16;
 constexpr uint64_t kKeepCalls = 64;
@@ -164,6 +166,18 @@ struct MemKeep {
     }
 };
 MemKeep g_keep;
+
+// Waits for all work on device dev, whatever stream it is on; false when that
+// failed.
+bool device_idle(int dev)
+{
+    int cur = -1;
+    if (dev < 0 || hipGetDevice(&cur) != hipSuccess) return false;
+    const bool ok = (cur == dev || hipSetDevice(dev) == hipSuccess) && hipDeviceSynchronize() == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    if (cur != dev) (void)hipSetDevice(cur);
+    return ok;
+}
 
 void mem_release(const DevMem *m, int n)
 {
@@ -209,7 +223,7 @@ bool mem_alloc(DevMem *m, size_t n)
     return true;
 }
 
-// idle: the stream that used the memory has been waited for
+// idle: nothing on the memory's device can still use it
 void mem_free(DevMem *m, bool idle)
 {
     if (!m->p) return;
@@ -452,7 +466,7 @@ int ensure_rec(lm_plan *P, int64_t words)
     if (words <= P->w.rec_words) return LM_OK;
     if (P->caller_ws) return LM_ERR_CAPACITY;
     HIPCHK(hipStreamSynchronize(P->st));
-    mem_free(&P->rec_mem, true);
+    mem_free(&P->rec_mem, device_idle(P->rec_mem.dev));
     P->w.rec = nullptr;
     P->w.rec_words = 0;
     if (!mem_alloc(&P->rec_mem, sizeof(uint32_t) * (size_t)words)) return LM_ERR_HIP;
@@ -650,7 +664,7 @@ int lm_plan_create(lm_plan **plan, const lm_lattice *lat, void *stream)
     carve_fixed(P, c, lat->n_nodes, lat->n_struts);
     carve_sched(P, c);
     if ((rc = first_prepare(P))) {
-        mem_free(&P->ws, rc != LM_ERR_HIP);
+        mem_free(&P->ws, rc != LM_ERR_HIP);  // (nobody else has seen it)
         delete P;
         return rc;
     }
@@ -841,7 +855,7 @@ int batch_alloc(lm_plan *P, int64_t n_parts)
     }
     if (n_parts > P->bt_cap) {
         HIPCHK(hipStreamSynchronize(P->st));
-        mem_free(&P->batch_parts_mem, true);
+        mem_free(&P->batch_parts_mem, device_idle(P->batch_parts_mem.dev));
         P->bt_cap = 0;
         Carver c0(nullptr);
         carve_batch_parts(P, c0, n_parts);
@@ -1087,7 +1101,7 @@ int lm_retriangulate(lm_plan *P, int k, const lm_outputs *out)
     if (base_in_w) {
         if (need > P->alt_rec_words && !P->caller_ws) {
             HIPCHK(hipStreamSynchronize(P->st));
-            mem_free(&P->alt_rec_mem, true);
+            mem_free(&P->alt_rec_mem, device_idle(P->alt_rec_mem.dev));
             P->alt_rec = nullptr;
             P->alt_rec_words = 0;
             if (!mem_alloc(&P->alt_rec_mem, sizeof(uint32_t) * (size_t)need)) return LM_ERR_HIP;
@@ -1224,16 +1238,19 @@ int lm_set_precision(lm_plan *P, float kappa_max)
 void lm_plan_destroy(lm_plan *P)
 {
     if (!P) return;
-    const bool idle = hipStreamSynchronize(P->st) == hipSuccess;
+    (void)hipStreamSynchronize(P->st);
     for (auto &e : P->ev) {
         (void)hipEventDestroy(e.second.first);
         (void)hipEventDestroy(e.second.second);
     }
     for (auto e : P->pool) (void)hipEventDestroy(e);
     // (all empty in a plan on a caller-owned workspace)
+    int waited = -1;
     for (DevMem *m : {&P->ws, &P->rec_mem, &P->alt_rec_mem, &P->sink_mem, &P->batch_mem, &P->batch_parts_mem,
-                      &P->alt_index_mem, &P->grad_mem, &P->thread_scratch})
-        mem_free(m, idle);
+                      &P->alt_index_mem, &P->grad_mem, &P->thread_scratch}) {
+        if (m->p && m->dev != waited && device_idle(m->dev)) waited = m->dev;
+        mem_free(m, m->dev == waited);
+    }
     delete P;
 }
 
