@@ -432,6 +432,11 @@ int lm_backward(lm_plan *plan, const float *d_dl_dx, float *d_grad_xyz, float *d
  * allocation of the library fails. */
 void lm_plan_destroy(lm_plan *plan);
 
+/* Give the device memory kept from destroyed plans back to the system: for a
+ * program that has no more plans to make, that needs the memory elsewhere, or
+ * that is about to reset the device.  Live plans are not affected. */
+void lm_release_memory(void);
+
 /* Text for an LM_OK / LM_ERR_* code (static storage). */
 const char *lm_status_string(int code);
 

@@ -124,8 +124,8 @@ struct PhaseTimer {
 // any stream, also where another stream replayed a captured pass of its former
 // owner; it goes back to the system when the pieces together would exceed
 // kKeepBytes or kKeepPieces, when kKeepCalls further ones were asked for or
-// returned, or when an allocation of the library fails.  One lock for all
-// threads; never throws.
+// returned, when an allocation of the library fails, or when
+// lm_release_memory is called.  One lock for all threads; never throws.
 constexpr size_t kKeepBytes = (size_t)256 << 20;
 constexpr int kKeepPieces = 16;
 constexpr uint64_t kKeepCalls = 64;
@@ -1252,6 +1252,17 @@ void lm_plan_destroy(lm_plan *P)
         mem_free(m, m->dev == waited);
     }
     delete P;
+}
+
+void lm_release_memory(void)
+{
+    DevMem old[kKeepPieces];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_keep.mu);
+        n = g_keep.expire(old, 0, 0);
+    }
+    mem_release(old, n);
 }
 
 const char *lm_status_string(int code)

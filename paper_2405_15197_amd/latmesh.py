@@ -65,6 +65,7 @@ EXPORTS = (
     "lm_arc_encode",
     "lm_arc_decode",
     "lm_plan_destroy",
+    "lm_release_memory",
     "lm_status_string",
 )
 
@@ -252,6 +253,8 @@ def load() -> ctypes.CDLL:
     lib.lm_arc_decode.restype = ctypes.c_int
     lib.lm_plan_destroy.argtypes = [P]
     lib.lm_plan_destroy.restype = None
+    lib.lm_release_memory.argtypes = []
+    lib.lm_release_memory.restype = None
     lib.lm_status_string.argtypes = [ctypes.c_int]
     lib.lm_status_string.restype = ctypes.c_char_p
     _lib = lib
@@ -466,6 +469,11 @@ def lm_set_precision(plan, kappa_max: float) -> None:
 
 def lm_plan_destroy(plan) -> None:
     load().lm_plan_destroy(plan)
+
+
+def lm_release_memory() -> None:
+    """Give the device memory kept from destroyed plans back to the system."""
+    load().lm_release_memory()
 
 
 # ---- torch helper ----------------------------------------------------------

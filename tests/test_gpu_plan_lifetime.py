@@ -1,11 +1,13 @@
 """When device memory of a plan may serve the next one: after all work on the
-device, on every stream."""
+device, on every stream, and back to the system when asked for."""
 
 import pytest
 
 import latgen
 
 pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
 
 
 def _lattice(n=8):
@@ -51,3 +53,32 @@ def test_memory_is_given_up_only_after_work_on_other_streams(how):
     finally:
         torch.cuda.synchronize()
         m.close()
+
+
+def test_kept_memory_is_released_on_request():
+    import torch
+
+    from paper_2405_15197_amd import Mesher, latmesh
+
+    def free():
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        return torch.cuda.mem_get_info()[0]
+
+    live = Mesher(_lattice(6))
+    want = live.count(12)
+    latmesh.lm_release_memory()
+    before = free()
+    plans = [Mesher(_lattice(24)) for _ in range(3)]
+    for m in plans:
+        m.count(16)
+    used = before - free()
+    for m in plans:
+        m.close()
+    del plans
+    latmesh.lm_release_memory()
+    assert used > 128 * MIB
+    assert before - free() <= 8 * MIB  # the runtime's own
+    latmesh.lm_release_memory()  # nothing left: no effect
+    assert live.count(12) == want
+    live.close()
