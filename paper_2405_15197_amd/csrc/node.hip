@@ -1562,8 +1562,11 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     if (nm[e] != kNoName) {
-                        const V3<T> w = conic_dir(arc_con(sh.A[j]), e ? en.es : en.ss, e ? en.ec : en.sc);
                         const int at = vbase + rank[e];
+                        // the rank counts the conic's pieces of rounds to come
+                        // (too many vertices, then: flagged below)
+                        if (!ONE && at >= CF::VC) continue;
+                        const V3<T> w = conic_dir(arc_con(sh.A[j]), e ? en.es : en.ss, e ? en.ec : en.sc);
                         sh.vname[at] = nm[e];
                         sh.vx[at] = w.x;
                         sh.vy[at] = w.y;
