@@ -52,7 +52,9 @@ __device__ inline void add3(float *p, float3 v, float s)
 //
 // A band lists the triangles of the edges of one end loop, then those of the
 // other, each in loop order; an edge triangle's apex is on the other loop.
-// So the wave adds without LDS atomics, in three steps of distinct addresses:
+// So the wave adds without LDS atomics, in steps of distinct addresses with a
+// barrier after each (of no cost in a block of one wave, and what orders a
+// lane's reads after the others' writes):
 // the edges of the node's own loop add their first ends, then their second
 // ends, and the other loop's edges, whose apexes on this one come in runs of
 // neighbouring lanes, add each run's sum.  (With an atomic per corner and
@@ -212,6 +214,7 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
                 add_any(T.i2, corner(T, T.a, T.b));
             }
         }
+        __syncthreads();
         // bands of the incident struts (terms at the lower end)
         for (int h = 0; h < v; ++h) {
             const int64_t b0 = ((int64_t)__builtin_amdgcn_readlane((int)(my_b0 >> 32), h) << 32) |
