@@ -596,7 +596,7 @@ int check_options(const lm_options *opt, lm_options *o)
     d.record_bytes = 0;
     d.max_parts = 0;
     *o = opt ? *opt : d;
-    if (o->k_max < 3 || o->k_max > 4096 || o->record_bytes < 0 || o->max_parts < 0 ||
+    if (o->k_max < 3 || o->k_max > lm::kMaxK || o->record_bytes < 0 || o->max_parts < 0 ||
         (o->flags & ~(LM_WS_SINK | LM_WS_GRADIENT | LM_WS_RETRI)))
         return LM_ERR_INVALID_ARG;
     return LM_OK;
@@ -718,7 +718,7 @@ int lm_end_radius_gradient(lm_plan *P, const float *d_grad_radius, float *d_grad
 
 int lm_count(lm_plan *P, int k, lm_totals *totals)
 {
-    if (!P || !totals || k < 3 || k > 4096) return LM_ERR_INVALID_ARG;
+    if (!P || !totals || k < 3 || k > lm::kMaxK) return LM_ERR_INVALID_ARG;
     int rc = LM_OK;
     if (P->w.rec_words == 0 && (rc = ensure_rec(P, rec_estimate(P, k)))) return rc;
     int32_t fl = 0;
@@ -756,7 +756,7 @@ int lm_fill(lm_plan *P, const lm_outputs *out)
 
 int lm_forward(lm_plan *P, int k, const lm_outputs *out)
 {
-    if (!P || !out || !out->d_mesh_xyz || !out->d_tri || k < 3 || k > 4096) return LM_ERR_INVALID_ARG;
+    if (!P || !out || !out->d_mesh_xyz || !out->d_tri || k < 3 || k > lm::kMaxK) return LM_ERR_INVALID_ARG;
     lm::FillOut f = to_fill(out);
     int rc = LM_OK;
     if (P->w.rec_words == 0 && (rc = ensure_rec(P, rec_estimate(P, k)))) return rc;
@@ -978,7 +978,7 @@ extern "C" {
 
 int lm_forward_sink(lm_plan *P, int k, int64_t chunk_nodes, uint64_t *d_out, int64_t n_chunks_cap)
 {
-    if (!P || !d_out || k < 3 || k > 4096 || chunk_nodes < 1) return LM_ERR_INVALID_ARG;
+    if (!P || !d_out || k < 3 || k > lm::kMaxK || chunk_nodes < 1) return LM_ERR_INVALID_ARG;
     const int64_t N = P->in.n_nodes;
     const int64_t nch = (N + chunk_nodes - 1) / chunk_nodes;
     if (nch > n_chunks_cap) return LM_ERR_CAPACITY;
@@ -1004,7 +1004,7 @@ int lm_batched(lm_plan *P, int64_t n_parts, const int64_t *part_off, const int32
     const int64_t N = P->in.n_nodes;
     if (part_off[0] != 0 || part_off[n_parts] != N) return LM_ERR_INVALID_ARG;
     for (int64_t p = 0; p < n_parts; ++p)
-        if (part_off[p + 1] < part_off[p] || part_k[p] < 3 || part_k[p] > 4096) return LM_ERR_INVALID_ARG;
+        if (part_off[p + 1] < part_off[p] || part_k[p] < 3 || part_k[p] > lm::kMaxK) return LM_ERR_INVALID_ARG;
     int t16 = 4, t32 = 8;
     int64_t group = 0;
     if (tune) {
@@ -1071,7 +1071,7 @@ int lm_batched(lm_plan *P, int64_t n_parts, const int64_t *part_off, const int32
 
 int lm_retriangulate(lm_plan *P, int k, const lm_outputs *out)
 {
-    if (!P || !out || !out->d_mesh_xyz || !out->d_tri || k < 3 || k > 4096) return LM_ERR_INVALID_ARG;
+    if (!P || !out || !out->d_mesh_xyz || !out->d_tri || k < 3 || k > lm::kMaxK) return LM_ERR_INVALID_ARG;
     if (P->k == 0) return LM_ERR_STATE;  // no meta-mesh from lm_count / lm_forward
     if (P->caller_ws && !(P->ws_flags & LM_WS_RETRI)) return LM_ERR_UNSUPPORTED;
     const int64_t N = P->in.n_nodes;
@@ -1327,7 +1327,7 @@ extern "C" {
 
 int lm_static_scratch_size(int64_t n_nodes, int64_t n_struts, int k, size_t *bytes)
 {
-    if (!bytes || k < 3 || k > 4096) return LM_ERR_INVALID_ARG;
+    if (!bytes || k < 3 || k > lm::kMaxK) return LM_ERR_INVALID_ARG;
     lm_options o;
     o.flags = LM_WS_SINK;
     o.k_max = k;
@@ -1342,7 +1342,7 @@ int lm_static_scratch_size(int64_t n_nodes, int64_t n_struts, int k, size_t *byt
 
 int lm_forward_sink_static(const lm_lattice *lat, int k, uint64_t *d_words, void *stream)
 {
-    if (!d_words || k < 3 || k > 4096) return LM_ERR_INVALID_ARG;
+    if (!d_words || k < 3 || k > lm::kMaxK) return LM_ERR_INVALID_ARG;
     int rc = check_lattice(lat);
     if (rc) return rc;
     size_t need = 0;

@@ -30,6 +30,7 @@ constexpr int kVmaxMid = 32;
 constexpr int kAcapMid = 96;
 constexpr int kVcapMid = 64;
 constexpr int kPieces = 4;      // kept arcs per conic
+constexpr int kMaxK = 4096;     // highest resolution: segments of a full turn
 
 constexpr float kTwoPi = 6.28318530717958647692f;
 constexpr float kInvTwoPi = 0.159154943091895335769f;

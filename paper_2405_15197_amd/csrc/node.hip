@@ -55,12 +55,13 @@ struct ArcL {
     T dt;            // t2 - t1, kept with its own relative precision
     uint32_t ns, ne; // vertex names at t1 / t2
     int mbase, fbase;
-    uint16_t nseg;       // at most k <= 4096
+    uint16_t nseg;       // at most kMaxK
     uint8_t vs, ve;      // local vertex indices
     uint8_t p, q, full;
     uint8_t contour;     // kNone: not on a hole
 };
 constexpr int kNone = 255;  // above every vertex and contour index
+static_assert(kMaxK < 65536 && kVcapBig < kNone && kAcapBig < kNone, "the narrow fields of ArcL");
 
 // A kept piece in final form.
 template <typename T>

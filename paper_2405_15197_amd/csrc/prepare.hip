@@ -466,8 +466,9 @@ __global__ void __launch_bounds__(kBlock) k_sizes_tiles(SizesParams P)
         if (nodes && dst2) dst2 += col * (N + 1);
         // Through LDS, so that neighbouring lanes load and store neighbouring
         // elements while each thread sums eight in a row (BCC 64^3: 56 -> 21
-        // us).  A tile's sum fits 32 bits: at most kAcapBig = 192 arcs of 4,096
-        // segments at either end of each of its 2,048 struts, 3.2e9.
+        // us).  A tile's sum fits 32 bits: the most are band triangles, one per
+        // segment of at most kAcapBig arcs at either end of each strut.
+        static_assert(2ull * kAcapBig * kMaxK * kTile < 1ull << 32, "a tile's sum in 32 bits");
         __shared__ uint32_t s_v[kTile + kTile / kScanItems];
         auto slot = [](int i) { return i + i / kScanItems; };
         const int64_t base = (int64_t)blockIdx.x * kTile;
