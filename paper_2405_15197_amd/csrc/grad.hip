@@ -593,7 +593,11 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         const float hc[3] = {__uint_as_float(RH[3 * c]), __uint_as_float(RH[3 * c + 1]), __uint_as_float(RH[3 * c + 2])};
         const float sum[3] = {sm.hole[c][0], sm.hole[c][1], sm.hole[c][2]}, cnt = sm.hole[c][3];
         const float sl = sqrtf(dotf(sum, sum));
-        const bool use_b = sl >= 1e-3f * rho * cnt;
+        // One strut: the hole is its whole circle, the barycentre rho sigma e,
+        // and the direction is e's whatever sigma is; through the barycentre
+        // rounding grows by 1 / sigma (radii alike to 1e-3: 1 % of the
+        // gradient).
+        const bool use_b = v > 1 && sl >= 1e-3f * rho * cnt;
         // dir = sgn b / |b|, or -sgn se / |se|: the sign is that of the
         // forward pass's centre
         float base[3], len = sl;
