@@ -410,8 +410,41 @@ __device__ inline float wave_sum(float x)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
-__device__ inline float dotf(const float *a, const float *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
-__device__ inline void crs(const float *a, const float *b, float *c)
+template <int CTRL, int ROWS = 0xf>
+__device__ inline double dpp_add(double x)
+{
+    return x + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, true),
+                                __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, true));
+}
+__device__ inline double wave_sum(double x)
+{
+    x = dpp_add<0x111>(x);
+    x = dpp_add<0x112>(x);
+    x = dpp_add<0x114>(x);
+    x = dpp_add<0x118>(x);
+    x = dpp_add<0x142, 0xa>(x);
+    x = dpp_add<0x143, 0xc>(x);
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                            __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+
+// 1 / x and 1 / sqrt(x) to some 48 bits: the hardware's estimate of 24, one
+// Newton step
+__device__ inline double rcp64(double x)
+{
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ inline double rsq64(double x)
+{
+    const double r = __builtin_amdgcn_rsq(x);
+    return fma(fma(-x * r, r, 1.0), 0.5 * r, r);
+}
+
+template <typename A, typename B>
+__device__ inline auto dotf(const A *a, const B *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
+template <typename A, typename B, typename C>
+__device__ inline void crs(const A *a, const B *b, C *c)
 {
     c[0] = a[1] * b[2] - a[2] * b[1];
     c[1] = a[2] * b[0] - a[0] * b[2];
@@ -461,8 +494,10 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
     const float4 c4 = W.node4[n];
     const float rho = c4.w;
     const float *L = P.dldx + 3 * moff;
-    // adjoint of this node's x, y, z and radius: this lane's share
-    float own[4] = {0.f, 0.f, 0.f, 0.f};
+    // adjoint of this node's x, y, z and radius: this lane's share.  The
+    // radius's terms all but cancel: added up in FP64.
+    float own[3] = {0.f, 0.f, 0.f};
+    double own_r = 0.0;
 
     // ---- strut table, vertices, arcs ---------------------------------------
     if (lane < v) {
@@ -616,7 +651,7 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         float dir[3], mu[3];
         for (int d = 0; d < 3; ++d) dir[d] = sgn * base[d] / len;
         const float dl = dotf(dir, lh);
-        own[3] += dl;  // apex rho * dir
+        own_r += dl;  // apex rho * dir
         for (int d = 0; d < 3; ++d) mu[d] = sgn * rho * (lh[d] - dir[d] * dl) / len;
         for (int d = 0; d < 3; ++d) {
             // the sum's length is cnt |b|, so this is 1 / cnt per vertex
@@ -695,117 +730,110 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         // square) are recomputed, then their adjoints taken in reverse order.
         // Inputs: g_p, h_p, g_q, h_q and rho (kappa_p and sigma_p follow from
         // g_p, h_p and rho, so 1 - |in-plane g_p|^2 = (g_p . n)^2 - (h_p / rho)^2).
-        const SL<float> &Sp = S[p], &Sq = S[q];
-        const float gp[3] = {Sp.gx, Sp.gy, Sp.gz}, gq[3] = {Sq.gx, Sq.gy, Sq.gz};
-        const float hp = Sp.h, hq = Sq.h;
-        float nv[3], nh[3];
-        for (int d = 0; d < 3; ++d) nv[d] = gp[d] - gq[d];
-        const float inn = 1.f / sqrtf(dotf(nv, nv));
-        for (int d = 0; d < 3; ++d) nh[d] = nv[d] * inn;
-        const float d0 = (hp - hq) * inn;
-        const float gpn = dotf(gp, nh);
-        const float epn = fabsf(gpn * Sp.kap), as = fabsf(Sp.sig);
-        const float om = (epn - as) * (epn + as) / (Sp.kap * Sp.kap);
-        if (!(om > 0.f)) {  // not an ellipse: the forward pass kept no arc of it
-            for (int f = 0; f < 8; ++f) sm.arc[j][f] = 0.f;
-            continue;
-        }
-        const float iom = 1.f / om;
-        float gam[3], u1[3], tv[3] = {0.f, 0.f, 0.f};
-        for (int d = 0; d < 3; ++d) gam[d] = gp[d] - nh[d] * gpn;
-        const float gl = sqrtf(dotf(gam, gam));
-        const bool axis_from_g = gl > 1e-4f * sqrtf(dotf(gp, gp));
+        // In FP64 from the FP32 record and table: what is left of a node's
+        // radius gradient are small differences of these terms (cubic 9^3, k =
+        // 10: error 2.9e-7 of its norm, with FP32 here and in own_r 3.3e-7; octet
+        // 32^3: kernel 404 -> 420 us).
         // u1 is the record's own, a / |a|: computed again it turns by a rounding
         // over |gam|, and with it the frame that a, b and their adjoints are in
         // (two struts 2.2e-4 from in line: gradient off by 1.4e-3 of the sum of
         // all |lambda| instead of 2e-6).
-        const float ia = 1.f / sqrtf(dotf(a[t], a[t]));
-        for (int d = 0; d < 3; ++d) u1[d] = a[t][d] * ia;
-        float il = 1.f / gl;  // 1 / length of the vector that u1 was normalised from
-        if (!axis_from_g) {
-            float x[3];
-            tv[fabsf(nh[0]) < 0.9f ? 0 : 1] = 1.f;
-            crs(nh, tv, x);
-            il = 1.f / sqrtf(dotf(x, x));
+        const SL<float> &Sp = S[p], &Sq = S[q];
+        const double gp[3] = {Sp.gx, Sp.gy, Sp.gz}, hp = Sp.h, ir = rcp64((double)rho);
+        const double nv[3] = {gp[0] - Sq.gx, gp[1] - Sq.gy, gp[2] - Sq.gz};
+        const double inn = rsq64(dotf(nv, nv));
+        double nh[3], gam[3], u1[3], tv[3] = {0.0, 0.0, 0.0};
+        for (int d = 0; d < 3; ++d) nh[d] = nv[d] * inn;
+        const double d0 = (hp - Sq.h) * inn, gpn = dotf(gp, nh), hr = hp * ir;
+        const double om = gpn * gpn - hr * hr;
+        for (int d = 0; d < 3; ++d) u1[d] = a[t][d];
+        const double a2 = dotf(u1, u1);
+        if (!(om > 0.0) || !(a2 > 0.0)) {  // not an ellipse: the forward pass kept no arc of it
+            for (int f = 0; f < 8; ++f) sm.arc[j][f] = 0.f;
+            continue;
         }
-        const float k0 = d0 * gpn - hp;
-        const float al0 = gl * k0 * iom;
-        const float R2 = rho * rho - d0 * d0 + k0 * k0 * iom;
-        const float Rr = sqrtf(fmaxf(R2, 0.f)), isom = 1.f / sqrtf(om), A = Rr * isom;
-        float cv[3];
+        const double iom = rcp64(om), ia = rsq64(a2);
+        for (int d = 0; d < 3; ++d) {
+            u1[d] *= ia;
+            gam[d] = gp[d] - nh[d] * gpn;
+        }
+        const double gl2 = dotf(gam, gam), igl = gl2 > 0.0 ? rsq64(gl2) : 0.0, gl = gl2 * igl;
+        const bool axis_from_g = gl2 > 1e-8 * dotf(gp, gp);
+        double il = igl;  // 1 / length of the vector that u1 is normalised from
+        if (!axis_from_g) {
+            double x[3];
+            tv[fabs(nh[0]) < 0.9 ? 0 : 1] = 1.0;
+            crs(nh, tv, x);
+            il = rsq64(dotf(x, x));
+        }
+        const double k0 = d0 * gpn - hp, ko = k0 * iom, al0 = gl * ko;
+        const double R2 = (double)rho * rho - d0 * d0 + k0 * ko;
+        const double iR = R2 > 0.0 ? rsq64(R2) : 0.0, Rr = R2 * iR, isom = rsq64(om), A = Rr * isom;
+        double cv[3];
         crs(u1, nh, cv);
         // o = d0 nh + al0 u1, a = A u1, b = R (u1 x nh)
         const float *Lo = acc[t], *La = acc[t] + 3, *Lb = acc[t] + 6;
-        float L_nh[3], L_u1[3], L_c[3], tmp[3];
+        double L_nh[3], L_u1[3], L_c[3], tmp[3];
         for (int d = 0; d < 3; ++d) {
             L_nh[d] = Lo[d] * d0;
             L_u1[d] = Lo[d] * al0 + La[d] * A;
             L_c[d] = Lb[d] * Rr;
         }
-        float L_d0 = dotf(Lo, nh), L_al0 = dotf(Lo, u1), L_A = dotf(La, u1), L_R = dotf(Lb, cv);
+        double L_d0 = dotf(Lo, nh);
+        const double L_al0 = dotf(Lo, u1), L_A = dotf(La, u1), L_R = dotf(Lb, cv) + L_A * isom;
         crs(nh, L_c, tmp);
         for (int d = 0; d < 3; ++d) L_u1[d] += tmp[d];
         crs(L_c, u1, tmp);
         for (int d = 0; d < 3; ++d) L_nh[d] += tmp[d];
         // A = R / sqrt(om), R = sqrt(max(R2, 0))
-        L_R += L_A * isom;
-        float L_om = -0.5f * L_A * A * iom;
-        const float L_R2 = Rr > 0.f ? 0.5f * L_R / Rr : 0.f;
+        double L_om = -0.5 * L_A * A * iom;
+        const double L_R2 = 0.5 * L_R * iR;
         // R2 = rho^2 - d0^2 + k0^2 / om, al0 = gl k0 / om, k0 = d0 gpn - hp
-        const float ko = k0 * iom;
-        float L_rho = 2.f * rho * L_R2;
-        L_d0 -= 2.f * d0 * L_R2;
-        float L_k0 = 2.f * ko * L_R2;
-        L_om -= ko * ko * L_R2;
-        const float L_gl = ko * L_al0;
-        L_k0 += gl * iom * L_al0;
-        L_om -= al0 * iom * L_al0;
+        double L_rho = 2.0 * rho * L_R2;
+        L_d0 -= 2.0 * d0 * L_R2;
+        const double L_gl = ko * L_al0, L_k0 = 2.0 * ko * L_R2 + gl * iom * L_al0;
+        L_om -= ko * ko * L_R2 + al0 * iom * L_al0;
         L_d0 += gpn * L_k0;
-        float L_gpn = d0 * L_k0, L_hp = -L_k0;
+        double L_gpn = d0 * L_k0, L_hp = -L_k0;
         // u1: gam / |gam| (the re-projection and renormalisation have zero
         // derivative: u1 stays a unit vector in the plane), else the unit
         // vector along nh x t
-        float L_gam[3] = {0.f, 0.f, 0.f};
-        const float uu = dotf(u1, L_u1);
+        double L_gam[3];
+        const double uu = dotf(u1, L_u1);
+        for (int d = 0; d < 3; ++d) L_gam[d] = gam[d] * (L_gl * igl);
+        for (int d = 0; d < 3; ++d) L_u1[d] = (L_u1[d] - u1[d] * uu) * il;
         if (axis_from_g) {
-            for (int d = 0; d < 3; ++d) L_gam[d] = (gam[d] * L_gl + (L_u1[d] - u1[d] * uu)) * il;
+            for (int d = 0; d < 3; ++d) L_gam[d] += L_u1[d];
         } else {
-            float Pm[3];
-            if (gl > 0.f)
-                for (int d = 0; d < 3; ++d) L_gam[d] = gam[d] * (L_gl / gl);
-            for (int d = 0; d < 3; ++d) Pm[d] = (L_u1[d] - u1[d] * uu) * il;
-            crs(tv, Pm, tmp);
+            crs(tv, L_u1, tmp);
             for (int d = 0; d < 3; ++d) L_nh[d] += tmp[d];
         }
         // gam = g_p - nh gpn
-        float L_gp[3];
-        const float gn = dotf(L_gam, nh);
+        double L_gp[3];
+        L_gpn -= dotf(L_gam, nh);
         for (int d = 0; d < 3; ++d) {
             L_gp[d] = L_gam[d];
             L_nh[d] -= gpn * L_gam[d];
         }
-        L_gpn -= gn;
         // om = gpn^2 - (h_p / rho)^2
-        const float ir2 = 1.f / (rho * rho);
-        L_gpn += 2.f * gpn * L_om;
-        L_hp -= 2.f * hp * ir2 * L_om;
-        L_rho += 2.f * hp * hp * ir2 / rho * L_om;
+        L_gpn += 2.0 * gpn * L_om;
+        L_hp -= 2.0 * hr * ir * L_om;
+        L_rho += 2.0 * hr * hr * ir * L_om;
         // gpn = g_p . nh
         for (int d = 0; d < 3; ++d) {
             L_gp[d] += nh[d] * L_gpn;
             L_nh[d] += gp[d] * L_gpn;
         }
         // d0 = (h_p - h_q) / |n|, nh = n / |n|, n = g_p - g_q
-        const float L_dn = L_d0 * inn, L_nn = -d0 * L_dn;
-        const float nl = dotf(nh, L_nh);
+        const double L_dn = L_d0 * inn, L_nn = -d0 * L_dn - dotf(nh, L_nh) * inn;
         for (int d = 0; d < 3; ++d) {
-            const float L_n = (L_nh[d] - nh[d] * nl) * inn + nh[d] * L_nn;
-            sm.arc[j][d] = L_gp[d] + L_n;
-            sm.arc[j][4 + d] = -L_n;
+            const double L_n = L_nh[d] * inn + nh[d] * L_nn;
+            sm.arc[j][d] = (float)(L_gp[d] + L_n);
+            sm.arc[j][4 + d] = (float)-L_n;
         }
-        sm.arc[j][3] = L_hp + L_dn;
-        sm.arc[j][7] = -L_dn;
-        own[3] += L_rho;
+        sm.arc[j][3] = (float)(L_hp + L_dn);
+        sm.arc[j][7] = (float)-L_dn;
+        own_r += L_rho;
     }
     __syncthreads();
 
@@ -854,7 +882,7 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         sm.vert[i][2] = mu2;
         for (int d = 0; d < 3; ++d) sm.vert[i][3 + d] = w[d];
         sm.vert[i][6] = -1.f;
-        own[3] += 2.f * rho * mu4;
+        own_r += 2.f * rho * mu4;
     }
     __syncthreads();
 
@@ -900,7 +928,7 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         // h = rho sigma / kappa, g = e / kappa, kappa = sqrt(1 - sigma^2)
         const float l_kap = rho * lab - (dotf(gh, g) + lh * s.h) * ik;
         const float l_sig = rho * lo_e + (lh * rho - l_kap * s.sig) * ik;
-        own[3] += s.sig * lo_e + s.kap * lab + lh * s.sig * ik + l_sig * iL;
+        own_r += s.sig * lo_e + s.kap * lab + lh * s.sig * ik + l_sig * iL;
         // frame: r = es x axis / |es x axis|, q = es x r
         const float ax = fabsf(es[0]), ay = fabsf(es[1]), az = fabsf(es[2]);
         const int ja = ay < ax ? (az < ay ? 2 : 1) : (az < ax ? 2 : 0);
@@ -928,8 +956,9 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         }
         out[3] = -l_sig * iL;
     }
-    for (int d = 0; d < 4; ++d) own[d] = wave_sum(own[d]);
-    if (lane == 0) *(float4 *)(W.grad_node + 4 * n) = make_float4(own[0], own[1], own[2], own[3]);
+    for (int d = 0; d < 3; ++d) own[d] = wave_sum(own[d]);
+    own_r = wave_sum(own_r);
+    if (lane == 0) *(float4 *)(W.grad_node + 4 * n) = make_float4(own[0], own[1], own[2], (float)own_r);
 }
 
 // nodes of up to kVmax struts, one block (wave) each
