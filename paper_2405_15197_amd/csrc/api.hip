@@ -66,6 +66,7 @@ struct lm_plan {
     int64_t cls_est[4];        // nodes per valence class when the plan was made (grid sizes only)
     bool has_cls_est = false;
     int k;          // resolution of the last count (0: none)
+    int mesh_k = 0; // resolution of the mesh in the current records
     float kappa_max;// FP32 -> FP64 hand-over threshold
     lm_totals last; // totals of the last lm_count
     bool last_on_host = false;  // `last` describes the current mesh (lm_count ran last)
@@ -733,7 +734,7 @@ int lm_count(lm_plan *P, int k, lm_totals *totals)
         if ((rc = ensure_rec(P, totals->n_record_bytes / 4 + totals->n_record_bytes / 64))) return rc;
     }
     if (fl & lm::DF_RECCAP) return LM_ERR_INTERNAL;
-    P->k = k;
+    P->k = P->mesh_k = k;
     P->base_slot = 0;
     P->last = *totals;
     P->last_on_host = true;
@@ -762,7 +763,7 @@ int lm_forward(lm_plan *P, int k, const lm_outputs *out)
     if (P->w.rec_words == 0 && (rc = ensure_rec(P, rec_estimate(P, k)))) return rc;
     rc = run_count(P, k, &f, to_offsets(out), P->w);
     if (rc) return rc;
-    P->k = k;
+    P->k = P->mesh_k = k;
     P->base_slot = 0;
     P->last_on_host = false;
     return fill_common(P, k, f, P->w);
@@ -806,7 +807,7 @@ int lm_loss(lm_plan *P, const lm_outputs *out, const lm_loss_weights *w, double 
     lm::FillOut f = to_fill(out);
     PhaseTimer t(P, PH_LOSS);
     HIPCHK(lm::launch_loss(P->in, P->w, f, make_float3(w->p0[0], w->p0[1], w->p0[2]), w->area, w->volume, w->sq_norm,
-                           d_dl_dx, d_terms, P->st));
+                           P->mesh_k, d_dl_dx, d_terms, P->st));
     return LM_OK;
 }
 
@@ -1130,6 +1131,7 @@ int lm_retriangulate(lm_plan *P, int k, const lm_outputs *out)
         std::swap(P->w.rec_top, P->alt_rec_top);
         P->base_slot = 1;
     }
+    P->mesh_k = k;
     P->last_on_host = false;
     return LM_OK;
 }

@@ -62,11 +62,12 @@ __device__ inline void add3(float *p, float3 v, float s)
 // unit's LDS per instruction.)  The bands' bookkeeping is read for all struts
 // at once, a lane per strut.  Octet 32^3, k = 16: 1.45 -> 0.62 ms.
 //
-// kLossLds vertices at a time; a node with more of them takes up to
-// kLossPasses passes over its triangles, beyond that it adds through global
-// atomics.
-constexpr int kLossLds = 512;
-constexpr int kLossPasses = 4;
+// LDS vertices at a time; a node with more of them passes over its triangles
+// again, up to kLossMost vertices, beyond that it adds through global atomics.
+// Room for 512 lets 25 waves onto a compute unit, for 1,024 twelve, which
+// spares nodes of 513 to 1,024 vertices the second pass: see launch_loss.
+constexpr int kLossMost = 2048;
+constexpr int kLossSmall = 512, kLossLarge = 1024;
 
 struct LParams {
     Inputs in;
@@ -100,9 +101,10 @@ __global__ void k_loss_rest(LParams P)
         P.dldx[i] = 0.f;
 }
 
+template <int LDS>
 __global__ void __launch_bounds__(64) k_loss_node(LParams P)
 {
-    __shared__ float gx[kLossLds], gy[kLossLds], gz[kLossLds];
+    __shared__ float gx[LDS], gy[LDS], gz[LDS];
     const Work &W = P.w;
     const int64_t N = P.in.n_nodes, S = P.in.n_struts;
     const int64_t n = blockIdx.x;
@@ -138,8 +140,8 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
         my_nb = (int)(W.band_off[he.y + 1] - my_b0);
     }
     double area = 0.0, vol = 0.0, sq = 0.0;
-    const bool lds = M <= kLossLds * kLossPasses;
-    int c0 = 0;  // vertices [c0, c0 + kLossLds) of the node are in LDS
+    const bool lds = M <= kLossMost;
+    int c0 = 0;  // vertices [c0, c0 + LDS) of the node are in LDS
     // a triangle and its normal; its terms when counted (area twice, volume
     // six times what they are: scaled once per node)
     struct Tri {
@@ -177,7 +179,7 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
     // place of a vertex in LDS, -1: not the node's, or of another pass
     auto place = [&](int32_t vi) {
         const uint32_t i = (uint32_t)vi - (uint32_t)(m0 + c0);
-        return i < (uint32_t)(M - c0 < kLossLds ? M - c0 : kLossLds) ? (int)i : -1;
+        return i < (uint32_t)(M - c0 < LDS ? M - c0 : LDS) ? (int)i : -1;
     };
     // adds of one step go to distinct places
     auto add = [&](int i, float3 d) {
@@ -199,9 +201,9 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
         for (int64_t i = 3 * m0 + lane; i < 3 * m1; i += 64) P.dldx[i] = 0.f;
         __threadfence();
     }
-    for (c0 = 0; c0 < M; c0 += lds ? kLossLds : M) {
+    for (c0 = 0; c0 < M; c0 += lds ? LDS : M) {
         const bool first = c0 == 0;
-        const int mc = M - c0 < kLossLds ? M - c0 : kLossLds;
+        const int mc = M - c0 < LDS ? M - c0 : LDS;
         if (lds)
             for (int i = lane; i < mc; i += 64) gx[i] = gy[i] = gz[i] = 0.f;
         __syncthreads();
@@ -1040,7 +1042,7 @@ constexpr int64_t kBigGridBwd = 1024;  // blocks of k_backward_big
 }  // namespace
 
 hipError_t launch_loss(const Inputs &in, const Work &w, const FillOut &o, float3 p0, float w_area, float w_vol,
-                       float w_sq, float *dldx, double *terms, hipStream_t st)
+                       float w_sq, int k, float *dldx, double *terms, hipStream_t st)
 {
     if (in.n_nodes == 0) {
         k_zero_d<<<1, 64, 0, st>>>(terms, 3);
@@ -1064,7 +1066,18 @@ hipError_t launch_loss(const Inputs &in, const Work &w, const FillOut &o, float3
         const unsigned g = grid_for(3 * o.cap_mesh);
         k_loss_rest<<<g < 2048 ? g : 2048, kBlock, 0, st>>>(P);
     }
-    k_loss_node<<<(unsigned)in.n_nodes, 64, 0, st>>>(P);
+    // Which room: a node of v struts has about v (k + 5) / 2 vertices.  The
+    // larger where the mean node needs it (us, 512 / 1,024: cubic 20^3 at k =
+    // 200, 580 vertices, 288 / 218; BCC 16^3 at 200, 740, 387 / 302; octet 14^3 at
+    // 128, 740, 437 / 425; but at k = 64, 390, 147 / 230, and at 200, 1,150, 939 /
+    // 1,004), and where all blocks fit the chip at once anyway, so that the last
+    // node's second pass is what the others wait for (9-NN 14^3, the mean below
+    // 512 but up to 589, 877, 1,164 at k = 64, 96, 128: 120 / 77, 171 / 101, 278 /
+    // 194; at k = 16 and 32 no difference).
+    const double mean = (double)in.n_struts / (double)in.n_nodes * (k + 5);
+    const bool large = (mean > kLossSmall && mean <= kLossLarge) || in.n_nodes <= 256 * 12;
+    if (large) k_loss_node<kLossLarge><<<(unsigned)in.n_nodes, 64, 0, st>>>(P);
+    else k_loss_node<kLossSmall><<<(unsigned)in.n_nodes, 64, 0, st>>>(P);
     double *partial = w.loss_node + 3 * (in.n_nodes + 1);  // kLossParts x 3 after the node terms
     k_loss_partial<<<kLossParts, kBlock, 0, st>>>(in.n_nodes, w.loss_node, partial);
     k_loss_reduce<<<1, kBlock, 0, st>>>(partial, terms);
