@@ -111,7 +111,7 @@ __device__ inline void sph(D3 v, double &r, double &th, double &ph)
     if (ph < 0.0) ph = ph + 2.0 * kPi;
 }
 // sin and cos of quarter turn k plus x, |x| <= pi / 4, by their series
-// (the first term left out is below 1e-18)
+// (the first terms left out are below 1e-19 and 2.1e-18)
 __device__ inline void sincos_at(int k, double x, double &s, double &c)
 {
     constexpr double S[8] = {-1.0 / 6,          1.0 / 120,           -1.0 / 5040,           1.0 / 362880,

@@ -1470,9 +1470,10 @@ __device__ __forceinline__ void node_body(const Params &P, Shared<T, CF> &sh, co
     // (18 of 36 at a BCC node) and come from every round: one pass, one piece
     // per lane, and no trimming state held across it.  Finishing each round's
     // conics in place, with every lane ready for the most pieces, took 168
-    // VGPRs in FP32 and all 256 in FP64, with spills; now 139 and 186, no
-    // spills.  BCC 64^3, k = 16: step 4.21 -> 3.94 ms; sink BCC 128^3, k = 12:
-    // 29.0 -> 26.7 ms; 24 mixed parts, mostly FP64: 3.47 -> 3.18 ms.
+    // VGPRs in FP32 and all 256 in FP64, with spills; with this change 139 and
+    // 186 and none (FP32 has been held to 128 since: see k_node32).  BCC 64^3, k
+    // = 16: step 4.21 -> 3.94 ms; sink BCC 128^3, k = 12: 29.0 -> 26.7 ms; 24 mixed
+    // parts, mostly FP64: 3.47 -> 3.18 ms.
     {
         constexpr bool ONE = CF::AC <= WL;  // a lane has at most one arc
         const int E = sh.n_arc;
@@ -2131,9 +2132,12 @@ __device__ inline int drain_class(const Params &P, int cls, Shared<float, C> *sh
 // At most 128 VGPRs and 10,240 bytes of LDS per block: four waves per SIMD.
 // The pass is bound by vector issue, at three waves 77 % of the peak with LDS
 // and scalar chains to wait for.  Three waves (12.5 KB; LDS is given out in
-// 1,280-byte pieces) against four, six registers spilled: BCC 64^3, k = 16,
-// step 3.84 -> 3.37 ms; sink BCC 128^3, k = 12, 26.4 -> 22.3 ms; octet 32^3
-// forward + adjoint 4.20 -> 4.04 ms.
+// 1,280-byte pieces) against four: BCC 64^3, k = 16, step 3.84 -> 3.37 ms; sink
+// BCC 128^3, k = 12, 26.4 -> 22.3 ms; octet 32^3 forward + adjoint 4.20 -> 4.04
+// ms (with 9..16 in a launch of their own).  Meshing and the redo list spill 16
+// registers as it is now (64 bytes of scratch a lane), sink mode 8 (32),
+// re-subdivision none: BCC 64^3 reads 0.77 GB instead of the 0.22 of the same
+// code held to three waves, which spills nothing.
 //
 // The one-wave classes, 9..kVmax struts, 5..8 (two nodes per wave) and up to 4
 // (four), in one persistent launch, the heavier first: the lighter nodes fill
