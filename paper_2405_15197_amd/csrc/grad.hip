@@ -161,12 +161,15 @@ __global__ void __launch_bounds__(64) k_loss_node(LParams P)
         T.a = sub3(f3(P.xyz + 3 * (int64_t)T.i0), P.p0);
         T.b = sub3(f3(P.xyz + 3 * (int64_t)T.i1), P.p0);
         T.c = sub3(f3(P.xyz + 3 * (int64_t)T.i2), P.p0);
-        T.n = crs3(sub3(T.b, T.a), sub3(T.c, T.a));
+        // the normal from the first end of the edge, of the edge and of a side:
+        // of the two sides from the apex it would be a small difference
+        const float3 q0 = turn ? T.b : T.a, q1 = turn ? T.c : T.b, q2 = turn ? T.a : T.c;
+        T.n = crs3(sub3(q1, q0), sub3(q2, q0));
         const float nl = sqrtf(T.n.x * T.n.x + T.n.y * T.n.y + T.n.z * T.n.z);
         if (count) {
-            const float3 bc = crs3(T.b, T.c);
+            const float3 x = crs3(q1, q2);
             area += (double)nl;
-            vol += (double)T.a.x * bc.x + (double)T.a.y * bc.y + (double)T.a.z * bc.z;
+            vol += (double)q0.x * x.x + (double)q0.y * x.y + (double)q0.z * x.z;
         }
         T.wa = (P.w_area != 0.f && nl > 0.f) ? 0.5f * P.w_area / nl : 0.f;
         return T;
