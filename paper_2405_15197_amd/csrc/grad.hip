@@ -847,6 +847,10 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
     // F3 = g_p . w - h_p - s, F4 = |w|^2 - rho^2 - s^2 (label 0: g = 0, h = 0).
     // J^T mu = (lam_w, 0) gives mu3 = -2 s mu4 and
     // [n1 | n2 | 2 (w - s g_p)] (mu1, mu2, mu4) = lam_w.
+    // In FP64: in FP32 the solve's own rounding, grown by the tie's condition, is
+    // what the least well conditioned nodes of a lattice leave in its gradient
+    // (cubic 9^3, k = 10, radius gradient, the worst of 60: error 11.4e-7 of its
+    // norm, 4.3e-7 so; octet 32^3: kernel +4 us).
 #pragma unroll
     for (int t = 0; t < NV; ++t) {
         const int i = lane + 64 * t;
@@ -854,40 +858,38 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         const uint4 vw = sm.v[i];
         const int p = (int)(vw.x >> 24), q = (int)((vw.x >> 16) & 0xffu), r = (int)((vw.x >> 8) & 0xffu);
         if (r == 0xff) continue;  // start point of a whole conic (handled with its arc)
-        const float w[3] = {__uint_as_float(vw.y), __uint_as_float(vw.z), __uint_as_float(vw.w)};
-        float gp[3] = {0.f, 0.f, 0.f}, gq[3], gr[3];
-        float hp = 0.f;
+        const double w[3] = {__uint_as_float(vw.y), __uint_as_float(vw.z), __uint_as_float(vw.w)};
+        double gp[3] = {0.0, 0.0, 0.0}, hp = 0.0;
         if (p) {
             gp[0] = S[p].gx; gp[1] = S[p].gy; gp[2] = S[p].gz;
             hp = S[p].h;
         }
-        gq[0] = S[q].gx; gq[1] = S[q].gy; gq[2] = S[q].gz;
-        gr[0] = S[r].gx; gr[1] = S[r].gy; gr[2] = S[r].gz;
-        const float s = dotf(gp, w) - hp;
-        float n1[3], n2[3], n3[3], lw[3];
+        const double gq[3] = {S[q].gx, S[q].gy, S[q].gz}, gr[3] = {S[r].gx, S[r].gy, S[r].gz};
+        const double s = dotf(gp, w) - hp;
+        double n1[3], n2[3], n3[3], lw[3];
         for (int d = 0; d < 3; ++d) {
             n1[d] = gp[d] - gq[d];
             n2[d] = gp[d] - gr[d];
-            n3[d] = 2.f * (w[d] - s * gp[d]);
-            lw[d] = L[3 * i + d] + sm.vert[i][d] + sm.vert[i][3 + d] + sm.vert[i][6 + d];
+            n3[d] = 2.0 * (w[d] - s * gp[d]);
+            lw[d] = (double)L[3 * i + d] + sm.vert[i][d] + sm.vert[i][3 + d] + sm.vert[i][6 + d];
         }
         // Cramer on columns n1, n2, n3
-        float x23[3], x31[3], x12[3];
+        double x23[3], x31[3], x12[3];
         crs(n2, n3, x23);
         crs(n3, n1, x31);
         crs(n1, n2, x12);
-        const float idt = 1.f / dotf(n1, x23);
-        const float mu1 = dotf(lw, x23) * idt;
-        const float mu2 = dotf(lw, x31) * idt;
-        const float mu4 = dotf(lw, x12) * idt;
-        const float mu3 = -2.f * s * mu4;
+        const double idt = rcp64(dotf(n1, x23));
+        const double mu1 = dotf(lw, x23) * idt;
+        const double mu2 = dotf(lw, x31) * idt;
+        const double mu4 = dotf(lw, x12) * idt;
+        const double mu3 = -2.0 * s * mu4;
         // dL/dtheta = -mu^T dF/dtheta: label m's g gets weight * w, its h -weight
-        sm.vert[i][0] = -(mu1 + mu2 + mu3);
-        sm.vert[i][1] = mu1;
-        sm.vert[i][2] = mu2;
-        for (int d = 0; d < 3; ++d) sm.vert[i][3 + d] = w[d];
+        sm.vert[i][0] = (float)-(mu1 + mu2 + mu3);
+        sm.vert[i][1] = (float)mu1;
+        sm.vert[i][2] = (float)mu2;
+        for (int d = 0; d < 3; ++d) sm.vert[i][3 + d] = (float)w[d];
         sm.vert[i][6] = -1.f;
-        own_r += 2.f * rho * mu4;
+        own_r += 2.0 * rho * mu4;
     }
     __syncthreads();
 
