@@ -469,7 +469,8 @@ __device__ inline void crs(const A *a, const B *b, C *c)
 // arcs and vertices that carry its label.  (Adding through LDS atomics, some
 // 50 instructions of 60 cycles of the compute unit's LDS each, the kernel
 // kept that unit busy for 82 % of its time.)  The strut table is taken in
-// reverse too, a lane per strut.  Octet 32^3, k = 16: 654 -> 401 us.
+// reverse too, a lane per strut.  Octet 32^3, k = 16: 654 -> 401 us,
+// 420 with the parts that are in FP64.
 template <int VM, int AC, int VC>
 __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const int64_t n)
 {
@@ -738,7 +739,7 @@ __device__ void backward_node(const BParams &P, BwdLds<VM, AC, VC> &sm, const in
         // In FP64 from the FP32 record and table: what is left of a node's
         // radius gradient are small differences of these terms (cubic 9^3, k =
         // 10: error 2.9e-7 of its norm, with FP32 here and in own_r 3.3e-7; octet
-        // 32^3: kernel 404 -> 420 us).
+        // 32^3: kernel 400 -> 416 us).
         // u1 is the record's own, a / |a|: computed again it turns by a rounding
         // over |gam|, and with it the frame that a, b and their adjoints are in
         // (two struts 2.2e-4 from in line: gradient off by 1.4e-3 of the sum of
