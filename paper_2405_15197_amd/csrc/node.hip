@@ -661,19 +661,19 @@ __device__ inline void split_steps(TrimRun<T> &st, T lo, T code, R &&label, std:
 template <typename T>
 __device__ inline T kept_code(int kind, T lc) { return kind == 2 ? lc : (kind ? (T)-1 : (T)8); }
 
-// Conic point at the direction (sin t, cos t) ~ (s, c).  FP32: the products
-// are fused by hand, so that every schedule of the node pass rounds alike.
+// Conic point at the direction (sin t, cos t) ~ (s, c).  The products are fused
+// by hand: in FP32 so that every schedule of the node pass rounds alike, in
+// FP64 because the last bit decides ties (planar lattices: the points in the
+// plane), which would fall as the compiler happens to fuse.
 template <typename T>
 __device__ inline V3<T> conic_dir(const Con<T> &C, T s, T c)
 {
-    if constexpr (sizeof(T) == 4) {
-        const T inv = __builtin_amdgcn_rsqf(fmaf(c, c, s * s)), u = s * inv, w = c * inv;
-        return v3(fmaf(C.b.x, w, fmaf(C.a.x, u, C.o.x)), fmaf(C.b.y, w, fmaf(C.a.y, u, C.o.y)),
-                  fmaf(C.b.z, w, fmaf(C.a.z, u, C.o.z)));
-    } else {
-        const T inv = (T)1 / m_sqrt(s * s + c * c);
-        return C.o + C.a * (s * inv) + C.b * (c * inv);
-    }
+    T inv;
+    if constexpr (sizeof(T) == 4) inv = __builtin_amdgcn_rsqf(fmaf(c, c, s * s));
+    else inv = (T)1 / m_sqrt(fma(s, s, c * c));
+    const T u = s * inv, w = c * inv;
+    return v3(fma(C.b.x, w, fma(C.a.x, u, C.o.x)), fma(C.b.y, w, fma(C.a.y, u, C.o.y)),
+              fma(C.b.z, w, fma(C.a.z, u, C.o.z)));
 }
 
 // Start t1 in [0, 2 pi) and span dt of a kept piece of pseudo length len
