@@ -31,12 +31,12 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 # by the kernel's sources and build flags they were taken on; a changed
 # kernel reports null.
 MEASURED_TRAFFIC = {
-    "135239f2d51b6e63": {"bytes": 2_933_124_000, "summary": "profiles/k_node32_bcc64_k16_hbm_counters.md"},
+    "2182b8d8ecae44be": {"bytes": 2_932_729_000, "summary": "profiles/k_node32_bcc64_k16_hbm_counters.md"},
 }
 # wave64 VALU instructions per node pass (SQ_INSTS_VALU summed over its
 # launches) from the same counter runs, keyed the same way
 MEASURED_VALU = {
-    "135239f2d51b6e63": {"insts": 1_070_800_000, "summary": "profiles/k_node32_bcc64_k16_hbm_counters.md"},
+    "2182b8d8ecae44be": {"insts": 1_070_800_000, "summary": "profiles/k_node32_bcc64_k16_hbm_counters.md"},
 }
 # VALU issue peak: 256 CUs x 4 SIMDs x 2.4 GHz, one wave64 instruction per
 # SIMD every 4 cycles (16 lanes wide; packed FP32 is not used)
